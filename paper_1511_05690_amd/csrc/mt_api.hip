@@ -845,7 +845,7 @@ mt_status estimate_impl(const void* A, const void* B, mt_dtype dtype, int64_t b,
         // pass of A, and B's column maxima run in the same launch (unless the
         // domain check must come before the planes)
         fuse_rowmax = !f64 && !(f.flags & MT_FLAG_VALIDATE) && g.kp <= kFusedRowMaxK && b <= 65535 && k > 0 &&
-                      n > 0 && g.mp * b >= ((n + 1023) / 1024) * ((k + 63) / 64) * b;
+                      n > 0 && rowmax_planes_colmax_fits(b, k, n, g.mp);
         if (!fuse_rowmax) {
             MT_TRY(launch_rowmax(A, f64, b * m, k, (double*)(ws + L.r), flag, st), "row max");
             MT_TRY(launch_colmax(B, f64, b, k, n, (double*)(ws + L.c), flag, st), "column max");

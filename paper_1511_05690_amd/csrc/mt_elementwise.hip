@@ -157,61 +157,94 @@ __global__ __launch_bounds__(kThreads) void mt_rowmax_kernel(const T* __restrict
 }
 
 // c[b, j] = max_k B[b, k, j] (times mul[b, k] when kMul: the balanced column
-// maximum): each thread owns kColVec consecutive columns (one 16-byte load
-// per row when n allows it), 64 rows per block, combined with an integer
-// atomic max on the bit pattern (exact for >= 0).
+// maximum).  A block covers one wave's width of columns (kColVec per lane,
+// 16 bytes a load) and rows_blk rows, a quarter of them per wave; the four
+// waves' maxima meet in LDS and each column takes one integer atomic max on
+// the bit pattern (exact for >= 0).  Bound by latency for small inputs and by
+// HBM for large ones, so a wave keeps kColUnroll row loads in flight, also
+// where the rows are not 16-byte aligned (n no multiple of kColVec): a dword
+// aligned 16-byte load costs the same there, one load per element did not
+// (513 x 255: 33 us with element loads one row after another in the launch
+// that holds this pass, 12 us now; 2050 x 1777: 79 and 24 us).
+constexpr int kColUnroll = 16;
+template <typename T>
+constexpr int col_block_cols() { return 64 * 16 / (int)sizeof(T); }
+// Rows per block: few, so that a small input still spreads over the CUs,
+// until there are about eight blocks per CU; then four times as many, for
+// fewer atomics.
+inline int64_t col_block_rows(int64_t b, int64_t k, int64_t n, int64_t cols_blk) {
+    return b * ((n + cols_blk - 1) / cols_blk) * ((k + 63) / 64) <= 2048 ? 64 : 256;
+}
 template <typename T, bool kMul>
 __device__ __forceinline__ void colmax_block(const T* __restrict__ B, int64_t k, int64_t n, double* __restrict__ c,
                                              int32_t* __restrict__ flag, const double* __restrict__ mul,
-                                             int64_t bx, int64_t by, int64_t bz) {
+                                             int64_t rows_blk, int64_t bx, int64_t by, int64_t bz) {
     constexpr int V = 16 / sizeof(T);
-    const int64_t j0 = (bx * kThreads + threadIdx.x) * V;
-    const int64_t k0 = by * 64;
+    typedef typename std::conditional<kMul, double, T>::type M;  // the maximum of T values is exact in T
+    __shared__ M part[kThreads / 64][V][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t j0 = (bx * 64 + lane) * V;
     const int64_t bi = bz;
-    if (j0 >= n) return;
+    const int64_t per_wave = rows_blk / (kThreads / 64);
+    const int64_t k0 = by * rows_blk + wave * per_wave;
+    const int64_t k1 = k0 + per_wave < k ? k0 + per_wave : k;
     const T* bb = B + bi * k * n + j0;
-    double mx[V];
+    M mx[V];
 #pragma unroll
-    for (int q = 0; q < V; ++q) mx[q] = 0.0;
+    for (int q = 0; q < V; ++q) mx[q] = M(0);
     bool bad = false;
-    const int64_t k1 = k0 + 64 < k ? k0 + 64 : k;
-    if (j0 + V <= n && (n % V) == 0) {
-        typedef T vecT __attribute__((ext_vector_type(V)));
-#pragma unroll 8
-        for (int64_t kk = k0; kk < k1; ++kk) {
-            const vecT v = *(const vecT*)(bb + kk * n);
-            const double f = kMul ? mul[bi * k + kk] : 1.0;
+    if (j0 + V <= n) {
+        typedef T vecT __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+        for (int64_t kc = k0; kc < k1; kc += kColUnroll) {
+            vecT v[kColUnroll];
+            double f[kColUnroll];
+            // rows past the end repeat the last one
 #pragma unroll
-            for (int q = 0; q < V; ++q) {
-                bad |= bad_value(v[q]);
-                mx[q] = fmax(mx[q], kMul ? (double)v[q] * f : (double)v[q]);
+            for (int u = 0; u < kColUnroll; ++u) {
+                const int64_t kk = kc + u < k1 ? kc + u : k1 - 1;
+                v[u] = *(const vecT*)(bb + kk * n);
+                if (kMul) f[u] = mul[bi * k + kk];
             }
+#pragma unroll
+            for (int u = 0; u < kColUnroll; ++u)
+#pragma unroll
+                for (int q = 0; q < V; ++q) {
+                    bad |= bad_value(v[u][q]);
+                    mx[q] = fmax(mx[q], kMul ? (M)((double)v[u][q] * f[u]) : (M)v[u][q]);
+                }
         }
-    } else {
-        for (int64_t kk = k0; kk < k1; ++kk) {
-            const double f = kMul ? mul[bi * k + kk] : 1.0;
+    } else if (j0 < n) {
+        for (int64_t kc = k0; kc < k1; ++kc) {
+            const double f = kMul ? mul[bi * k + kc] : 1.0;
 #pragma unroll
             for (int q = 0; q < V; ++q)
                 if (j0 + q < n) {
-                    const T v = bb[kk * n + q];
+                    const T v = bb[kc * n + q];
                     bad |= bad_value(v);
-                    mx[q] = fmax(mx[q], kMul ? (double)v * f : (double)v);
+                    mx[q] = fmax(mx[q], kMul ? (M)((double)v * f) : (M)v);
                 }
         }
     }
     if (bad) atomicOr(flag, 1);
 #pragma unroll
-    for (int q = 0; q < V; ++q)
-        if (j0 + q < n && (mx[q] > 0.0 || mx[q] != mx[q]))
-            atomicMax((unsigned long long*)(c + bi * n + j0 + q), (unsigned long long)__double_as_longlong(mx[q]));
+    for (int q = 0; q < V; ++q) part[wave][q][lane] = mx[q];
+    __syncthreads();
+    // wave w finishes elements w, w + 4, ... of the columns
+    for (int q = wave; q < V; q += kThreads / 64) {
+        M m = part[0][q][lane];
+#pragma unroll
+        for (int w = 1; w < kThreads / 64; ++w) m = fmax(m, part[w][q][lane]);
+        if (j0 + q < n && m > M(0))
+            atomicMax((unsigned long long*)(c + bi * n + j0 + q), (unsigned long long)__double_as_longlong((double)m));
+    }
 }
 
 template <typename T, bool kMul = false>
 __global__ __launch_bounds__(kThreads) void mt_colmax_kernel(const T* __restrict__ B, int64_t k,
                                                              int64_t n, double* __restrict__ c,
-                                                             int32_t* __restrict__ flag,
+                                                             int32_t* __restrict__ flag, int64_t rows_blk,
                                                              const double* __restrict__ mul = nullptr) {
-    colmax_block<T, kMul>(B, k, n, c, flag, mul, blockIdx.x, blockIdx.y, blockIdx.z);
+    colmax_block<T, kMul>(B, k, n, c, flag, mul, rows_blk, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Inner-index balancing: d = sqrt(b / a) per inner index (a = largest entry
@@ -545,7 +578,7 @@ __global__ __launch_bounds__(kThreads) void mt_rowmax_planes_colmax_kernel(
     const float* __restrict__ A, int64_t rows, int64_t cols, int64_t rows_pad, int64_t cols_pad,
     double* __restrict__ r, int32_t* __restrict__ flag, PlaneSpec spec, void* __restrict__ planes,
     const float* __restrict__ B, int64_t kb, int64_t nb, double* __restrict__ c, int64_t na, int64_t nc,
-    int64_t ratio, int64_t cgx, int64_t cgy) {
+    int64_t ratio, int64_t cgx, int64_t cgy, int64_t crows) {
     __shared__ float wmax[kThreads / 64];
     const int64_t id = blockIdx.x;
     const int64_t span = nc * (ratio + 1);
@@ -558,7 +591,7 @@ __global__ __launch_bounds__(kThreads) void mt_rowmax_planes_colmax_kernel(
         a_idx = nc * ratio + (id - span);
     }
     if (c_idx >= 0) {
-        colmax_block<float, false>(B, kb, nb, c, flag, nullptr, c_idx % cgx, (c_idx / cgx) % cgy, c_idx / (cgx * cgy));
+        colmax_block<float, false>(B, kb, nb, c, flag, nullptr, crows, c_idx % cgx, (c_idx / cgx) % cgy, c_idx / (cgx * cgy));
         return;
     }
     if (a_idx < na)
@@ -784,11 +817,14 @@ hipError_t launch_colmax(const void* B, int f64, int64_t b, int64_t k, int64_t n
                          int32_t* flag, hipStream_t st, const double* mul) {
     hipError_t e = launch_fill_zero_u32(c, b * n * 2, st);
     if (e != hipSuccess || k <= 0) return e;
-    const int64_t per_block = (int64_t)kThreads * (f64 ? 2 : 4);  // columns per block
-    const dim3 grid((unsigned)((n + per_block - 1) / per_block), (unsigned)((k + 63) / 64), (unsigned)b);
+    const int64_t cols_blk = f64 ? col_block_cols<double>() : col_block_cols<float>();
+    const int64_t rows_blk = col_block_rows(b, k, n, cols_blk);
+    const dim3 grid((unsigned)((n + cols_blk - 1) / cols_blk), (unsigned)((k + rows_blk - 1) / rows_blk),
+                    (unsigned)b);
     timing_before("mt_colmax", st);
 #define MT_COLMAX(T, M) \
-    hipLaunchKernelGGL((mt_colmax_kernel<T, M>), grid, dim3(kThreads), 0, st, (const T*)B, k, n, c, flag, mul)
+    hipLaunchKernelGGL((mt_colmax_kernel<T, M>), grid, dim3(kThreads), 0, st, (const T*)B, k, n, c, flag, \
+                       rows_blk, mul)
     if (f64) {
         if (mul) MT_COLMAX(double, true); else MT_COLMAX(double, false);
     } else {
@@ -895,6 +931,24 @@ hipError_t launch_planes_if(const int32_t* cond, const void* A, const void* B, i
     return hipGetLastError();
 }
 
+namespace {
+// Blocks of the column maxima of B (FP32, b x cols x nb) along the columns
+// and along the rows, and the rows of each.
+struct ColBlocks {
+    int64_t gx, gy, rows;
+};
+ColBlocks col_blocks_f32(int64_t b, int64_t cols, int64_t nb) {
+    const int64_t cols_blk = col_block_cols<float>();
+    const int64_t rows = col_block_rows(b, cols, nb, cols_blk);
+    return ColBlocks{(nb + cols_blk - 1) / cols_blk, (cols + rows - 1) / rows, rows};
+}
+}  // namespace
+
+bool rowmax_planes_colmax_fits(int64_t b, int64_t cols, int64_t nb, int64_t rows_pad) {
+    const ColBlocks cb = col_blocks_f32(b, cols, nb);
+    return rows_pad * b + cb.gx * cb.gy * b <= (int64_t)1 << 23;  // below 2^32 threads
+}
+
 hipError_t launch_rowmax_planes_colmax(const float* A, const float* B, int64_t b, int64_t rows, int64_t cols,
                                        int64_t rows_pad, int64_t cols_pad, int64_t nb, double* r, double* c,
                                        int32_t* flag, const PlaneSpec& spec, int bf16, void* planes,
@@ -905,20 +959,19 @@ hipError_t launch_rowmax_planes_colmax(const float* A, const float* B, int64_t b
     hipError_t e = launch_fill_zero_u32(c, b * nb * 2, st);
     if (e != hipSuccess) return e;
     // B is b x cols x nb (its inner index runs over A's columns)
-    const int64_t cgx = (nb + (int64_t)kThreads * 4 - 1) / ((int64_t)kThreads * 4);
-    const int64_t cgy = (cols + 63) / 64;
-    const int64_t na = rows_pad * b, nc = cgx * cgy * b;
-    if (na < nc || na + nc > 0x7fffffff) return hipErrorInvalidValue;
-    const int64_t ratio = na / nc;
+    if (!rowmax_planes_colmax_fits(b, cols, nb, rows_pad)) return hipErrorInvalidValue;
+    const ColBlocks cb = col_blocks_f32(b, cols, nb);
+    const int64_t na = rows_pad * b, nc = cb.gx * cb.gy * b;
+    const int64_t ratio = na / nc;  // 0 (few plane rows): the column-max blocks first
     timing_before(bf16 ? "mt_power_planes_bf16" : "mt_power_planes_f64", st);
     if (bf16)
         hipLaunchKernelGGL(mt_rowmax_planes_colmax_kernel<true>, dim3((unsigned)(na + nc)), dim3(kThreads), 0, st,
                            A, rows, cols, rows_pad, cols_pad, r, flag, spec, planes, B, cols, nb, c, na, nc, ratio,
-                           cgx, cgy);
+                           cb.gx, cb.gy, cb.rows);
     else
         hipLaunchKernelGGL(mt_rowmax_planes_colmax_kernel<false>, dim3((unsigned)(na + nc)), dim3(kThreads), 0, st,
                            A, rows, cols, rows_pad, cols_pad, r, flag, spec, planes, B, cols, nb, c, na, nc, ratio,
-                           cgx, cgy);
+                           cb.gx, cb.gy, cb.rows);
     timing_after(st);
     return hipGetLastError();
 }

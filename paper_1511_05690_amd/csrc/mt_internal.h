@@ -234,9 +234,10 @@ struct PlaneSpec {
 // launch_power_planes (untransposed, no column scales or multipliers), for
 // cols_pad <= kFusedRowMaxK; with the column maxima c of B (FP32,
 // b x cols x nb) taken in the same launch (c is cleared first), so the two
-// passes share the GPU.  Needs at least as many plane rows (b rows_pad) as
-// column-max blocks.
+// passes share the GPU; rowmax_planes_colmax_fits says whether the launch
+// holds the blocks of both.
 constexpr int64_t kFusedRowMaxK = 8192;
+bool rowmax_planes_colmax_fits(int64_t b, int64_t cols, int64_t nb, int64_t rows_pad);
 hipError_t launch_rowmax_planes_colmax(const float* A, const float* B, int64_t b, int64_t rows, int64_t cols,
                                        int64_t rows_pad, int64_t cols_pad, int64_t nb, double* r, double* c,
                                        int32_t* flag, const PlaneSpec& spec, int bf16, void* planes,
