@@ -27,22 +27,72 @@ __device__ inline uint16_t bf16_rne(float x) {
 
 __device__ inline float bf16_to_float(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
+// g x^-e for x > 0 by binary powering of 1 / x as an unevaluated sum h + l
+// (l holds what the product h rounded off), so that the result is good to
+// about one rounding whatever e: at e = 63 some 60 FP64 operations, where
+// exp(-e log x), whose error grows as |e log x| 2^-53, took about 200.
+// Beyond the FP64 range the result is infinite, as exp's was.
+__device__ inline double times_pow_neg(double g, double x, int e) {
+    double xh = 1.0 / x;
+    double xl = fma(-x, xh, 1.0) * xh;
+    double yh = 1.0, yl = 0.0;
+    while (true) {
+        if (e & 1) {
+            const double h = yh * xh;
+            yl = fma(yh, xl, fma(yl, xh, fma(yh, xh, -h)));
+            yh = h;
+        }
+        e >>= 1;
+        if (e == 0) break;
+        const double h = xh * xh;
+        xl = fma(2.0 * xh, xl, fma(xh, xh, -h));
+        xh = h;
+    }
+    if (!(yh <= DBL_MAX)) return g * HUGE_VAL;
+    return fma(g, yh, g * yl);
+}
+
 // hist[q] = number of entries whose p is family index q (MT_PSTAR_NONE -> 0).
+// Almost every entry of a product often has the same p, so one counter per p
+// and block serialised the LDS atomics of a wave (64 x 512^2 codes: 59 us;
+// 12 us now, the 17 MB read take 3 us).  Each lane counts into a column of
+// its own (64 columns, shared by the block's waves: one bank each), 16 codes
+// a load, and a block adds each p once.
+constexpr int kHistBytes = 16;
 __global__ __launch_bounds__(kThreads) void mt_pstar_hist_kernel(const uint8_t* __restrict__ ps,
                                                                  int64_t total, int n_p,
                                                                  int32_t* __restrict__ hist) {
-    __shared__ int32_t h[MT_MAX_P];
-    for (int i = threadIdx.x; i < MT_MAX_P; i += kThreads) h[i] = 0;
+    __shared__ int32_t h[MT_MAX_P][64];
+    const int lane = threadIdx.x & 63;
+    for (int i = threadIdx.x; i < MT_MAX_P * 64; i += kThreads) ((int32_t*)h)[i] = 0;
     __syncthreads();
-    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * kThreads) {
-        int q = ps[e];
-        if (q == MT_PSTAR_NONE || q >= n_p) q = 0;
-        atomicAdd(&h[q], 1);
+    auto count = [&](int q) { atomicAdd(&h[q == MT_PSTAR_NONE || q >= n_p ? 0 : q][lane], 1); };
+    // p_star may start at any byte: the loads are 16 bytes wide, not aligned
+    typedef uint32_t codes __attribute__((ext_vector_type(4), aligned(1)));
+    const int64_t chunks = total / kHistBytes;
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    const int64_t first = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    for (int64_t v = first; v < chunks; v += stride) {
+        const codes w = *(const codes*)(ps + v * kHistBytes);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // four equal codes (the common case) are one add
+            const int q = (int)(w[i] & 255u);
+            if (w[i] == (uint32_t)q * 0x01010101u) {
+                atomicAdd(&h[q == MT_PSTAR_NONE || q >= n_p ? 0 : q][lane], 4);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) count((int)((w[i] >> (8 * t)) & 255u));
+            }
+        }
     }
+    for (int64_t e = chunks * kHistBytes + first; e < total; e += stride) count(ps[e]);
     __syncthreads();
-    for (int i = threadIdx.x; i < n_p; i += kThreads)
-        if (h[i]) atomicAdd(&hist[i], h[i]);
+    for (int q = threadIdx.x >> 6; q < n_p; q += kThreads / 64) {
+        int32_t v = h[q][lane];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (lane == 0 && v) atomicAdd(&hist[q], v);
+    }
 }
 
 // Per batch item, the binary exponents of the largest row scale and of the
@@ -80,11 +130,38 @@ __global__ __launch_bounds__(kThreads) void mt_scale_exp_kernel(const double* __
     }
 }
 
+// 8 consecutive values as BF16 hi and lo planes (kBf16) or as doubles.
+template <bool kBf16>
+__device__ __forceinline__ void store_adjoint8(void* planes, int64_t pos, int64_t plane_elems, const double (&v)[8]) {
+    if (kBf16) {
+        uint16_t* pl = (uint16_t*)planes + pos;
+        u32x4 hi, lo;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float f0 = (float)v[2 * t], f1 = (float)v[2 * t + 1];
+            const uint16_t h0 = bf16_rne(f0), h1 = bf16_rne(f1);
+            hi[t] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+            lo[t] = (uint32_t)bf16_rne(f0 - bf16_to_float(h0)) | ((uint32_t)bf16_rne(f1 - bf16_to_float(h1)) << 16);
+        }
+        *(u32x4*)pl = hi;
+        *(u32x4*)(pl + plane_elems) = lo;
+    } else {
+        double* pl = (double*)planes + pos;
+#pragma unroll
+        for (int t = 0; t < 8; t += 2) *(double2*)(pl + t) = double2{v[t], v[t + 1]};
+    }
+}
+
 // Adjoint planes for one 64 x 64 (i, j) tile of one batch item.
 //   XA: [b][plane][m_pad][n_kpad]  Gt_p   (rows i, inner j)  -> dA product
 //   YB: [b][plane][n_pad][m_kpad]  Gt'_p^T (rows j, inner i) -> dB product
 // For the BF16 path each p has a hi and a lo plane (planes 2q, 2q + 1);
 // for FP64 one plane (q).  Planes of p that no entry uses are not written.
+// Bound by the latency of its loads and of the weights' FP64 chain: a thread
+// owns 8 consecutive j of two rows, so that all its loads are in flight at
+// once (16 rounds of one element each, with the family's p looked up in the
+// arguments, ran at 1.9 TB/s: 152 us at 64 x 512^2, 117 us now), and its XA
+// chunks go out from registers; only YB takes the LDS transpose.
 template <typename T, bool kBf16>
 __global__ __launch_bounds__(kThreads) void mt_adjoint_prep_kernel(
     const T* __restrict__ G, const T* __restrict__ C, const uint8_t* __restrict__ pstar,
@@ -96,9 +173,39 @@ __global__ __launch_bounds__(kThreads) void mt_adjoint_prep_kernel(
     __shared__ double rsh[64], csh[64];  // r_i and c_j as the planes take them (/ 2^ex on the BF16 path)
     __shared__ double rm[64], cm[64];    // mantissas of r_i and c_j
     __shared__ int re[64], ce[64];       // and their exponents
+    __shared__ int pt[MT_MAX_P];         // the family
     const int64_t bi = blockIdx.z;
     const int64_t i0 = (int64_t)blockIdx.y * 64, j0 = (int64_t)blockIdx.x * 64;
     const int64_t base = bi * m * n;
+
+    // this thread's tasks: row tid / 8 + 32 t, columns 8 (tid % 8) .. + 7
+    constexpr int kTasks = 64 * 8 / kThreads;
+    typedef T vec8 __attribute__((ext_vector_type(8), aligned(sizeof(T))));
+    typedef uint8_t code8 __attribute__((ext_vector_type(8), aligned(1)));
+    const int ch = threadIdx.x & 7;
+    const int64_t j = j0 + ch * 8;
+    vec8 gv[kTasks], cv[kTasks];
+    code8 pv[kTasks];
+#pragma unroll
+    for (int t = 0; t < kTasks; ++t) {
+        const int64_t i = i0 + (threadIdx.x >> 3) + t * (kThreads / 8);
+        const int64_t o = base + i * n + j;
+        if (i < m && j + 8 <= n) {
+            gv[t] = *(const vec8*)(G + o);
+            cv[t] = *(const vec8*)(C + o);
+            pv[t] = *(const code8*)(pstar + o);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool in = i < m && j + u < n;
+                gv[t][u] = in ? G[o + u] : T(0);
+                cv[t][u] = in ? C[o + u] : T(0);
+                pv[t][u] = in ? pstar[o + u] : 0;
+            }
+        }
+    }
+    uint32_t used = 0;
+    for (int q = 0; q < spec.n_p; ++q) used |= (hist[q] != 0 ? 1u : 0u) << q;
     if (threadIdx.x < 128) {
         const bool is_r = threadIdx.x < 64;
         const int t = threadIdx.x & 63;
@@ -117,91 +224,65 @@ __global__ __launch_bounds__(kThreads) void mt_adjoint_prep_kernel(
             ce[t] = e;
         }
     }
+    for (int q = threadIdx.x; q < spec.n_p; q += kThreads) pt[q] = spec.p[q];
     __syncthreads();
 
-    // 1. per-entry weights (FP64), coalesced along j
-    for (int e = threadIdx.x; e < 64 * 64; e += kThreads) {
-        const int ii = e >> 6, jj = e & 63;
-        const int64_t i = i0 + ii, j = j0 + jj;
-        double w = 0.0;
-        int q = 0;
-        if (i < m && j < n) {
-            const int64_t o = base + i * n + j;
-            const int code = pstar[o];
-            q = (code == MT_PSTAR_NONE || code >= spec.n_p) ? 0 : code;
+#pragma unroll
+    for (int t = 0; t < kTasks; ++t) {
+        // 1. per-entry weights (FP64)
+        const int ii = (threadIdx.x >> 3) + t * (kThreads / 8);
+        const int64_t i = i0 + ii;
+        double w[8];
+        int q8[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int jj = ch * 8 + u;
+            const int code = pv[t][u];
+            const int q = (code == MT_PSTAR_NONE || code >= spec.n_p) ? 0 : code;
             // C' = C / (r_i c_j), formed as (C 2^-(e_r + e_c)) / (m_r m_c)
             // so that r_i c_j itself never has to be representable
             const double mrc = rm[ii] * cm[jj];
-            const double cs = mrc > 0.0 ? ldexp((double)C[o], -(re[ii] + ce[jj])) / mrc : 0.0;
-            if (cs > 0.0) {
-                const int p = spec.p[q];
-                w = (double)G[o] * (p == 1 ? 1.0 : exp((double)(1 - p) * log(cs)));  // G C'^(1-p)
+            const double cs = mrc > 0.0 ? ldexp((double)cv[t][u], -(re[ii] + ce[jj])) / mrc : 0.0;
+            w[u] = cs > 0.0 ? times_pow_neg((double)gv[t][u], cs, pt[q] - 1) : 0.0;  // G C'^(1-p)
+            q8[u] = q;
+            gw[ii][jj] = w[u];
+            qq[ii][jj] = (uint8_t)q;
+        }
+        // 2. XA planes (rows i, inner j)
+        if (i < spec.xa_rows_pad && j < spec.xa_cols_pad) {
+            for (uint32_t left = used; left != 0u; left &= left - 1u) {
+                const int q = __builtin_ctz(left);
+                double v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = q8[u] == q ? w[u] * csh[ch * 8 + u] : 0.0;
+                const int64_t plane = bi * spec.planes + (kBf16 ? 2 * q : q);
+                const int64_t elems = spec.xa_rows_pad * spec.xa_cols_pad;
+                store_adjoint8<kBf16>(XA, plane * elems + i * spec.xa_cols_pad + j, elems, v);
             }
         }
-        gw[ii][jj] = w;
-        qq[ii][jj] = (uint8_t)q;
     }
     __syncthreads();
 
-    // 2. XA planes (rows i, inner j): 8 consecutive j per task
-    for (int task = threadIdx.x; task < 64 * 8; task += kThreads) {
-        const int ii = task >> 3, ch = task & 7;
-        const int64_t i = i0 + ii, j = j0 + ch * 8;
-        if (i >= spec.xa_rows_pad || j >= spec.xa_cols_pad) continue;
-        for (int q = 0; q < spec.n_p; ++q) {
-            if (hist[q] == 0) continue;
-            double v[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) v[t] = qq[ii][ch * 8 + t] == q ? gw[ii][ch * 8 + t] * csh[ch * 8 + t] : 0.0;
-            if (kBf16) {
-                uint16_t* pl = (uint16_t*)XA + ((bi * spec.planes + 2 * q) * spec.xa_rows_pad + i) * spec.xa_cols_pad + j;
-                u32x4 hi, lo;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float f0 = (float)v[2 * t], f1 = (float)v[2 * t + 1];
-                    const uint16_t h0 = bf16_rne(f0), h1 = bf16_rne(f1);
-                    hi[t] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-                    lo[t] = (uint32_t)bf16_rne(f0 - bf16_to_float(h0)) |
-                            ((uint32_t)bf16_rne(f1 - bf16_to_float(h1)) << 16);
-                }
-                *(u32x4*)pl = hi;
-                *(u32x4*)(pl + spec.xa_rows_pad * spec.xa_cols_pad) = lo;
-            } else {
-                double* pl = (double*)XA + ((bi * spec.planes + q) * spec.xa_rows_pad + i) * spec.xa_cols_pad + j;
-#pragma unroll
-                for (int t = 0; t < 8; t += 2) *(double2*)(pl + t) = double2{v[t], v[t + 1]};
-            }
-        }
-    }
-
     // 3. YB planes (rows j, inner i): 8 consecutive i per task (transposed)
     for (int task = threadIdx.x; task < 64 * 8; task += kThreads) {
-        const int jj = task >> 3, ch = task & 7;
-        const int64_t j = j0 + jj, i = i0 + ch * 8;
-        if (j >= spec.yb_rows_pad || i >= spec.yb_cols_pad) continue;
-        for (int q = 0; q < spec.n_p; ++q) {
-            if (hist[q] == 0) continue;
+        const int jj = task >> 3, ci = task & 7;
+        const int64_t jr = j0 + jj, i = i0 + ci * 8;
+        if (jr >= spec.yb_rows_pad || i >= spec.yb_cols_pad) continue;
+        double w[8];
+        int q8[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            w[u] = gw[ci * 8 + u][jj] * rsh[ci * 8 + u];
+            q8[u] = qq[ci * 8 + u][jj];
+        }
+        for (uint32_t left = used; left != 0u; left &= left - 1u) {
+            const int q = __builtin_ctz(left);
             double v[8];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) v[t] = qq[ch * 8 + t][jj] == q ? gw[ch * 8 + t][jj] * rsh[ch * 8 + t] : 0.0;
-            if (kBf16) {
-                uint16_t* pl = (uint16_t*)YB + ((bi * spec.planes + 2 * q) * spec.yb_rows_pad + j) * spec.yb_cols_pad + i;
-                u32x4 hi, lo;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float f0 = (float)v[2 * t], f1 = (float)v[2 * t + 1];
-                    const uint16_t h0 = bf16_rne(f0), h1 = bf16_rne(f1);
-                    hi[t] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-                    lo[t] = (uint32_t)bf16_rne(f0 - bf16_to_float(h0)) |
-                            ((uint32_t)bf16_rne(f1 - bf16_to_float(h1)) << 16);
-                }
-                *(u32x4*)pl = hi;
-                *(u32x4*)(pl + spec.yb_rows_pad * spec.yb_cols_pad) = lo;
-            } else {
-                double* pl = (double*)YB + ((bi * spec.planes + q) * spec.yb_rows_pad + j) * spec.yb_cols_pad + i;
-#pragma unroll
-                for (int t = 0; t < 8; t += 2) *(double2*)(pl + t) = double2{v[t], v[t + 1]};
-            }
+            for (int u = 0; u < 8; ++u) v[u] = q8[u] == q ? w[u] : 0.0;
+            const int64_t plane = bi * spec.planes + (kBf16 ? 2 * q : q);
+            const int64_t elems = spec.yb_rows_pad * spec.yb_cols_pad;
+            store_adjoint8<kBf16>(YB, plane * elems + jr * spec.yb_cols_pad + i, elems, v);
         }
     }
 }
@@ -211,8 +292,9 @@ __global__ __launch_bounds__(kThreads) void mt_adjoint_prep_kernel(
 hipError_t launch_pstar_hist(const uint8_t* ps, int64_t total, int n_p, int32_t* hist,
                              hipStream_t st) {
     if (total <= 0) return hipSuccess;
-    int64_t g = (total + kThreads * 16 - 1) / (kThreads * 16);
-    if (g > 2048) g = 2048;
+    // at most two blocks per CU: their adds to the same few counters queue
+    int64_t g = (total + kThreads * kHistBytes - 1) / (kThreads * kHistBytes);
+    if (g > 512) g = 512;
     timing_before("mt_pstar_hist", st);
     hipLaunchKernelGGL(mt_pstar_hist_kernel, dim3((unsigned)g), dim3(kThreads), 0, st, ps, total, n_p, hist);
     timing_after(st);

@@ -66,9 +66,11 @@ __global__ void tail_hist_kernel(const TailEntry* __restrict__ in, const uint32_
 // 4 long, read and written as int4; the bucket array is 16-byte aligned and
 // padded to a multiple of 4 entries).
 constexpr int kScanThreads = 1024;
-__global__ __launch_bounds__(kScanThreads) void tail_scan_kernel(int32_t* __restrict__ bucket, int32_t nb) {
+__global__ __launch_bounds__(kScanThreads) void tail_scan_kernel(const uint32_t* __restrict__ count,
+                                                                 int32_t* __restrict__ bucket, int32_t nb) {
     __shared__ int32_t part[kScanThreads];
     const int t = threadIdx.x;
+    if (*count == 0) return;  // nothing to place
     const int nb4 = (nb + 3) / 4;
     const int per4 = (nb4 + kScanThreads - 1) / kScanThreads;
     const int lo = min(t * per4, nb4), hi = min(lo + per4, nb4);
@@ -283,11 +285,12 @@ __device__ inline T ipow(T x, int p) {
 // doubles the previous power, binary powering otherwise; BF16 planes take
 // hi = RNE(power) and, for a split p, lo = RNE(power - hi) in the next plane.
 template <typename TC, bool kBf16>
-__device__ __forceinline__ void write_power_chunk(const TC (&x)[8], const PlaneSpec& spec, void* __restrict__ planes,
-                                                  int64_t bi, int64_t plane_elems, int64_t pos) {
+__device__ __forceinline__ void write_power_chunk(const TC (&x)[8], const PlaneSpec& spec, uint32_t mask,
+                                                  void* __restrict__ planes, int64_t bi, int64_t plane_elems,
+                                                  int64_t pos) {
     TC pw[8];
     int prev = 0;
-    for (int q = 0; q < spec.n_p; ++q) {
+    for (int q = 0; (mask >> q) != 0u; ++q) {
         const int p = spec.p[q];
         if (prev > 0 && p == 2 * prev) {
 #pragma unroll
@@ -299,7 +302,10 @@ __device__ __forceinline__ void write_power_chunk(const TC (&x)[8], const PlaneS
         prev = p;
         // powers whose planes are not wanted are still formed: the next
         // power may square them
-        if (!((spec.write_mask >> q) & 1u)) continue;
+        if (!((mask >> q) & 1u)) {
+            if (q == 31) break;
+            continue;
+        }
         const int64_t pl = spec.first_plane[q];
         const int64_t off = (bi * spec.n_planes + pl) * plane_elems + pos;
         if (kBf16) {
@@ -371,6 +377,7 @@ __device__ __forceinline__ void power_planes_block(const TS* __restrict__ src, i
 
     typedef typename std::conditional<kBf16, float, double>::type TC;
     const int64_t plane_elems = rows_pad * cols_pad;
+    const uint32_t mask = plane_mask(spec);
     for (int rep = 0; rep < PT::TASKS / kThreads; ++rep) {
         const int task = threadIdx.x + rep * kThreads;
         const int tt = task / PT::CHUNKS, ch = task % PT::CHUNKS;
@@ -426,7 +433,7 @@ __device__ __forceinline__ void power_planes_block(const TS* __restrict__ src, i
                 x[i] = (TC)v;
             }
         }
-        write_power_chunk<TC, kBf16>(x, spec, planes, bi, plane_elems, t * cols_pad + u);
+        write_power_chunk<TC, kBf16>(x, spec, mask, planes, bi, plane_elems, t * cols_pad + u);
     }
 }
 
@@ -492,19 +499,26 @@ __global__ __launch_bounds__(kThreads) void mt_planes_if_kernel(const int32_t* _
 
 // Row maxima and power planes of a row-major FP32 operand in one pass, for
 // rows of at most kFusedRowMaxK padded inner elements: one workgroup per
-// plane row holds the row in registers (kFusedChunks chunks of 8 per thread),
-// takes r = max_k A_ik (Sec. 2.1 scaling; the domain check of the row-max
+// plane row, or one wave for rows of at most kWaveRowMaxK (kWaveRow), holds
+// the row in registers (kFusedChunks chunks of 8 per thread), takes r = max_k A_ik (Sec. 2.1 scaling; the domain check of the row-max
 // kernel included), then writes the planes of A / r with the plane kernel's
 // arithmetic (the FP64 reciprocal of r for whole 8-element chunks of rows
 // whose length allows 16-byte loads, a division otherwise).  Padding rows
 // and columns get zeros; r is written for the real rows.
 constexpr int kFusedChunks = (int)(kFusedRowMaxK / 8 / kThreads);
-template <bool kBf16>
+// A row this short leaves most of a workgroup without a chunk (64 of 256
+// threads at k = 512): a wave takes it alone, four rows to the workgroup and
+// no barrier (64 x 512 rows of 512, 10 planes: 178 us by workgroups, 91 us
+// by waves).
+constexpr int64_t kWaveRowMaxK = kFusedChunks * 64 * 8;
+template <bool kBf16, bool kWaveRow>
 __device__ __forceinline__ void rowmax_planes_block(const float* __restrict__ A, int64_t rows, int64_t cols,
                                                     int64_t rows_pad, int64_t cols_pad, double* __restrict__ r,
                                                     int32_t* __restrict__ flag, const PlaneSpec& spec,
                                                     void* __restrict__ planes, int64_t t, int64_t bi,
                                                     float* wmax) {
+    constexpr int kRow = kWaveRow ? 64 : kThreads;  // threads on the row
+    const int lane = threadIdx.x % kRow;
     const bool real_row = t < rows;
     const float* s = A + (bi * rows + (real_row ? t : 0)) * cols;
     const bool vec_row = (cols & 3) == 0 && ((uintptr_t)s % 16) == 0;
@@ -513,7 +527,7 @@ __device__ __forceinline__ void rowmax_planes_block(const float* __restrict__ A,
     bool bad = false;
 #pragma unroll
     for (int c = 0; c < kFusedChunks; ++c) {
-        const int64_t u = ((int64_t)c * kThreads + threadIdx.x) * 8;
+        const int64_t u = ((int64_t)c * kRow + lane) * 8;
         if (real_row && vec_row && u + 8 <= cols) {
             typedef float vec4 __attribute__((ext_vector_type(4)));
             const vec4 a0 = *(const vec4*)(s + u);
@@ -533,24 +547,27 @@ __device__ __forceinline__ void rowmax_planes_block(const float* __restrict__ A,
             mx = fmaxf(mx, v[c][i]);
         }
     }
-    // the row's maximum (exact in FP32) over the workgroup
+    // the row's maximum (exact in FP32) over its threads
     for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    mx = wmax[0];
+    if (!kWaveRow) {
+        if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
+        __syncthreads();
+        mx = wmax[0];
 #pragma unroll
-    for (int w = 1; w < kThreads / 64; ++w) mx = fmaxf(mx, wmax[w]);
+        for (int w = 1; w < kThreads / 64; ++w) mx = fmaxf(mx, wmax[w]);
+    }
     const double sc = (double)mx;
-    if (real_row && threadIdx.x == 0) r[bi * rows + t] = sc;
+    if (real_row && lane == 0) r[bi * rows + t] = sc;
     if (bad) atomicOr(flag, 1);
 
     typedef typename std::conditional<kBf16, float, double>::type TC;
     const int64_t plane_elems = rows_pad * cols_pad;
+    const uint32_t mask = plane_mask(spec);
     const bool zero_row = !real_row || sc == 0.0;
     const double inv = sc > 0.0 ? 1.0 / sc : 0.0;
 #pragma unroll
     for (int c = 0; c < kFusedChunks; ++c) {
-        const int64_t u = ((int64_t)c * kThreads + threadIdx.x) * 8;
+        const int64_t u = ((int64_t)c * kRow + lane) * 8;
         if (u >= cols_pad) continue;
         TC x[8];
         if (!zero_row && sc >= DBL_MIN && u + 8 <= cols && (cols & 3) == 0) {
@@ -564,7 +581,7 @@ __device__ __forceinline__ void rowmax_planes_block(const float* __restrict__ A,
                 x[i] = (TC)y;
             }
         }
-        write_power_chunk<TC, kBf16>(x, spec, planes, bi, plane_elems, t * cols_pad + u);
+        write_power_chunk<TC, kBf16>(x, spec, mask, planes, bi, plane_elems, t * cols_pad + u);
     }
 }
 
@@ -573,7 +590,7 @@ __device__ __forceinline__ void rowmax_planes_block(const float* __restrict__ A,
 // (one every ratio + 1 while both last), so the two HBM-bound passes share
 // the GPU instead of running one after the other.  c must be zero before
 // the launch.
-template <bool kBf16>
+template <bool kBf16, bool kWaveRow>
 __global__ __launch_bounds__(kThreads) void mt_rowmax_planes_colmax_kernel(
     const float* __restrict__ A, int64_t rows, int64_t cols, int64_t rows_pad, int64_t cols_pad,
     double* __restrict__ r, int32_t* __restrict__ flag, PlaneSpec spec, void* __restrict__ planes,
@@ -594,9 +611,11 @@ __global__ __launch_bounds__(kThreads) void mt_rowmax_planes_colmax_kernel(
         colmax_block<float, false>(B, kb, nb, c, flag, nullptr, crows, c_idx % cgx, (c_idx / cgx) % cgy, c_idx / (cgx * cgy));
         return;
     }
-    if (a_idx < na)
-        rowmax_planes_block<kBf16>(A, rows, cols, rows_pad, cols_pad, r, flag, spec, planes, a_idx % rows_pad,
-                                   a_idx / rows_pad, wmax);
+    if (a_idx >= na) return;
+    // (rows_pad is a multiple of the rows per block)
+    const int64_t row = kWaveRow ? a_idx * (kThreads / 64) + (threadIdx.x >> 6) : a_idx;
+    rowmax_planes_block<kBf16, kWaveRow>(A, rows, cols, rows_pad, cols_pad, r, flag, spec, planes, row % rows_pad,
+                                         row / rows_pad, wmax);
 }
 
 // X = exp(-s W) in FP64; +inf -> 0; diagonal -> 1.
@@ -788,7 +807,8 @@ hipError_t launch_tail_sort(const EpiArgs& epi, int64_t rows, int64_t cap, hipSt
     timing_before("mt_tail_sort", st);
     hipLaunchKernelGGL(tail_hist_kernel, grid, dim3(kThreads), 0, st, epi.tail, epi.tail_count, rows,
                        epi.tail_shift, epi.tail_bucket);
-    hipLaunchKernelGGL(tail_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, epi.tail_bucket, epi.tail_buckets);
+    hipLaunchKernelGGL(tail_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, epi.tail_count,
+                       epi.tail_bucket, epi.tail_buckets);
     hipLaunchKernelGGL(tail_scatter_kernel, grid, dim3(kThreads), 0, st, epi.tail, epi.tail_count, rows,
                        epi.tail_shift, epi.tail_bucket, epi.tail_sorted);
     timing_after(st);
@@ -961,17 +981,21 @@ hipError_t launch_rowmax_planes_colmax(const float* A, const float* B, int64_t b
     // B is b x cols x nb (its inner index runs over A's columns)
     if (!rowmax_planes_colmax_fits(b, cols, nb, rows_pad)) return hipErrorInvalidValue;
     const ColBlocks cb = col_blocks_f32(b, cols, nb);
-    const int64_t na = rows_pad * b, nc = cb.gx * cb.gy * b;
+    const bool wave_row = cols_pad <= kWaveRowMaxK;
+    if (rows_pad % (kThreads / 64)) return hipErrorInvalidValue;
+    const int64_t na = rows_pad * b / (wave_row ? kThreads / 64 : 1), nc = cb.gx * cb.gy * b;
     const int64_t ratio = na / nc;  // 0 (few plane rows): the column-max blocks first
     timing_before(bf16 ? "mt_power_planes_bf16" : "mt_power_planes_f64", st);
-    if (bf16)
-        hipLaunchKernelGGL(mt_rowmax_planes_colmax_kernel<true>, dim3((unsigned)(na + nc)), dim3(kThreads), 0, st,
-                           A, rows, cols, rows_pad, cols_pad, r, flag, spec, planes, B, cols, nb, c, na, nc, ratio,
-                           cb.gx, cb.gy, cb.rows);
-    else
-        hipLaunchKernelGGL(mt_rowmax_planes_colmax_kernel<false>, dim3((unsigned)(na + nc)), dim3(kThreads), 0, st,
-                           A, rows, cols, rows_pad, cols_pad, r, flag, spec, planes, B, cols, nb, c, na, nc, ratio,
-                           cb.gx, cb.gy, cb.rows);
+#define MT_ROWPLANES(BF, WR)                                                                                       \
+    hipLaunchKernelGGL((mt_rowmax_planes_colmax_kernel<BF, WR>), dim3((unsigned)(na + nc)), dim3(kThreads), 0, st, \
+                       A, rows, cols, rows_pad, cols_pad, r, flag, spec, planes, B, cols, nb, c, na, nc, ratio,    \
+                       cb.gx, cb.gy, cb.rows)
+    if (bf16) {
+        if (wave_row) MT_ROWPLANES(true, true); else MT_ROWPLANES(true, false);
+    } else {
+        if (wave_row) MT_ROWPLANES(false, true); else MT_ROWPLANES(false, false);
+    }
+#undef MT_ROWPLANES
     timing_after(st);
     return hipGetLastError();
 }

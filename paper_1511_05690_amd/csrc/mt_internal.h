@@ -228,7 +228,18 @@ struct PlaneSpec {
     int32_t first_plane[MT_MAX_P];  // plane index of power q (hi plane if split)
     int32_t n_planes;
     uint32_t write_mask;            // bit q: the planes of power q are written
+    // nullable, on the device: of those, the planes of power q are written
+    // only where use[q] > 0 (the backward: p* histogram)
+    const int32_t* use;
 };
+// The write mask of a spec with its device-side part applied.
+__device__ __forceinline__ uint32_t plane_mask(const PlaneSpec& spec) {
+    uint32_t mask = spec.write_mask;
+    if (spec.use != nullptr)
+        for (int q = 0; q < spec.n_p; ++q)
+            if (spec.use[q] <= 0) mask &= ~(1u << q);
+    return spec.n_p < 32 ? mask & ((1u << spec.n_p) - 1u) : mask;
+}
 // Row maxima r of a row-major FP32 operand A (b x rows x cols) and its power
 // planes in one pass, the same values as launch_rowmax followed by
 // launch_power_planes (untransposed, no column scales or multipliers), for
