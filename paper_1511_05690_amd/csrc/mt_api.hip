@@ -493,12 +493,46 @@ BwdLayout backward_layout(const Family& f, int64_t b, int64_t m, int64_t k, int6
     return L;
 }
 
-// The product pipeline on already-validated arguments.  X-mode (APSP):
+// Does the pilot choose where the search starts (products large enough, the
+// tail on, no r = 1 projection)?
+bool uses_pilot(const Family& f, const Layout& L, int32_t s0, int64_t b, int64_t m, int64_t k, int64_t n) {
+    return !(f.flags & (MT_FLAG_PROJECT_R1 | MT_FLAG_PROJECT_R2)) && s0 == kStartAuto && L.tail_max > 0 && f.n > 2 && k >= 256 && b * m * n >= kPilotMinOutputs;
+}
+
+size_t pilot_part_bytes(const Family& f) {
+    return align_up((size_t)kPilotKParts * f.n * kMaxPilotSide * kMaxPilotSide * (f.bf16 ? 4 : 8));
+}
+
+// The tail's list is sorted by row where one power's planes of both operands
+// exceed this: entries of a row then share the loads of its plane row.
+// Smaller planes stay in the caches whatever the order, and the three sort
+// launches (about 5 us each) cost more than the sharing gives.
+constexpr int64_t kTailSortBytes = (int64_t)32 << 20;
+
+bool sorts_tail(const Geom& g, int64_t b) {
+    return b * (g.mp + g.np) * g.kp * (int64_t)g.esize > kTailSortBytes;
+}
+
+// What run_product's kernels expect set in the workspace before them: the
+// tail count, where the search starts, the deferred-plane flags, the pilot's
+// counts, the tail's buckets (the domain flag is the caller's).
+void product_fills(const Family& f, const Geom& g, const Layout& L, uint8_t* ws, int64_t b, int64_t k, int32_t s0,
+                   bool pilot, FillList* fills) {
+    WsHeader* hdr = (WsHeader*)(ws + L.hdr);
+    fills->add(&hdr->tail_count, 1);
+    fills->add(&hdr->start, 1, (uint32_t)(s0 < 0 ? 0 : (s0 < f.n ? s0 : f.n - 1)));
+    fills->add(&hdr->low_missed, 2);
+    if (pilot) fills->add(ws + L.pilot + pilot_part_bytes(f), sizeof(PilotCounts) / 4);
+    if (L.tail_max > 0 && k > 0 && sorts_tail(g, b)) fills->add(ws + L.tail_bucket, (L.tail_buckets + 3) / 4 * 4);
+}
+
+// The product pipeline on already-validated arguments (and the workspace set
+// up by product_fills; pilot: uses_pilot).  X-mode (APSP):
 // A = B = X (n x n, r = c = 1 by construction), the output goes back to X.
 mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64_t m, int64_t k,
                       int64_t n, const Family& f, const PlaneSpec& ps, const Geom& g,
                       const Layout& L, uint8_t* ws, bool scale, int mode, int clamp, void* out,
-                      int out_f64, uint8_t* pstar, hipStream_t st, bool fuse_rowmax = false) {
+                      int out_f64, uint8_t* pstar, hipStream_t st, bool pilot, bool fuse_rowmax = false) {
     double* r = scale ? (double*)(ws + L.r) : nullptr;
     double* c = scale ? (double*)(ws + L.c) : nullptr;
     void* ap = ws + L.ap;
@@ -509,11 +543,6 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
     const double* dinv = bal ? (const double*)(ws + L.bal + 3 * align_up((size_t)(b * k) * 8)) : nullptr;
     const FamilyPlan plan = family_plan(f, ps, k);
     WsHeader* hdr = (WsHeader*)(ws + L.hdr);
-    // The pilot chooses where the search starts (below: products large
-    // enough, the tail on, no r = 1 projection).
-    const int32_t s0 = g_start_entry.load();
-    const bool pilot = !plan.r1 && s0 == kStartAuto && L.tail_max > 0 && f.n > 2 && k >= 256 &&
-                       b * m * n >= kPilotMinOutputs;
     // Deferred planes (plain products the pilot steers): the planes of the
     // smaller p are written only once some entry needs them, which the
     // pilot's sample tells before the GEMM, or a tile or tail entry that
@@ -588,7 +617,7 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
             // GEMM's rate), measured on MI355X: about 1/250
             pa.kappa = 1.0f / 250.0f;
             pa.part = ws + L.pilot;
-            pa.counts = ws + L.pilot + align_up((size_t)kPilotKParts * f.n * kMaxPilotSide * kMaxPilotSide * (f.bf16 ? 4 : 8));
+            pa.counts = ws + L.pilot + pilot_part_bytes(f);
             pa.n_eval = n_eval;
             pa.low_need = defer ? &hdr->low_need : nullptr;
             pa.low_missed = defer ? &hdr->low_missed : nullptr;
@@ -597,21 +626,18 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
                 MT_TRY(launch_planes_if(&hdr->low_need, A, B, in_f64, f.bf16, b, m, n, k, g.mp, g.np, g.kp, r, c,
                                         d, dinv, ps_late, ap, bp, st),
                        "deferred planes (the pilot's sample needs them)");
-        } else {
-            const int32_t s1 = s0 < 0 ? 0 : (s0 < f.n ? s0 : f.n - 1);
-            MT_TRY(launch_fill_u32(&hdr->start, (uint32_t)s1, 1, st), "p search start");
         }
         epi.start = &hdr->start;
     }
     if (L.tail_max > 0 && k > 0) {
-        MT_TRY(launch_fill_zero_u32(&hdr->tail_count, 1, st), "clear tail count");
         epi.tail = (TailEntry*)(ws + L.tail);
         epi.tail_count = &hdr->tail_count;
         epi.tail_max = L.tail_max;
-        epi.tail_sorted = (TailEntry*)(ws + L.tail_sorted);
+        const bool sorted = sorts_tail(g, b);
+        epi.tail_sorted = sorted ? (TailEntry*)(ws + L.tail_sorted) : epi.tail;
         epi.tail_bucket = (int32_t*)(ws + L.tail_bucket);
         epi.tail_shift = L.tail_shift;
-        epi.tail_buckets = L.tail_buckets;
+        epi.tail_buckets = sorted ? L.tail_buckets : 0;
     }
     if (f.bf16) {
         epi.mode = mode;
@@ -822,12 +848,20 @@ mt_status estimate_impl(const void* A, const void* B, mt_dtype dtype, int64_t b,
         return MT_OK;
     }
     int32_t* flag = (int32_t*)(ws + L.hdr);
-    // everything the kernels expect at zero is cleared by kernels of the
-    // call itself (the header: domain flag, tail count, p* histogram), so a
+    // everything the kernels expect at zero is cleared by a kernel of the
+    // call itself (domain flag, tail count, column maxima, ...), so a
     // workspace that holds an earlier call's contents is fine
-    MT_TRY(launch_fill_zero_u32(ws + L.hdr, sizeof(WsHeader) / 4, st), "clear header");
+    const bool bal = (f.flags & MT_FLAG_BALANCE) && k > 0;
+    FillList fills;
+    fills.add(flag, 1);
+    fills.add(ws + L.c, b * n * 2);
+    if (bal) fills.add(ws + L.bal, b * k * 2);  // column maxima of A
+    const int32_t s0 = g_start_entry.load();
+    const bool pilot = uses_pilot(f, L, s0, b, m, k, n);
+    product_fills(f, g, L, ws, b, k, s0, pilot, &fills);
+    MT_TRY(launch_fills(fills, st), "clear header and column maxima");
     bool fuse_rowmax = false;
-    if ((f.flags & MT_FLAG_BALANCE) && k > 0) {
+    if (bal) {
         // inner-index balancing: a_k = max_i A_ik, b_k = max_j B_kj,
         // d_k = sqrt(b_k / a_k); then r_i = max_k A_ik d_k, c_j = max_k B_kj / d_k
         const size_t sec = align_up((size_t)(b * k) * 8);
@@ -855,7 +889,7 @@ mt_status estimate_impl(const void* A, const void* B, mt_dtype dtype, int64_t b,
         if ((s = read_domain_flag(ws + L.hdr, st)) != MT_OK) return s;
     }
     return run_product(A, B, f64, b, m, k, n, f, ps, g, L, ws, true, EPI_PLAIN,
-                       (f.flags & MT_FLAG_CLAMP) ? 1 : 0, C, f64, p_star, st, fuse_rowmax);
+                       (f.flags & MT_FLAG_CLAMP) ? 1 : 0, C, f64, p_star, st, pilot, fuse_rowmax);
 }
 
 }  // namespace
@@ -922,16 +956,21 @@ mt_status apsp_estimate(const float* W, int64_t n, double s_scale, int32_t n_squ
     uint8_t* ws = (uint8_t*)workspace;
     void* X = ws + L.x;
     int32_t* flag = (int32_t*)(ws + L.hdr);
-    MT_TRY(launch_fill_zero_u32(ws + L.hdr, sizeof(WsHeader) / 4, st), "clear header");
+    MT_TRY(launch_fill_zero_u32(flag, 1, st), "clear domain flag");
     MT_TRY(launch_apsp_transform(W, n, s_scale, X, x_f64, flag, st), "exp transform");
     if (f.flags & MT_FLAG_VALIDATE) {
         if ((s = read_domain_flag(ws + L.hdr, st)) != MT_OK) return s;
     }
     // X has X_ii = 1 and X <= 1 after the transform and after every squaring,
     // so its row and column maxima are 1: the scaled call needs no scaling.
+    FillList fills;
+    const int32_t s0 = g_start_entry.load();
+    const bool pilot = uses_pilot(f, L, s0, 1, n, n, n);
+    product_fills(f, g, L, ws, 1, n, s0, pilot, &fills);
     for (int t = 0; t < T; ++t) {
+        MT_TRY(launch_fills(fills, st), "clear product state");
         s = run_product(X, X, x_f64, 1, n, n, n, f, ps, g, L, ws, false, EPI_APSP_X, 1, X, x_f64,
-                        t == T - 1 ? p_star_last : nullptr, st);
+                        t == T - 1 ? p_star_last : nullptr, st, pilot);
         if (s != MT_OK) return s;
     }
     MT_TRY(launch_apsp_to_dist(X, x_f64, n, s_scale, D, d_dtype == MT_F64,
@@ -988,12 +1027,16 @@ mt_status maxtimes_estimate_backward(const void* A, const void* B, const void* G
     int32_t* hist = ((WsHeader*)(ws + L.hdr))->hist;
     double* r = (double*)(ws + L.r);
     double* c = (double*)(ws + L.c);
-    MT_TRY(launch_fill_zero_u32(ws + L.hdr, sizeof(WsHeader) / 4, st), "clear header");
+    const bool bal = (f.flags & MT_FLAG_BALANCE) != 0;
+    FillList fills;
+    fills.add(ws + L.hdr, sizeof(WsHeader) / 4);
+    fills.add(c, b * n * 2);
+    if (bal) fills.add(ws + L.bal, b * k * 2);  // column maxima of A
+    MT_TRY(launch_fills(fills, st), "clear header and column maxima");
     // A balanced forward (MT_FLAG_BALANCE) is differentiated on the balanced
     // pair (A D, D^-1 B), whose scaled quantities stay in range, and taken
     // back by the chain rule (columns of dA times d_k, rows of dB over d_k);
     // with p* given, C does not depend on d
-    const bool bal = (f.flags & MT_FLAG_BALANCE) != 0;
     const size_t bsec = align_up((size_t)(b * k) * 8);
     double* dfac = bal ? (double*)(ws + L.bal + 2 * bsec) : nullptr;
     double* dinv = bal ? (double*)(ws + L.bal + 3 * bsec) : nullptr;

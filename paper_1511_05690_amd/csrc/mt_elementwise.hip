@@ -43,6 +43,13 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t value, int64_t words) {
     for (; i < words; i += stride) p[i] = value;
 }
 
+__global__ void fills_kernel(FillList f) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int q = 0; q < f.n; ++q)
+        for (int64_t i = i0; i < f.r[q].words; i += stride) f.r[q].p[i] = f.r[q].value;
+}
+
 // ---------------------------------------------------------------- tail sort
 // Counting sort of the sparse-tail list by row bucket and state: counts, an exclusive
 // scan of the counts (one block), then each entry to its bucket's next slot.
@@ -799,10 +806,18 @@ hipError_t launch_fill_u32(void* p, uint32_t value, int64_t words, hipStream_t s
 
 hipError_t launch_fill_zero_u32(void* p, int64_t words, hipStream_t st) { return launch_fill_u32(p, 0u, words, st); }
 
+hipError_t launch_fills(const FillList& fills, hipStream_t st) {
+    int64_t most = 0;
+    for (int q = 0; q < fills.n; ++q) most = fills.r[q].words > most ? fills.r[q].words : most;
+    if (most <= 0) return hipSuccess;
+    timing_before("mt_fill", st);
+    hipLaunchKernelGGL(fills_kernel, dim3(grid_for(most, kThreads, 1024)), dim3(kThreads), 0, st, fills);
+    timing_after(st);
+    return hipGetLastError();
+}
+
 hipError_t launch_tail_sort(const EpiArgs& epi, int64_t rows, int64_t cap, hipStream_t st) {
-    if (cap <= 0) return hipSuccess;
-    hipError_t e = launch_fill_zero_u32(epi.tail_bucket, (epi.tail_buckets + 3) / 4 * 4, st);
-    if (e != hipSuccess) return e;
+    if (cap <= 0 || epi.tail_buckets == 0) return hipSuccess;
     const dim3 grid(grid_for(cap, kThreads, 1024));
     timing_before("mt_tail_sort", st);
     hipLaunchKernelGGL(tail_hist_kernel, grid, dim3(kThreads), 0, st, epi.tail, epi.tail_count, rows,
@@ -835,8 +850,7 @@ hipError_t launch_rowmax(const void* A, int f64, int64_t rows, int64_t k, double
 
 hipError_t launch_colmax(const void* B, int f64, int64_t b, int64_t k, int64_t n, double* c,
                          int32_t* flag, hipStream_t st, const double* mul) {
-    hipError_t e = launch_fill_zero_u32(c, b * n * 2, st);
-    if (e != hipSuccess || k <= 0) return e;
+    if (k <= 0) return hipSuccess;
     const int64_t cols_blk = f64 ? col_block_cols<double>() : col_block_cols<float>();
     const int64_t rows_blk = col_block_rows(b, k, n, cols_blk);
     const dim3 grid((unsigned)((n + cols_blk - 1) / cols_blk), (unsigned)((k + rows_blk - 1) / rows_blk),
@@ -976,8 +990,6 @@ hipError_t launch_rowmax_planes_colmax(const float* A, const float* B, int64_t b
     if (rows_pad <= 0 || cols_pad <= 0 || b <= 0 || nb <= 0 || cols <= 0)
         return hipErrorInvalidValue;
     if (cols_pad > kFusedRowMaxK || cols > cols_pad) return hipErrorInvalidValue;
-    hipError_t e = launch_fill_zero_u32(c, b * nb * 2, st);
-    if (e != hipSuccess) return e;
     // B is b x cols x nb (its inner index runs over A's columns)
     if (!rowmax_planes_colmax_fits(b, cols, nb, rows_pad)) return hipErrorInvalidValue;
     const ColBlocks cb = col_blocks_f32(b, cols, nb);

@@ -150,7 +150,24 @@ struct AdjArgs {
 // Every launcher returns hipSuccess or the launch error.
 hipError_t launch_fill_zero_u32(void* p, int64_t words, hipStream_t st);
 hipError_t launch_fill_u32(void* p, uint32_t value, int64_t words, hipStream_t st);
+// Several fills in one launch: everything a product expects cleared (header,
+// column maxima, pilot counts, tail buckets) is set before its first kernel
+// by one launch of about 5 us instead of five.
+struct FillList {
+    static constexpr int kMax = 8;
+    int32_t n = 0;
+    struct Region {
+        uint32_t* p;
+        int64_t words;
+        uint32_t value;
+    } r[kMax];
+    void add(void* p, int64_t words, uint32_t value = 0u) {
+        if (words > 0) r[n++] = Region{(uint32_t*)p, words, value};
+    }
+};
+hipError_t launch_fills(const FillList& fills, hipStream_t st);
 
+// (counts cleared by the caller, launch_fills)
 // Pilot of the search start: S_p of every plan entry on a grid of nr x nc
 // sampled output entries (nr, nc <= kMaxPilotSide) of the planes, then the
 // start with the lowest estimated cost (dense tile entries + kappa per tail
@@ -197,9 +214,13 @@ hipError_t launch_affine_correct(void* D, int f64, int64_t n, const int32_t* src
                                  double* ab, uint8_t* ws, int apply, hipStream_t st);
 // Counting sort of the sparse-tail list (length *count, read on the device)
 // into epi.tail_sorted by row bucket; rows = rows of the output per batch item.
+// The buckets are cleared by the caller.  Without buckets (tail_buckets 0) the
+// tail runs the list as it is (epi.tail_sorted == epi.tail) and nothing is
+// launched.
 hipError_t launch_tail_sort(const EpiArgs& epi, int64_t rows, int64_t cap, hipStream_t st);
 // Row maxima of A (rows x k; with mul, of A_rj mul[r / rows_per_batch][j])
-// and column maxima of B (b x k x n; with mul, of B_bkj mul[b][k]).
+// and column maxima of B (b x k x n; with mul, of B_bkj mul[b][k]; c is zero
+// before the launch).
 hipError_t launch_rowmax(const void* A, int f64, int64_t rows, int64_t k, double* r,
                          int32_t* flag, hipStream_t st, const double* mul = nullptr,
                          int64_t rows_per_batch = 1);
@@ -244,7 +265,7 @@ __device__ __forceinline__ uint32_t plane_mask(const PlaneSpec& spec) {
 // planes in one pass, the same values as launch_rowmax followed by
 // launch_power_planes (untransposed, no column scales or multipliers), for
 // cols_pad <= kFusedRowMaxK; with the column maxima c of B (FP32,
-// b x cols x nb) taken in the same launch (c is cleared first), so the two
+// b x cols x nb) taken in the same launch (c is zero before it), so the two
 // passes share the GPU; rowmax_planes_colmax_fits says whether the launch
 // holds the blocks of both.
 constexpr int64_t kFusedRowMaxK = 8192;

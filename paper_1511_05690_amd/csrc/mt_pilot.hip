@@ -409,8 +409,6 @@ hipError_t launch_choose_start(const PilotArgs& pa, const FamilyPlan& plan, int3
         }
         return launch_fill_u32(start, 0u, 1, st);
     }
-    hipError_t e = launch_fill_zero_u32(pa.counts, sizeof(PilotCounts) / 4, st);
-    if (e != hipSuccess) return e;
     if (pa.n_eval < 1 || pa.n_eval > plan.n) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((pa.nr + kPilotRows - 1) / kPilotRows), (unsigned)pa.n_eval, (unsigned)pa.kparts);
     const dim3 cgrid((unsigned)((pa.nr * pa.nc + kPilotThreads - 1) / kPilotThreads));
