@@ -315,17 +315,29 @@ RootSpec root_spec(const Family& f, int64_t k, int mode, int clamp) {
     return r;
 }
 
+// The pilot runs for products of at least this many output entries (below,
+// its fixed cost is not worth it and the search starts at the largest p).
+constexpr int64_t kPilotMinOutputs = (int64_t)1 << 22;
+
 // ------------------------------------------------------------------ geometry
 struct Geom {
     int64_t mp, np, kp;  // padded sizes of the planes
-    int bm;              // FP64 tile (128 or 64); 256 for BF16
+    int bm;              // output tile side: 256 or 128 (BF16), 128 or 64 (FP64)
     size_t esize;        // plane element bytes
 };
 
 Geom product_geom(const Family& f, int64_t b, int64_t m, int64_t k, int64_t n) {
     Geom g;
     if (f.bf16) {
-        g.bm = kBf16BM;
+        // Products the pilot does not steer: 128-wide tiles while two per CU
+        // hold them all (one round at about 0.7 of a 256-wide tile's time
+        // against one round of 256-wide tiles on half the CUs or fewer), and
+        // wherever the padding to 256 would be most of the tile.  Products it
+        // steers are large or batched, and their tiles' share of the search
+        // is planned in 256-wide tiles.
+        const int64_t tiles128 = b * ((m + 127) / 128) * ((n + 127) / 128);
+        const bool pilot_size = !(f.flags & (MT_FLAG_PROJECT_R1 | MT_FLAG_PROJECT_R2)) && b * m * n >= kPilotMinOutputs;
+        g.bm = !pilot_size && (tiles128 <= 512 || m <= 128 || n <= 128) ? kBf16SmallBM : kBf16BM;
         g.kp = round_up(k, kBf16BK);
         g.esize = 2;
     } else {
@@ -348,7 +360,18 @@ struct Layout {
 
 // A tile with at most this many undecided entries hands them to the sparse
 // tail (0 disables it).  512 of a 256 x 256 BF16 tile is 0.8 %.
-std::atomic<int32_t> g_tail_max{512};
+// Unless the caller sets a threshold, which holds for any tile, a smaller
+// BF16 tile takes its share of the 512 (kTailUnset).
+constexpr int32_t kTailDefault = 512, kTailUnset = -1;
+std::atomic<int32_t> g_tail_max{kTailUnset};
+// The threshold of a tile of side bm: a tail dot product costs about as much
+// as 1 / 250 of a dense tile entry at 256 x 256 BF16 outputs, so the share
+// goes with the tile's area.
+int32_t tail_threshold_of(bool bf16, int bm) {
+    const int32_t v = g_tail_max.load();
+    if (v != kTailUnset) return v;
+    return bf16 ? kTailDefault / ((kBf16BM / bm) * (kBf16BM / bm)) : kTailDefault;
+}
 // Products with b m k n up to this many multiply-adds take the one-kernel
 // FP64 path (mt_small.hip) when their options allow it; 0: never.
 constexpr int64_t kSmallProductDefault = (int64_t)1 << 25;
@@ -361,9 +384,6 @@ std::atomic<int32_t> g_start_entry{kStartAuto};
 // Deferred planes of the smaller p (on by default).
 std::atomic<int32_t> g_defer_planes{1};
 
-// The pilot runs for products of at least this many output entries (below,
-// its fixed cost is not worth it and the search starts at the largest p).
-constexpr int64_t kPilotMinOutputs = (int64_t)1 << 22;
 constexpr int32_t kPilotKParts = kMaxPilotKParts;
 
 // The workspace of one product (plus an APSP X buffer when x_bytes > 0).
@@ -393,7 +413,7 @@ Layout product_layout(const Family& f, const PlaneSpec& ps, const Geom& g, int64
     // sparse-tail list: at most tail_max entries per tile (none if the family
     // has a single p: nothing would be left to run; none for the r = 2
     // projection, which keeps every ring result)
-    L.tail_max = f.n > 1 && !r2 ? g_tail_max.load() : 0;
+    L.tail_max = f.n > 1 && !r2 ? tail_threshold_of(f.bf16, g.bm) : 0;
     const int64_t tiles = b * (g.mp / g.bm) * (g.np / g.bm);
     const size_t list_bytes = align_up((size_t)tiles * (size_t)L.tail_max * sizeof(TailEntry));
     L.tail = off;
@@ -611,7 +631,7 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
             pa.nc = (int32_t)std::min<int64_t>(kMaxPilotSide, n);
             pa.kparts = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kPilotKParts, g.kp / 512));
             pa.tail_max = L.tail_max;
-            pa.tile_entries = (int64_t)std::min<int64_t>(g.bm, m) * std::min<int64_t>(f.bf16 ? kBf16BN : g.bm, n);
+            pa.tile_entries = (int64_t)std::min<int64_t>(g.bm, m) * std::min<int64_t>(g.bm, n);
             // one tail dot product (two plane rows of k_pad elements from
             // HBM) against one dense tile entry (2 BM BN k_pad flops at the
             // GEMM's rate), measured on MI355X: about 1/250
@@ -652,7 +672,7 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
             epi.n_eval = n_eval;
         }
         MT_TRY(launch_pfamily_gemm_bf16((const uint16_t*)ap, (const uint16_t*)bp, b, m, n, g.mp, g.np,
-                                        g.kp, ps.n_planes, plan, epi, st),
+                                        g.kp, ps.n_planes, g.bm, plan, epi, st),
                "p-family GEMM (BF16)");
         if (defer) {
             // tiles or tail entries that reached the deferred planes: write
@@ -1440,7 +1460,10 @@ mt_status maxtimes_set_tail_threshold(int32_t max_entries) {
     return MT_OK;
 }
 
-int32_t maxtimes_tail_threshold(void) { return g_tail_max.load(); }
+int32_t maxtimes_tail_threshold(void) {
+    const int32_t v = g_tail_max.load();
+    return v == kTailUnset ? kTailDefault : v;
+}
 
 mt_status maxtimes_set_search_start(int32_t entry) {
     g_last_error.clear();

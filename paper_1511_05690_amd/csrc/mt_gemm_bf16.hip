@@ -91,13 +91,17 @@ struct GemmGeom {
     int64_t kp;             // padded inner length
     int64_t rows, cols;     // output rows x cols per batch item
     int32_t tiles_m, tiles_n;
+    int32_t bm;                // output tile side
     unsigned long long* work;  // if set: MFMA flops executed, summed over workgroups
 };
 
 // WAVES_M x WAVES_N waves, each owning WT_M x WT_N MFMA tiles of 32 x 32.
-template <int WAVES_M, int WAVES_N, int WT_M_, int WT_N_, int MINW_ = 1>
+// STAGES_ pipeline buffers of one K step each: the loads run STAGES_ - 1
+// steps ahead of the MFMAs.
+template <int WAVES_M, int WAVES_N, int WT_M_, int WT_N_, int MINW_ = 1, int STAGES_ = 2>
 struct Cfg {
     static constexpr int MINW = MINW_;  // waves per SIMD the kernel must allow
+    static constexpr int STAGES = STAGES_;
     static constexpr int NW = WAVES_M * WAVES_N;
     static constexpr int THREADS = 64 * NW;
     static constexpr int WT_M = WT_M_, WT_N = WT_N_;
@@ -107,13 +111,15 @@ struct Cfg {
     static constexpr int A_BYTES = BM * 128;
     static constexpr int B_BYTES = BN * 128;
     static constexpr int BUF_BYTES = A_BYTES + B_BYTES;
-    static constexpr int PIPE_BYTES = 2 * BUF_BYTES;
+    static constexpr int PIPE_BYTES = STAGES * BUF_BYTES;
     static constexpr int GA = BM / 8 / NW;  // load instructions per wave per plain step (X)
     static constexpr int GB = BN / 8 / NW;  // (Y)
     static constexpr int SA = BM / 16 / NW;  // per wave per split step, each of X hi / X lo
     static constexpr int SB = BN / 16 / NW;  // (Y hi / Y lo)
     static_assert(GA % 2 == 0 && GB % 2 == 0, "row groups per wave must be even");
     static_assert(SA >= 1 && SB >= 1, "split steps need 16 rows per wave");
+    static constexpr int LOADS = GA + GB;  // load instructions per wave and step, plain or split
+    static_assert(2 * SA + 2 * SB == LOADS, "plain and split steps issue the same number of loads");
 };
 
 struct TileCtx {
@@ -814,17 +820,66 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
         }
     };
 
-    // Software pipeline: the loads of the next K step (possibly of the next
-    // family entry) are issued before the MFMAs of the current one.
-    set_cursor();
-    if (nkt64 > 0 && nact > 0) {
-        issue(0);
-        advance();
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-
+    // Software pipeline: the loads of the next STAGES - 1 K steps (possibly of
+    // the next family entry) fly while the MFMAs of the current one run.
+    //
+    // Two stages: the next step's loads are issued before the MFMAs of the
+    // current one; the step ends with a wait for them and a barrier.
+    //
+    // More stages: a step begins with a wait that leaves the loads of the
+    // later steps in flight and a barrier (which also ends the reads of the
+    // buffer that is refilled next), then issues the loads of STAGES - 1
+    // steps ahead.  __syncthreads would wait for every load (its fence), so
+    // these barriers are bare; the memory clobbers keep the LDS reads on
+    // their side.
+    constexpr int S = C::STAGES;
     int buf = 0;
+    int ahead = 0;  // steps issued and not yet run
+    auto fill = [&]() {
+#pragma unroll
+        for (int i = 0; i < S - 1; ++i) {
+            if (la_ < nact) {
+                int b = buf + i;
+                if (b >= S) b -= S;
+                issue(b);
+                advance();
+                ++ahead;
+            }
+        }
+        if (S == 2) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+    };
+    auto step_begin = [&]() {
+        if constexpr (S > 2) {
+            if (ahead >= S - 1)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * C::LOADS) : "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        if (la_ < nact) {
+            int b = buf + S - 1;
+            if (b >= S) b -= S;
+            issue(b);
+            advance();
+            ++ahead;
+        }
+    };
+    auto step_end = [&]() {
+        if constexpr (S == 2) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+        --ahead;
+        if (++buf == S) buf = 0;
+    };
+    set_cursor();
+    if (nkt64 > 0 && nact > 0) fill();
+    else __syncthreads();
+
     int64_t kunits = 0;  // executed MFMA work in units of BM x BN x 1 products
     if (tid == 0) epi.record_tile(tile_id, false);
     for (int ai = 0; ai < nact; ++ai) {
@@ -838,10 +893,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
         if (plan.e[e].nseg == 3) {
             // split p: hi.hi + hi.lo + lo.hi per K step of 32
             for (int st = 0; st < nkt32; ++st) {
-                if (la_ < nact) {
-                    issue(buf ^ 1);
-                    advance();
-                }
+                step_begin();
                 const uint8_t* pxh = smem + buf * C::BUF_BYTES + t.wm * WT_M * 32 * 64;
                 const uint8_t* pxl = pxh + C::BM * 64;
                 const uint8_t* pyh = smem + buf * C::BUF_BYTES + C::A_BYTES + t.wn * WT_N * 32 * 64;
@@ -874,17 +926,12 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
                 }
                 __builtin_amdgcn_iglp_opt(1);
                 __builtin_amdgcn_s_setprio(0);
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
-                buf ^= 1;
+                step_end();
             }
             kunits += (int64_t)nkt32 * 96;
         } else {
             for (int st = 0; st < nkt64; ++st) {
-                if (la_ < nact) {
-                    issue(buf ^ 1);
-                    advance();
-                }
+                step_begin();
                 const uint8_t* pa = smem + buf * C::BUF_BYTES + t.wm * WT_M * 32 * 128;
                 const uint8_t* pb = smem + buf * C::BUF_BYTES + C::A_BYTES + t.wn * WT_N * 32 * 128;
                 // MFMA issue runs at raised wave priority; the fragments of
@@ -916,15 +963,18 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
                 // time on the 8192^2 forward)
                 __builtin_amdgcn_iglp_opt(1);
                 __builtin_amdgcn_s_setprio(0);
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
-                buf ^= 1;
+                step_end();
             }
             kunits += (int64_t)nkt64 * 64;
         }
-        // the buffer the last step read is free until the next step's loads,
-        // which wait for the barrier below
-        epi.entry(e, s, plan, acc, t, smem + (buf ^ 1) * C::BUF_BYTES);
+        // the buffer the last step read (every wave: the barrier) is free
+        // until the next step's loads, which wait for the barrier below
+        if (S > 2) {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        epi.entry(e, s, plan, acc, t, smem + (buf == 0 ? S - 1 : buf - 1) * C::BUF_BYTES);
         int lane_pre = 0;
         if (Epi::kCanStop) {
             // undecided entries per lane -> exclusive prefix in the wave
@@ -949,6 +999,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
                 s_open[ai & 1][wave] = wopen;
             }
         }
+        if (S > 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (Epi::kCanStop) {
             int total = 0, open = 0, wave_pre = 0;
@@ -986,12 +1037,9 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
                 la_ = nact - s;
                 lkt = 0;
                 set_cursor();
-                if (nkt64 > 0) {
-                    issue(buf);
-                    advance();
-                }
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
+                // (every load issued so far has landed: the barrier above)
+                ahead = 0;
+                if (nkt64 > 0) fill();
             }
         }
     }
@@ -1242,8 +1290,8 @@ __global__ __launch_bounds__(256) void mt_tail_bf16_kernel(GemmGeom g, FamilyPla
 #pragma unroll
                     for (int q = 0; q < G; ++q)
                         if (live[q] && lane == 0) {
-                            const int64_t tile = ((int64_t)te[q].bi * g.tiles_m + te[q].i / kBf16BM) * g.tiles_n +
-                                                 te[q].j / kBf16BN;
+                            const int64_t tile = ((int64_t)te[q].bi * g.tiles_m + te[q].i / g.bm) * g.tiles_n +
+                                                 te[q].j / g.bm;
                             a.missed_tile[tile] = 1u;
                             *a.low_missed = 1;
                         }
@@ -1317,18 +1365,30 @@ hipError_t launch_gemm(const GemmGeom& g, int64_t b, const FamilyPlan& plan,
 
 // Forward: 8 waves (2 per SIMD) in 2 x 4, each 128 x 64 -> 256 x 256 tiles.
 using FwdCfg = Cfg<2, 4, 4, 2>;
+// Forward of products too small to fill the GPU with those: 8 waves of 64 x
+// 32 -> 128 x 128 tiles.  A tile's K step then takes 0.55 us whatever the
+// number of tiles (its MFMAs alone 0.21): the planes come from beyond the L2
+// with some 1.5 us of latency, so the rate is the bytes in flight over that.
+// Up to one tile per CU, four stages (96 KB in flight, one workgroup per CU);
+// up to two per CU, two stages and 128 registers, so that two workgroups share
+// a CU.  1500 x 2050 x 1777, P = {1..128}: 337 us on 42 tiles of 256 x 256,
+// 175 us on 168 tiles with two stages, 131 us with four.
+using FwdSmallCfg = Cfg<2, 4, 2, 1, 4>;
+using FwdDeepCfg = Cfg<2, 4, 2, 1, 2, 4>;
+constexpr int64_t kDeepTiles = 256;  // one per CU
 // Adjoint: 8 waves in 2 x 4, each 64 x 32 -> 128 x 128 tiles, held to 128
 // registers (4 waves per SIMD) so that two workgroups share a CU and one's
 // loads and barriers overlap the other's MFMAs (the batched 512^3 products
 // have short K loops); the accumulator plus running sum fit that budget with
 // the epilogue walking one sub-tile at a time.
 using AdjCfg = Cfg<2, 4, 2, 1, 4>;
-static_assert(FwdCfg::BM == kBf16BM && FwdCfg::BN == kBf16BN, "forward tile");
+static_assert(FwdCfg::BM == kBf16BM && FwdCfg::BN == kBf16BM, "forward tile");
+static_assert(FwdSmallCfg::BM == kBf16SmallBM && FwdSmallCfg::BN == kBf16SmallBM, "small forward tile");
 static_assert(AdjCfg::BM == kAdjBM && AdjCfg::BN == kAdjBM, "adjoint tile");
 
 GemmGeom make_geom(const uint16_t* X, const uint16_t* Y, int64_t rows, int64_t cols,
                    int64_t rows_pad, int64_t cols_pad, int64_t kp, int32_t x_planes,
-                   int32_t y_planes, int bm, int bn) {
+                   int32_t y_planes, int bm) {
     GemmGeom g;
     g.rows = rows;
     g.cols = cols;
@@ -1340,7 +1400,8 @@ GemmGeom make_geom(const uint16_t* X, const uint16_t* Y, int64_t rows, int64_t c
     g.y_batch_elems = g.y_plane_elems * y_planes;
     g.kp = kp;
     g.tiles_m = (int32_t)(rows_pad / bm);
-    g.tiles_n = (int32_t)(cols_pad / bn);
+    g.tiles_n = (int32_t)(cols_pad / bm);
+    g.bm = bm;
     g.work = nullptr;
     return g;
 }
@@ -1349,17 +1410,22 @@ GemmGeom make_geom(const uint16_t* X, const uint16_t* Y, int64_t rows, int64_t c
 
 hipError_t launch_pfamily_gemm_bf16(const uint16_t* Ap, const uint16_t* Bp, int64_t b, int64_t m,
                                     int64_t n, int64_t mp, int64_t np, int64_t kp,
-                                    int32_t n_planes, const FamilyPlan& plan, const EpiArgs& epi,
+                                    int32_t n_planes, int bm, const FamilyPlan& plan, const EpiArgs& epi,
                                     hipStream_t st) {
-    const GemmGeom g = make_geom(Ap, Bp, m, n, mp, np, kp, n_planes, n_planes, kBf16BM, kBf16BN);
+    const GemmGeom g = make_geom(Ap, Bp, m, n, mp, np, kp, n_planes, n_planes, bm);
     const char* name = "mt_pfamily_gemm_bf16";
-    using CF = FwdCfg;
+    if (bm != kBf16BM && bm != kBf16SmallBM) return hipErrorInvalidValue;
+    const bool deep = b * (int64_t)g.tiles_m * g.tiles_n <= kDeepTiles;
     // the GEMM, then (when a tail list is given) the sparse tail for the
     // entries the tiles handed over
     const int64_t cap = (int64_t)epi.tail_max * b * g.tiles_m * g.tiles_n;
 #define MT_SEL(MODE, TO, R1)                                                                     \
     {                                                                                            \
-        hipError_t e = launch_gemm<CF, SelectEpi<CF, MODE, TO, R1>>(g, b, plan, epi, name, st);  \
+        hipError_t e =                                                                           \
+            bm == kBf16BM                                                                        \
+                ? launch_gemm<FwdCfg, SelectEpi<FwdCfg, MODE, TO, R1>>(g, b, plan, epi, name, st) \
+            : deep ? launch_gemm<FwdDeepCfg, SelectEpi<FwdDeepCfg, MODE, TO, R1>>(g, b, plan, epi, name, st)    \
+                   : launch_gemm<FwdSmallCfg, SelectEpi<FwdSmallCfg, MODE, TO, R1>>(g, b, plan, epi, name, st); \
         if (e == hipSuccess && epi.tail) e = launch_tail<MODE, TO, R1>(g, plan, epi, cap, st);   \
         return e;                                                                                \
     }
@@ -1370,7 +1436,7 @@ hipError_t launch_pfamily_gemm_bf16(const uint16_t* Ap, const uint16_t* Bp, int6
     }
     if (epi.low_need != nullptr) {
         // deferred planes (plain products, no r = 1 projection)
-        if (plan.r1 || epi.mode != EPI_PLAIN || !epi.tail) return hipErrorInvalidValue;
+        if (plan.r1 || epi.mode != EPI_PLAIN || !epi.tail || bm != kBf16BM) return hipErrorInvalidValue;
         if (epi.out_f64) MT_SEL(EPI_PLAIN, double, false) else MT_SEL(EPI_PLAIN, float, false)
     }
     if (epi.out_f64) MT_SEL2(EPI_PLAIN, double) else MT_SEL2(EPI_PLAIN, float)
@@ -1382,7 +1448,7 @@ hipError_t launch_rerun_gemm_bf16(const uint16_t* Ap, const uint16_t* Bp, int64_
                                   int64_t mp, int64_t np, int64_t kp, int32_t n_planes, const FamilyPlan& plan,
                                   const EpiArgs& epi, hipStream_t st) {
     if (epi.missed_tile == nullptr || plan.r1 || epi.mode != EPI_PLAIN) return hipErrorInvalidValue;
-    const GemmGeom g = make_geom(Ap, Bp, m, n, mp, np, kp, n_planes, n_planes, kBf16BM, kBf16BN);
+    const GemmGeom g = make_geom(Ap, Bp, m, n, mp, np, kp, n_planes, n_planes, kBf16BM);
     // a launch of its own name: the forward GEMM's timing and work stay apart
     // (a tile that is not marked adds no work and ends no span)
     if (epi.out_f64)
@@ -1397,7 +1463,7 @@ hipError_t launch_adjoint_gemm_bf16(const uint16_t* Xp, const uint16_t* Yp, int6
                                     int32_t x_planes, int32_t y_planes, const FamilyPlan& plan,
                                     const AdjArgs& adj, hipStream_t st) {
     const GemmGeom g =
-        make_geom(Xp, Yp, rows, cols, rows_pad, cols_pad, kp, x_planes, y_planes, kAdjBM, kAdjBM);
+        make_geom(Xp, Yp, rows, cols, rows_pad, cols_pad, kp, x_planes, y_planes, kAdjBM);
     const char* name = "mt_adjoint_gemm_bf16";
     using CA = AdjCfg;
     if (adj.m_f64) return launch_gemm<CA, AdjointEpi<CA, double>>(g, b, plan, adj, name, st);

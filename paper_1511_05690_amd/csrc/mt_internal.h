@@ -20,9 +20,10 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void glb_cvoid;
 
 // ---------------------------------------------------------------- tiling
-// BF16 p-family GEMM: 256 x 256 output tile per workgroup, K step 64.
+// BF16 p-family GEMM: 256 x 256 or 128 x 128 output tile per workgroup, K
+// step 64.
 constexpr int kBf16BM = 256;
-constexpr int kBf16BN = 256;
+constexpr int kBf16SmallBM = 128;
 constexpr int kBf16BK = 64;
 // FP64 p-family GEMM: BM x BM output tile (BM = 128 or 64), K step 16.
 constexpr int kF64BK = 16;
@@ -294,7 +295,7 @@ hipError_t launch_planes_if(const int32_t* cond, const void* A, const void* B, i
 
 // Fused p-family GEMM + selection epilogue.
 hipError_t launch_pfamily_gemm_bf16(const uint16_t* Ap, const uint16_t* Bp, int64_t b, int64_t m,
-                                    int64_t n, int64_t mp, int64_t np, int64_t kp, int32_t n_planes,
+                                    int64_t n, int64_t mp, int64_t np, int64_t kp, int32_t n_planes, int bm,
                                     const FamilyPlan& plan, const EpiArgs& epi, hipStream_t st);
 // The rerun launch of deferred planes: the tiles marked in epi.missed_tile
 // again from the start, every plane written, without the sparse tail.
