@@ -489,10 +489,6 @@ __global__ __launch_bounds__(kThreads, 2) void mt_pfamily_gemm_f64_kernel(GemmGe
     const double* Ybase = g.Y + (int64_t)t.bi * g.y_batch_elems + t.col0 * g.kp;
     const int nkt = (int)(g.kp / 16);
 
-    // Loads: lane l fills row R0 + l/8, physical 16-byte chunk l%8 holding
-    // logical chunk (l%8) ^ swz(row) = (l%8) ^ ((i&1)*4 + l/16).
-    const int32_t ld_even = (lane >> 3) * (int32_t)g.kp + (((lane & 7) ^ (lane >> 4)) * 2);
-    const int32_t ld_odd = (lane >> 3) * (int32_t)g.kp + (((lane & 7) ^ (4 + (lane >> 4))) * 2);
     // Operand reads: row l%16 of a 16-row block, k = 4*kk + l/16, i.e.
     // logical chunk 2*kk + l/32, half (l/16)&1; swizzle (l >> 1) & 7.
     const int32_t rd_base = (lane & 15) * 128 + (((lane >> 5) ^ ((lane >> 1) & 7)) * 16) + ((lane >> 4) & 1) * 8;
@@ -500,38 +496,53 @@ __global__ __launch_bounds__(kThreads, 2) void mt_pfamily_gemm_f64_kernel(GemmGe
     __syncthreads();
     const int nact = __builtin_amdgcn_readfirstlane(s_act[0]);
 
-    auto issue = [&](int ai, int s, int kt, int buf) {
-        const int e = __builtin_amdgcn_readfirstlane(s_act[1 + ai]);
-        const double* xsrc = Xbase + (int64_t)plan.e[e].a_plane[s] * g.x_plane_elems + kt * 16;
-        const double* ysrc = Ybase + (int64_t)plan.e[e].b_plane[s] * g.y_plane_elems + kt * 16;
-        uint8_t* la = smem + buf * C::BUF_BYTES;
-        uint8_t* lb = la + C::A_BYTES;
+    // Loads: instruction i of this wave fills rows R0 .. R0 + 7, R0 = (wave *
+    // G + i) * 8; lane l fills row R0 + l/8, physical 16-byte chunk l%8 holding
+    // logical chunk (l%8) ^ swz(row) = (l%8) ^ ((i&1)*4 + l/16).  The lane's
+    // addresses are set when the loads move to the next entry and advance by
+    // one K step per issue (looking the entry up for every step put an LDS
+    // read and a dependent scalar load in front of each step's MFMAs).
+    constexpr int G = C::BM / 32;
+    int la_ = 0, ls = 0, lkt = 0, lseg = 1;
+    const double *lx[G], *ly[G];
+    auto set_cursor = [&]() {
+        if (la_ >= nact) return;
+        const PlanEntry& pe = plan.e[__builtin_amdgcn_readfirstlane(s_act[1 + la_])];
+        lseg = pe.nseg;
+        const double* x = Xbase + (int64_t)pe.a_plane[ls] * g.x_plane_elems;
+        const double* y = Ybase + (int64_t)pe.b_plane[ls] * g.y_plane_elems;
 #pragma unroll
-        for (int i = 0; i < C::BM / 32; ++i) {
-            const int R0 = (wave * (C::BM / 32) + i) * 8;
-            const int32_t lo = (i & 1) ? ld_odd : ld_even;
-            __builtin_amdgcn_global_load_lds((glb_cvoid*)(xsrc + (int64_t)R0 * g.kp + lo),
-                                             (lds_void*)(la + R0 * 128), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((glb_cvoid*)(ysrc + (int64_t)R0 * g.kp + lo),
-                                             (lds_void*)(lb + R0 * 128), 16, 0, 0);
+        for (int i = 0; i < G; ++i) {
+            const int64_t o = (int64_t)((wave * G + i) * 8 + (lane >> 3)) * g.kp +
+                              (((lane & 7) ^ ((i & 1) * 4 + (lane >> 4))) * 2);
+            lx[i] = x + o;
+            ly[i] = y + o;
         }
     };
-    auto advance = [&](int& ai, int& s, int& kt) {
-        if (++kt == nkt) {
-            kt = 0;
-            const int e = __builtin_amdgcn_readfirstlane(s_act[1 + ai]);
-            if (++s == plan.e[e].nseg) {
-                s = 0;
-                ++ai;
+    // the next K step's loads into buffer b, and the cursor one step on
+    auto issue = [&](int b) {
+        uint8_t* la = smem + b * C::BUF_BYTES;
+        uint8_t* lb = la + C::A_BYTES;
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int R0 = (wave * G + i) * 8;
+            __builtin_amdgcn_global_load_lds((glb_cvoid*)lx[i], (lds_void*)(la + R0 * 128), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_cvoid*)ly[i], (lds_void*)(lb + R0 * 128), 16, 0, 0);
+            lx[i] += 16;
+            ly[i] += 16;
+        }
+        if (++lkt == nkt) {
+            lkt = 0;
+            if (++ls == lseg) {
+                ls = 0;
+                ++la_;
             }
+            set_cursor();
         }
     };
 
-    int la_ = 0, ls = 0, lkt = 0;
-    if (nkt > 0 && nact > 0) {
-        issue(la_, ls, lkt, 0);
-        advance(la_, ls, lkt);
-    }
+    set_cursor();
+    if (nkt > 0 && nact > 0) issue(0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
@@ -547,10 +558,8 @@ __global__ __launch_bounds__(kThreads, 2) void mt_pfamily_gemm_f64_kernel(GemmGe
 
         const int ntiles = plan.e[e].nseg * nkt;
         for (int st = 0; st < ntiles; ++st) {
-            if (la_ < nact) {
-                issue(la_, ls, lkt, buf ^ 1);
-                advance(la_, ls, lkt);
-            }
+            if (la_ < nact) issue(buf ^ 1);
+            __builtin_amdgcn_s_setprio(1);
             const uint8_t* pa = smem + buf * C::BUF_BYTES + t.wm * WT * 16 * 128;
             const uint8_t* pb = smem + buf * C::BUF_BYTES + C::A_BYTES + t.wn * WT * 16 * 128;
 #pragma unroll
@@ -568,6 +577,7 @@ __global__ __launch_bounds__(kThreads, 2) void mt_pfamily_gemm_f64_kernel(GemmGe
                         acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
             }
 
+            __builtin_amdgcn_s_setprio(0);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             buf ^= 1;
@@ -635,10 +645,8 @@ __global__ __launch_bounds__(kThreads, 2) void mt_pfamily_gemm_f64_kernel(GemmGe
                 la_ = n_down;
                 ls = 0;
                 lkt = 0;
-                if (nkt > 0) {
-                    issue(la_, ls, lkt, buf);
-                    advance(la_, ls, lkt);
-                }
+                set_cursor();
+                if (nkt > 0) issue(buf);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
             }
