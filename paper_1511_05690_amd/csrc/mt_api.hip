@@ -563,14 +563,16 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
     const double* dinv = bal ? (const double*)(ws + L.bal + 3 * align_up((size_t)(b * k) * 8)) : nullptr;
     const FamilyPlan plan = family_plan(f, ps, k);
     WsHeader* hdr = (WsHeader*)(ws + L.hdr);
-    // Deferred planes (plain products the pilot steers): the planes of the
+    // Deferred planes (products the pilot steers): the planes of the
     // smaller p are written only once some entry needs them, which the
     // pilot's sample tells before the GEMM, or a tile or tail entry that
     // reaches them tells after it (those tiles then run again, after the
     // planes of their rows are written).  BF16 path: the two smallest p;
     // FP64 path, whose tau puts p* near the largest p: all but the three
     // largest.
-    const bool defer = pilot && mode == EPI_PLAIN && !(f.flags & MT_FLAG_PROJECT_R2) && plan.n >= 5 &&
+    // (The BF16 path writes APSP's X in place from the GEMM, so nothing could
+    // be formed from it afterwards; the FP64 path writes it in the root pass.)
+    const bool defer = pilot && (mode == EPI_PLAIN || !f.bf16) && !(f.flags & MT_FLAG_PROJECT_R2) && plan.n >= 5 &&
                        g_defer_planes.load() != 0;
     const int32_t n_eval = defer ? (f.bf16 ? plan.n - 2 : 3) : plan.n;
     PlaneSpec ps_now = ps, ps_late = ps;

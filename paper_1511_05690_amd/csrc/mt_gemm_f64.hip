@@ -664,44 +664,104 @@ __global__ __launch_bounds__(kThreads, 2) void mt_pfamily_gemm_f64_kernel(GemmGe
 }
 
 // ------------------------------------------------------------ the sparse tail
-// One wave per handed-over entry: S_p as an FP64 dot product of the entry's
-// X and Y plane rows for the plan entries from e_next on, recorded exactly
-// as the record epilogue does (S, p* index; with the r = 1 projection S at
-// the next smaller p in out2) for the select-root pass.
-// S_p of one entry: lane l sums the 2-element chunks l, l + 64, ... in
-// order, U chunks loaded before any is used (16 loads in flight per wave).
-__device__ double tail_dot_f64(const double* xr, const double* yr, const PlanEntry& pe, const GemmGeomF64& g,
-                               int lane) {
-    const double* xp = xr + (int64_t)pe.a_plane[0] * g.x_plane_elems;
-    const double* yp = yr + (int64_t)pe.b_plane[0] * g.y_plane_elems;
-    double acc = 0.0;
+// Handed-over entries: S_p as an FP64 dot product of the entry's X and Y plane
+// rows for the plan entries from e_next on, recorded exactly as the record
+// epilogue does (S, p* index; with the r = 1 projection S at the next smaller
+// p in out2) for the select-root pass.
+//
+// Bound by the plane rows' bytes, mostly from the caches: a wave takes up to
+// kTailGroup entries of one row and state together and loads the row's X
+// chunks once for them (2048-vertex APSP, 11 squarings: 2.58 ms one entry at
+// a time, 1.72 ms in groups of four).  Lane l sums the 2-element chunks l, l + 64,
+// ... in order, U chunks loaded before any is used.
+constexpr int kTailGroup = 4;
+template <int N>
+__device__ __forceinline__ void tail_dot_n_f64(const double* xp, const double* const (&yp)[N], int64_t kp, int lane,
+                                               double (&S)[N]) {
+    constexpr int U = N == 1 ? 8 : 4;
+    double acc[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) acc[q] = 0.0;
     int64_t k0 = lane * 2;
-    constexpr int U = 8;
-    for (; k0 + (U - 1) * 128 < g.kp; k0 += U * 128) {
-        double2 vx[U], vy[U];
+    for (; k0 + (U - 1) * 128 < kp; k0 += U * 128) {
+        double2 vx[U], vy[N][U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             vx[u] = *(const double2*)(xp + k0 + u * 128);
-            vy[u] = *(const double2*)(yp + k0 + u * 128);
+#pragma unroll
+            for (int q = 0; q < N; ++q) vy[q][u] = *(const double2*)(yp[q] + k0 + u * 128);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            acc = fma(vx[u].x, vy[u].x, acc);
-            acc = fma(vx[u].y, vy[u].y, acc);
+        for (int q = 0; q < N; ++q)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                acc[q] = fma(vx[u].x, vy[q][u].x, acc[q]);
+                acc[q] = fma(vx[u].y, vy[q][u].y, acc[q]);
+            }
+    }
+    for (; k0 < kp; k0 += 128) {
+        const double2 vx = *(const double2*)(xp + k0);
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const double2 vy = *(const double2*)(yp[q] + k0);
+            acc[q] = fma(vx.x, vy.x, acc[q]);
+            acc[q] = fma(vx.y, vy.y, acc[q]);
         }
     }
-    for (; k0 < g.kp; k0 += 128) {
-        const double2 vx = *(const double2*)(xp + k0), vy = *(const double2*)(yp + k0);
-        acc = fma(vx.x, vy.x, acc);
-        acc = fma(vx.y, vy.y, acc);
-    }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d);
-    return acc;
+    for (int q = 0; q < N; ++q) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) acc[q] += __shfl_xor(acc[q], d);
+        S[q] = acc[q];
+    }
+}
+// S of the active entries of a group at plan entry pe (the others' S is left).
+__device__ void tail_dot_group_f64(const double* xr, const double* const (&yr)[kTailGroup],
+                                   const bool (&act)[kTailGroup], const PlanEntry& pe, const GemmGeomF64& g, int lane,
+                                   double (&S)[kTailGroup]) {
+    const double* xp = xr + (int64_t)pe.a_plane[0] * g.x_plane_elems;
+    const int64_t oy = (int64_t)pe.b_plane[0] * g.y_plane_elems;
+    int n_act = 0, only = 0;
+#pragma unroll
+    for (int q = 0; q < kTailGroup; ++q)
+        if (act[q]) {
+            ++n_act;
+            only = q;
+        }
+    if (n_act == 1) {
+        const double* y = yr[0];
+#pragma unroll
+        for (int q = 1; q < kTailGroup; ++q)
+            if (only == q) y = yr[q];
+        const double* const y1[1] = {y + oy};
+        double s1[1];
+        tail_dot_n_f64<1>(xp, y1, g.kp, lane, s1);
+#pragma unroll
+        for (int q = 0; q < kTailGroup; ++q)
+            if (only == q) S[q] = s1[0];
+        return;
+    }
+    // an inactive entry repeats an active one's row (its loads hit the same
+    // lines) and its sum is dropped
+    const double* yp[kTailGroup];
+#pragma unroll
+    for (int q = 0; q < kTailGroup; ++q) {
+        const double* y = yr[0];
+#pragma unroll
+        for (int t = 0; t < kTailGroup; ++t)
+            if ((act[q] ? q : only) == t) y = yr[t];
+        yp[q] = y + oy;
+    }
+    double Sg[kTailGroup];
+    tail_dot_n_f64<kTailGroup>(xp, yp, g.kp, lane, Sg);
+#pragma unroll
+    for (int q = 0; q < kTailGroup; ++q)
+        if (act[q]) S[q] = Sg[q];
 }
 
 template <bool R1>
 __global__ __launch_bounds__(256) void mt_tail_f64_kernel(GemmGeomF64 g, FamilyPlan plan, EpiArgs a) {
+    constexpr int G = kTailGroup;
     const int lane = threadIdx.x & 63;
     const uint32_t count = __builtin_amdgcn_readfirstlane(*a.tail_count);
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
@@ -715,52 +775,136 @@ __global__ __launch_bounds__(256) void mt_tail_f64_kernel(GemmGeomF64 g, FamilyP
     // for the rerun launch instead
     int n_eval = MT_MAX_P;
     if (a.low_need != nullptr && __builtin_amdgcn_readfirstlane(*a.low_need) == 0) n_eval = a.n_eval;
-    for (int64_t w = w0; w < w1; ++w) {
-        const TailEntry te = a.tail_sorted[w];
-        const int64_t o = ((int64_t)te.bi * g.rows + te.i) * g.cols + te.j;
-        const double* xr = g.X + (int64_t)te.bi * g.x_batch_elems + (int64_t)te.i * g.kp;
-        const double* yr = g.Y + (int64_t)te.bi * g.y_batch_elems + (int64_t)te.j * g.kp;
-        if (!R1 && te.state == kTailRise) {
+    const int last = plan.n - 1;
+    for (int64_t w = w0; w < w1;) {
+        // up to G entries of one row and state, each with the plan entry it
+        // runs next (nxt, -1: done)
+        const TailEntry t0 = a.tail_sorted[w];
+        const int64_t row = (int64_t)t0.bi * g.rows + t0.i;
+        const double* xr = g.X + (int64_t)t0.bi * g.x_batch_elems + (int64_t)t0.i * g.kp;
+        const double* yr[G];
+        int64_t o[G];
+        int nxt[G], col[G];
+        int gn = 0;
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            nxt[q] = -1;
+            col[q] = t0.j;
+            bool in = q == 0;
+            if (q > 0 && gn == q && w + q < w1) {
+                const TailEntry t = a.tail_sorted[w + q];
+                in = t.bi == t0.bi && t.i == t0.i && t.state == t0.state;
+                if (in) {
+                    col[q] = t.j;
+                    nxt[q] = t.e_next;
+                }
+            }
+            if (q == 0) nxt[q] = t0.e_next;
+            if (in) ++gn;
+            yr[q] = g.Y + (int64_t)t0.bi * g.y_batch_elems + (int64_t)col[q] * g.kp;
+            o[q] = row * g.cols + col[q];
+        }
+        w += gn;
+        auto mark = [&](int q) {
+            if (lane == 0) {
+                a.missed_tile[((int64_t)t0.bi * g.tiles_m + t0.i / g.bm) * g.tiles_n + col[q] / g.bm] = 1u;
+                *a.low_missed = 1;
+            }
+        };
+        bool act[G];
+        double S[G];
+        if (!R1 && t0.state == kTailRise) {
             // stable at e_next + 1 (recorded): go up while a larger p may be
             // stable too; an unstable p leaves the record below standing
-            for (int e = te.e_next; e >= 0; --e) {
+            while (true) {
+                int e = -1;
+#pragma unroll
+                for (int q = 0; q < G; ++q) e = max(e, nxt[q]);
+                if (e < 0) break;
+#pragma unroll
+                for (int q = 0; q < G; ++q) act[q] = nxt[q] == e;
                 const PlanEntry& pe = plan.e[e];
-                const double acc = tail_dot_f64(xr, yr, pe, g, lane);
-                if (!(acc >= plan.tau)) break;
-                if (lane == 0) {
-                    out[o] = acc;
-                    a.pstar[o] = (uint8_t)pe.pidx;
+                tail_dot_group_f64(xr, yr, act, pe, g, lane, S);
+#pragma unroll
+                for (int q = 0; q < G; ++q) {
+                    if (!act[q]) continue;
+                    nxt[q] = -1;
+                    if (!(S[q] >= plan.tau)) continue;
+                    if (lane == 0) {
+                        out[o[q]] = S[q];
+                        a.pstar[o[q]] = (uint8_t)pe.pidx;
+                    }
+                    if (S[q] >= pe.rise_thr) nxt[q] = e - 1;
                 }
-                if (!(acc >= pe.rise_thr)) break;
             }
             continue;
         }
-        bool pend = R1 && te.state == kTailR1;
-        for (int e = te.e_next; e < plan.n; ++e) {
+        // going down from e_next.  An entry whose S is exactly 0 (every term 0
+        // or underflowed: pairs a sparse APSP operand does not connect) looks
+        // at the smallest p, once and where its planes are written: if S is
+        // below tau there too, no p between them is stable, since S_p does not
+        // grow with p for terms in [0, 1]; otherwise it goes on from where it
+        // was (back).
+        constexpr int kNotLooked = -1, kLooked = -2;
+        bool pend[G];
+        int back[G];
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            pend[q] = R1 && t0.state == kTailR1;
+            back[q] = kNotLooked;
+        }
+        while (true) {
+            int e = MT_MAX_P;
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+                if (nxt[q] >= 0) e = min(e, nxt[q]);
+            if (e >= MT_MAX_P) break;
+#pragma unroll
+            for (int q = 0; q < G; ++q) act[q] = nxt[q] == e;
             if (e >= n_eval) {
-                if (lane == 0) {
-                    a.missed_tile[((int64_t)te.bi * g.tiles_m + te.i / g.bm) * g.tiles_n + te.j / g.bm] = 1u;
-                    *a.low_missed = 1;
-                }
-                break;
-            }
-            const PlanEntry& pe = plan.e[e];
-            const double acc = tail_dot_f64(xr, yr, pe, g, lane);
-            if (R1 && pend) {
-                if (lane == 0) out2[o] = acc;
-                break;
-            }
-            const bool stable = acc >= plan.tau;
-            if (!(stable || e == plan.n - 1)) continue;
-            if (lane == 0) {
-                out[o] = acc;
-                a.pstar[o] = stable ? (uint8_t)pe.pidx : (uint8_t)MT_PSTAR_NONE;
-            }
-            if (R1 && stable && pe.inv_dp > 0.f) {
-                pend = true;
+#pragma unroll
+                for (int q = 0; q < G; ++q)
+                    if (act[q]) {
+                        mark(q);
+                        nxt[q] = -1;
+                    }
                 continue;
             }
-            break;
+            const PlanEntry& pe = plan.e[e];
+            tail_dot_group_f64(xr, yr, act, pe, g, lane, S);
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                if (!act[q]) continue;
+                if (R1 && pend[q]) {
+                    if (lane == 0) out2[o[q]] = S[q];
+                    nxt[q] = -1;
+                    continue;
+                }
+                const bool stable = S[q] >= plan.tau;
+                if (back[q] >= 0 && stable) {
+                    // stable at the smallest p after all: the p in between
+                    nxt[q] = back[q] + 1;
+                    back[q] = kLooked;
+                    continue;
+                }
+                if (!(stable || e == last)) {
+                    nxt[q] = e + 1;
+                    if (!R1 && S[q] == 0.0 && back[q] == kNotLooked && e + 1 < last && last < n_eval) {
+                        back[q] = e;
+                        nxt[q] = last;
+                    }
+                    continue;
+                }
+                if (lane == 0) {
+                    out[o[q]] = S[q];
+                    a.pstar[o[q]] = stable ? (uint8_t)pe.pidx : (uint8_t)MT_PSTAR_NONE;
+                }
+                nxt[q] = -1;
+                if (R1 && stable && pe.inv_dp > 0.f) {
+                    pend[q] = true;
+                    nxt[q] = e + 1;
+                }
+            }
         }
     }
 }
@@ -849,7 +993,7 @@ hipError_t launch_pfamily_gemm_f64(const double* Ap, const double* Bp, int64_t b
 hipError_t launch_rerun_gemm_f64(const double* Ap, const double* Bp, int64_t b, int64_t m, int64_t n, int64_t mp,
                                  int64_t np, int64_t kp, int32_t n_planes, int bm, const FamilyPlan& plan,
                                  const EpiArgs& epi, hipStream_t st) {
-    if (epi.missed_tile == nullptr || plan.r1 || epi.mode != EPI_PLAIN) return hipErrorInvalidValue;
+    if (epi.missed_tile == nullptr || plan.r1 || epi.mode == EPI_STORE_ALL) return hipErrorInvalidValue;
     const GemmGeomF64 g = make_geom(Ap, Bp, m, n, mp, np, kp, n_planes, n_planes, bm);
     // a launch of its own name: the forward GEMM's timing and work stay apart
     // (a tile that is not marked adds no work and ends no span)
