@@ -353,9 +353,8 @@ Geom product_geom(const Family& f, int64_t b, int64_t m, int64_t k, int64_t n) {
 }
 
 struct Layout {
-    size_t hdr, r, c, bal, ap, bp, s, s2, code, tail, tail_sorted, tail_bucket, pilot, missed, x, total;
+    size_t hdr, r, c, bal, ap, bp, s, s2, code, tail, tail_sorted, tile_count, pilot, missed, x, total;
     int32_t tail_max;  // sparse-tail threshold the layout was sized for (0: no tail)
-    int32_t tail_shift, tail_buckets;  // row buckets of the tail sort
 };
 
 // A tile with at most this many undecided entries hands them to the sparse
@@ -418,16 +417,11 @@ Layout product_layout(const Family& f, const PlaneSpec& ps, const Geom& g, int64
     const size_t list_bytes = align_up((size_t)tiles * (size_t)L.tail_max * sizeof(TailEntry));
     L.tail = off;
     off += list_bytes;
-    // the list sorted by row bucket and state (two buckets per row bucket):
-    // rows (over the batch) merged in powers of two until at most
-    // kTailBuckets buckets remain
-    L.tail_shift = 0;
-    while (2 * (((b * m - 1) >> L.tail_shift) + 1) > kTailBuckets) ++L.tail_shift;
-    L.tail_buckets = L.tail_max > 0 && b * m > 0 ? (int32_t)(2 * (((b * m - 1) >> L.tail_shift) + 1)) : 0;
+    // the list with the entries of a row together, and each tile's count
     L.tail_sorted = off;
     off += L.tail_max > 0 ? list_bytes : 0;
-    L.tail_bucket = off;
-    off += align_up((size_t)(L.tail_buckets + 3) / 4 * 16);
+    L.tile_count = off;
+    off += L.tail_max > 0 ? align_up((size_t)tiles * 4) : 0;
     // pilot partial sums (float on the BF16 path, double on FP64)
     L.pilot = off;
     off += f.n > 1 ? align_up((size_t)kPilotKParts * f.n * kMaxPilotSide * kMaxPilotSide * (f.bf16 ? 4 : 8)) +
@@ -525,25 +519,25 @@ size_t pilot_part_bytes(const Family& f) {
 
 // The tail's list is sorted by row where one power's planes of both operands
 // exceed this: entries of a row then share the loads of its plane row.
-// Smaller planes stay in the caches whatever the order, and the three sort
-// launches (about 5 us each) cost more than the sharing gives.
+// Smaller planes stay in the caches whatever the order, and the sort's launch
+// (5 us and more) costs more than the sharing gives.
 constexpr int64_t kTailSortBytes = (int64_t)32 << 20;
 
-bool sorts_tail(const Geom& g, int64_t b) {
-    return b * (g.mp + g.np) * g.kp * (int64_t)g.esize > kTailSortBytes;
+bool sorts_tail(const Geom& g, const Layout& L, int64_t b) {
+    // (a tile's place in the list is a 32-bit index)
+    return b * (g.mp + g.np) * g.kp * (int64_t)g.esize > kTailSortBytes &&
+           b * (g.mp / g.bm) * (g.np / g.bm) * L.tail_max <= (int64_t)0xffffffff;
 }
 
 // What run_product's kernels expect set in the workspace before them: the
 // tail count, where the search starts, the deferred-plane flags, the pilot's
-// counts, the tail's buckets (the domain flag is the caller's).
-void product_fills(const Family& f, const Geom& g, const Layout& L, uint8_t* ws, int64_t b, int64_t k, int32_t s0,
-                   bool pilot, FillList* fills) {
+// counts (the domain flag is the caller's).
+void product_fills(const Family& f, const Layout& L, uint8_t* ws, int32_t s0, bool pilot, FillList* fills) {
     WsHeader* hdr = (WsHeader*)(ws + L.hdr);
     fills->add(&hdr->tail_count, 1);
     fills->add(&hdr->start, 1, (uint32_t)(s0 < 0 ? 0 : (s0 < f.n ? s0 : f.n - 1)));
     fills->add(&hdr->low_missed, 2);
     if (pilot) fills->add(ws + L.pilot + pilot_part_bytes(f), sizeof(PilotCounts) / 4);
-    if (L.tail_max > 0 && k > 0 && sorts_tail(g, b)) fills->add(ws + L.tail_bucket, (L.tail_buckets + 3) / 4 * 4);
 }
 
 // The product pipeline on already-validated arguments (and the workspace set
@@ -655,11 +649,9 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
         epi.tail = (TailEntry*)(ws + L.tail);
         epi.tail_count = &hdr->tail_count;
         epi.tail_max = L.tail_max;
-        const bool sorted = sorts_tail(g, b);
+        const bool sorted = sorts_tail(g, L, b);
         epi.tail_sorted = sorted ? (TailEntry*)(ws + L.tail_sorted) : epi.tail;
-        epi.tail_bucket = (int32_t*)(ws + L.tail_bucket);
-        epi.tail_shift = L.tail_shift;
-        epi.tail_buckets = sorted ? L.tail_buckets : 0;
+        epi.tile_count = sorted ? (uint32_t*)(ws + L.tile_count) : nullptr;
     }
     if (f.bf16) {
         epi.mode = mode;
@@ -880,7 +872,7 @@ mt_status estimate_impl(const void* A, const void* B, mt_dtype dtype, int64_t b,
     if (bal) fills.add(ws + L.bal, b * k * 2);  // column maxima of A
     const int32_t s0 = g_start_entry.load();
     const bool pilot = uses_pilot(f, L, s0, b, m, k, n);
-    product_fills(f, g, L, ws, b, k, s0, pilot, &fills);
+    product_fills(f, L, ws, s0, pilot, &fills);
     MT_TRY(launch_fills(fills, st), "clear header and column maxima");
     bool fuse_rowmax = false;
     if (bal) {
@@ -988,7 +980,7 @@ mt_status apsp_estimate(const float* W, int64_t n, double s_scale, int32_t n_squ
     FillList fills;
     const int32_t s0 = g_start_entry.load();
     const bool pilot = uses_pilot(f, L, s0, 1, n, n, n);
-    product_fills(f, g, L, ws, 1, n, s0, pilot, &fills);
+    product_fills(f, L, ws, s0, pilot, &fills);
     for (int t = 0; t < T; ++t) {
         MT_TRY(launch_fills(fills, st), "clear product state");
         s = run_product(X, X, x_f64, 1, n, n, n, f, ps, g, L, ws, false, EPI_APSP_X, 1, X, x_f64,

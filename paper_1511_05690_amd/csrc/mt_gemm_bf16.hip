@@ -167,6 +167,16 @@ struct SelectEpi {
     // end.
     __device__ int down_end(const FamilyPlan& plan) const { return min(plan.n, n_eval); }
     static __device__ bool skip_tile(const Args& a, int64_t tile) { return RERUN && a.missed_tile[tile] == 0u; }
+    // The tile's number of handed-over entries (0 first).
+    __device__ void record_count(int64_t tile, uint32_t n) const {
+        if (!RERUN && a.tile_count != nullptr) a.tile_count[tile] = n;
+    }
+    // Where this tile's `total` entries go in the tail list (one thread).
+    __device__ uint32_t take_slots(int64_t tile, int total) const {
+        if (a.tile_count == nullptr) return atomicAdd(a.tail_count, (uint32_t)total);
+        a.tile_count[tile] = (uint32_t)total;
+        return (uint32_t)(tile * a.tail_max);
+    }
     __device__ void record_tile(int64_t tile, bool missed) const {
         if (RERUN || a.missed_tile == nullptr) return;
         a.missed_tile[tile] = missed ? 1u : 0u;
@@ -196,7 +206,6 @@ struct SelectEpi {
     }
     __device__ int32_t start_index() const { return (!R1 && a.start) ? *a.start : 0; }
     __device__ bool can_hand_over(int total) const { return !RERUN && a.tail != nullptr && total <= a.tail_max; }
-    __device__ uint32_t* tail_counter() const { return a.tail_count; }
     // Write this lane's undecided entries to the sparse-tail list from `pos`
     // on, after plan entry e of a search that started at plan entry s.
     __device__ void hand_over(uint32_t pos, int e, int s, const TileCtx& t) const {
@@ -534,7 +543,8 @@ struct AdjointEpi {
     __device__ void counts(int& open, int& parked) const { open = parked = 0; }
     __device__ int32_t start_index() const { return 0; }
     __device__ bool can_hand_over(int) const { return false; }
-    __device__ uint32_t* tail_counter() const { return nullptr; }
+    __device__ uint32_t take_slots(int64_t, int) const { return 0u; }
+    __device__ void record_count(int64_t, uint32_t) const {}
     __device__ void hand_over(uint32_t, int, int, const TileCtx&) const {}
 
     __device__ void setup(const TileCtx& t, const GemmGeom& g, uint8_t* lds, int tid) {
@@ -881,7 +891,10 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
     else __syncthreads();
 
     int64_t kunits = 0;  // executed MFMA work in units of BM x BN x 1 products
-    if (tid == 0) epi.record_tile(tile_id, false);
+    if (tid == 0) {
+        epi.record_tile(tile_id, false);
+        epi.record_count(tile_id, 0u);
+    }
     for (int ai = 0; ai < nact; ++ai) {
         const int e = entry_of(ai);
         f32x16 acc[WT_M][WT_N];
@@ -1019,7 +1032,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
             // Only a few are left: hand them to the sparse tail, which runs
             // the remaining p for them alone, and stop the tile.
             if (ai + 1 < nact && epi.can_hand_over(total)) {
-                if (tid == 0) s_tail_base = atomicAdd(epi.tail_counter(), (uint32_t)total);
+                if (tid == 0) s_tail_base = epi.take_slots(tile_id, total);
                 __syncthreads();
                 epi.hand_over(s_tail_base + (uint32_t)(wave_pre + lane_pre), e, s, t);
                 break;
@@ -1325,9 +1338,9 @@ __global__ __launch_bounds__(256) void mt_tail_bf16_kernel(GemmGeom g, FamilyPla
 }
 
 template <int MODE, typename TO, bool R1>
-hipError_t launch_tail(const GemmGeom& g, const FamilyPlan& plan, const EpiArgs& epi, int64_t cap,
+hipError_t launch_tail(const GemmGeom& g, int64_t b, const FamilyPlan& plan, const EpiArgs& epi, int64_t cap,
                        hipStream_t st) {
-    hipError_t e = launch_tail_sort(epi, g.rows, cap, st);
+    hipError_t e = launch_tail_sort(epi, b * g.tiles_m, g.tiles_n, g.bm, st);
     if (e != hipSuccess) return e;
     int64_t blocks = (cap + 3) / 4;
     if (blocks > 2048) blocks = 2048;
@@ -1426,7 +1439,7 @@ hipError_t launch_pfamily_gemm_bf16(const uint16_t* Ap, const uint16_t* Bp, int6
                 ? launch_gemm<FwdCfg, SelectEpi<FwdCfg, MODE, TO, R1>>(g, b, plan, epi, name, st) \
             : deep ? launch_gemm<FwdDeepCfg, SelectEpi<FwdDeepCfg, MODE, TO, R1>>(g, b, plan, epi, name, st)    \
                    : launch_gemm<FwdSmallCfg, SelectEpi<FwdSmallCfg, MODE, TO, R1>>(g, b, plan, epi, name, st); \
-        if (e == hipSuccess && epi.tail) e = launch_tail<MODE, TO, R1>(g, plan, epi, cap, st);   \
+        if (e == hipSuccess && epi.tail) e = launch_tail<MODE, TO, R1>(g, b, plan, epi, cap, st);   \
         return e;                                                                                \
     }
 #define MT_SEL2(MODE, TO) \

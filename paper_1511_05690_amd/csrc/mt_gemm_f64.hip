@@ -85,6 +85,16 @@ struct RecordEpi {
     // end.
     __device__ int down_end(const FamilyPlan& plan) const { return min(plan.n, n_eval); }
     static __device__ bool skip_tile(const Args& a, int64_t tile) { return RERUN && a.missed_tile[tile] == 0u; }
+    // The tile's number of handed-over entries (0 first).
+    __device__ void record_count(int64_t tile, uint32_t n) const {
+        if (!RERUN && a.tile_count != nullptr) a.tile_count[tile] = n;
+    }
+    // Where this tile's `total` entries go in the tail list (one thread).
+    __device__ uint32_t take_slots(int64_t tile, int total) const {
+        if (a.tile_count == nullptr) return atomicAdd(a.tail_count, (uint32_t)total);
+        a.tile_count[tile] = (uint32_t)total;
+        return (uint32_t)(tile * a.tail_max);
+    }
     __device__ void record_tile(int64_t tile, bool missed) const {
         if (RERUN || a.missed_tile == nullptr) return;
         a.missed_tile[tile] = missed ? 1u : 0u;
@@ -111,7 +121,6 @@ struct RecordEpi {
     }
     __device__ int32_t start_index() const { return (!R1 && a.start) ? *a.start : 0; }
     __device__ bool can_hand_over(int total) const { return !RERUN && a.tail != nullptr && total <= a.tail_max; }
-    __device__ uint32_t* tail_counter() const { return a.tail_count; }
     // Write this lane's undecided entries to the sparse-tail list from `pos`
     // on, after plan entry e of a search that started at plan entry s.
     __device__ void hand_over(uint32_t pos, int e, int s, const TileCtx& t) const {
@@ -273,7 +282,8 @@ struct StoreAllEpi {
     __device__ void counts(int& open, int& parked) const { open = parked = 0; }
     __device__ int32_t start_index() const { return 0; }
     __device__ bool can_hand_over(int) const { return false; }
-    __device__ uint32_t* tail_counter() const { return nullptr; }
+    __device__ uint32_t take_slots(int64_t, int) const { return 0u; }
+    __device__ void record_count(int64_t, uint32_t) const {}
     __device__ void hand_over(uint32_t, int, int, const TileCtx&) const {}
 
     __device__ void setup(const TileCtx& t, const GemmGeomF64& g, uint8_t*, int) {
@@ -328,7 +338,8 @@ struct AdjointEpiF64 {
     __device__ void counts(int& open, int& parked) const { open = parked = 0; }
     __device__ int32_t start_index() const { return 0; }
     __device__ bool can_hand_over(int) const { return false; }
-    __device__ uint32_t* tail_counter() const { return nullptr; }
+    __device__ uint32_t take_slots(int64_t, int) const { return 0u; }
+    __device__ void record_count(int64_t, uint32_t) const {}
     __device__ void hand_over(uint32_t, int, int, const TileCtx&) const {}
 
     __device__ void setup(const TileCtx& t, const GemmGeomF64& g, uint8_t* lds, int tid) {
@@ -468,7 +479,10 @@ __global__ __launch_bounds__(kThreads, 2) void mt_pfamily_gemm_f64_kernel(GemmGe
     Epi epi;
     epi.a = args;
     epi.setup(t, g, smem + C::PIPE_BYTES, tid);
-    if (tid == 0) epi.record_tile(tile_id, false);
+    if (tid == 0) {
+        epi.record_tile(tile_id, false);
+        epi.record_count(tile_id, 0u);
+    }
     // The p search starts at plan entry e0 (0: the largest p), goes down to
     // the smallest p and then up from e0 - 1 to the largest; s_act holds the
     // active plan entries in that order.
@@ -626,7 +640,7 @@ __global__ __launch_bounds__(kThreads, 2) void mt_pfamily_gemm_f64_kernel(GemmGe
             if (total == 0) break;
             // a few left: the sparse tail finishes them
             if (ai + 1 < nact && epi.can_hand_over(total)) {
-                if (tid == 0) s_tail_base = atomicAdd(epi.tail_counter(), (uint32_t)total);
+                if (tid == 0) s_tail_base = epi.take_slots(tile_id, total);
                 __syncthreads();
                 epi.hand_over(s_tail_base + (uint32_t)(wave_pre + lane_pre), e, e0, t);
                 break;
@@ -976,7 +990,7 @@ hipError_t launch_pfamily_gemm_f64(const double* Ap, const double* Bp, int64_t b
     if (e != hipSuccess || !epi.tail) return e;
     // the sparse tail for the entries the tiles handed over
     const int64_t cap = (int64_t)epi.tail_max * b * g.tiles_m * g.tiles_n;
-    e = launch_tail_sort(epi, g.rows, cap, st);
+    e = launch_tail_sort(epi, b * g.tiles_m, g.tiles_n, bm, st);
     if (e != hipSuccess) return e;
     int64_t blocks = (cap + 3) / 4;
     if (blocks > 2048) blocks = 2048;

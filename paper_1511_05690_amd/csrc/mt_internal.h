@@ -104,14 +104,14 @@ struct EpiArgs {
     uint32_t* tail_count;
     int32_t tail_max;    // a tile with 1..tail_max undecided entries hands them over
     const int32_t* start;  // nullable: plan index the p search starts at (0: largest p)
-    // The tail kernel runs the list sorted by row bucket (bi * rows + i) >>
-    // tail_shift and state, so that entries of one row can share its plane
-    // rows: tail_sorted has the list's capacity, tail_bucket one int32 per
-    // bucket (tail_buckets of them, two per row bucket, at most kTailBuckets).
+    // With tile_count (one word per output tile) each tile hands over into its
+    // own tail_max slots of `tail` and writes its count there; the tail sort
+    // then fills tail_sorted (the list's capacity), entries of one row and
+    // state together, and *tail_count.  Without it the tiles append to `tail`
+    // through *tail_count and the tail runs the list as it is (tail_sorted ==
+    // tail).
     TailEntry* tail_sorted;
-    int32_t* tail_bucket;
-    int32_t tail_shift;
-    int32_t tail_buckets;
+    uint32_t* tile_count;
     int64_t stack_stride;  // EPI_STORE_ALL: elements per plane of the S stack (b m n)
     // Deferred planes (the forward GEMMs): the planes of plan entries n_eval
     // and beyond are written before the GEMM only when *low_need is set.
@@ -125,7 +125,6 @@ struct EpiArgs {
     uint32_t* missed_tile;  // b x tiles_m x tiles_n: 1 where the tile must run again
     int32_t n_eval;         // plan entries whose planes are always written
 };
-constexpr int64_t kTailBuckets = 65536;
 
 // Adjoint epilogue: out = sum over the p that some entry uses of
 // (M / scale_rows / scale_cols)^(p-1) .* (X_p Y_p^T).
@@ -152,7 +151,7 @@ struct AdjArgs {
 hipError_t launch_fill_zero_u32(void* p, int64_t words, hipStream_t st);
 hipError_t launch_fill_u32(void* p, uint32_t value, int64_t words, hipStream_t st);
 // Several fills in one launch: everything a product expects cleared (header,
-// column maxima, pilot counts, tail buckets) is set before its first kernel
+// column maxima, pilot counts) is set before its first kernel
 // by one launch of about 5 us instead of five.
 struct FillList {
     static constexpr int kMax = 8;
@@ -213,12 +212,11 @@ hipError_t launch_exact_rows(const float* W, int64_t n, const int32_t* src, int3
 size_t affine_workspace();
 hipError_t launch_affine_correct(void* D, int f64, int64_t n, const int32_t* src, int32_t nsrc, const double* ex,
                                  double* ab, uint8_t* ws, int apply, hipStream_t st);
-// Counting sort of the sparse-tail list (length *count, read on the device)
-// into epi.tail_sorted by row bucket; rows = rows of the output per batch item.
-// The buckets are cleared by the caller.  Without buckets (tail_buckets 0) the
-// tail runs the list as it is (epi.tail_sorted == epi.tail) and nothing is
-// launched.
-hipError_t launch_tail_sort(const EpiArgs& epi, int64_t rows, int64_t cap, hipStream_t st);
+// The tail entries of every tile (epi.tile_count) into epi.tail_sorted, those
+// of one output row and state together, their number into *epi.tail_count
+// (zero before the launch); nothing without epi.tile_count.  tile_rows = output
+// tile rows over the batch, tiles_n = tiles of each, bm = the tile side.
+hipError_t launch_tail_sort(const EpiArgs& epi, int64_t tile_rows, int tiles_n, int bm, hipStream_t st);
 // Row maxima of A (rows x k; with mul, of A_rj mul[r / rows_per_batch][j])
 // and column maxima of B (b x k x n; with mul, of B_bkj mul[b][k]; c is zero
 // before the launch).
