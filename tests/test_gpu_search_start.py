@@ -225,3 +225,34 @@ def test_pilot_start(knobs, path):
     rows = np.arange(0, m, 97)
     ref = oracle.pnorm_estimate_rows(A, B, P128, TAU[path], rows)
     compare_estimate(res[-1][0][rows], res[-1][1][rows], ref, P128, path)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_pilot_start_is_no_more_work_than_top_down(gpu_lib, seed):
+    """Log-normal products have a few entries per tile at a small p, mostly
+    missing from the pilot's sample: the start it chooses must not run that p
+    (and a way up) densely where the search from the largest p hands those
+    entries to the tail."""
+    import torch
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    A, B = (torch.randn((2560, 2560), generator=g, device="cuda").mul_(2).exp_().clamp_(max=1e6) for _ in range(2))
+    P = [1, 2, 4, 8, 16, 32, 64, 128]
+    work = {}
+    old = gpu_lib.search_start()
+    try:
+        for start in (-1, 0):
+            gpu_lib.set_search_start(start)
+            gpu_lib.timing_reset()
+            gpu_lib.timing_enable(True)
+            gpu_lib.estimate(A, B, P=P, path="bf16")
+            torch.cuda.synchronize()
+            work[start] = gpu_lib.timing_work("mt_pfamily_gemm_bf16")
+            gpu_lib.timing_enable(False)
+    finally:
+        gpu_lib.timing_enable(False)
+        gpu_lib.timing_reset()
+        gpu_lib.set_search_start(old)
+    print(f"[pilot] seed {seed}: work {work[-1] / work[0]:.3f} of top-down", flush=True)
+    assert work[-1] <= 1.02 * work[0]
