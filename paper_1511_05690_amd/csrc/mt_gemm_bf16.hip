@@ -118,6 +118,8 @@ struct Cfg {
     static constexpr int SB = BN / 16 / NW;  // (Y hi / Y lo)
     static_assert(GA % 2 == 0 && GB % 2 == 0, "row groups per wave must be even");
     static_assert(SA >= 1 && SB >= 1, "split steps need 16 rows per wave");
+    // 256 x 256 tiles: the main loop scheduled by hand (wide_* below).
+    static constexpr bool WIDE = WAVES_M * WT_M_ == 8 && WAVES_N * WT_N_ == 8;
     static constexpr int LOADS = GA + GB;  // load instructions per wave and step, plain or split
     static_assert(2 * SA + 2 * SB == LOADS, "plain and split steps issue the same number of loads");
 };
@@ -676,6 +678,9 @@ struct AdjointEpi {
 };
 
 // ------------------------------------------------------------ the main loop
+#define MT_SCHED(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
+constexpr int kSchedMfma = 0x8, kSchedVmemRead = 0x20, kSchedDsRead = 0x100;
+
 template <class C, class Epi>
 __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kernel(GemmGeom g,
                                                                             FamilyPlan plan,
@@ -846,6 +851,15 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
     int buf = 0;
     int ahead = 0;  // steps issued and not yet run
     auto fill = [&]() {
+        if constexpr (C::WIDE) {
+            if (la_ < nact) {
+                issue(buf);
+                advance();
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < S - 1; ++i) {
             if (la_ < nact) {
@@ -886,6 +900,282 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
         --ahead;
         if (++buf == S) buf = 0;
     };
+    // The 256 x 256 loop.  What bounded its plain form (loads at the step's
+    // start, a wait for all of them and a barrier at its end) was the loads: 64
+    // KB a step through the L2.  128-byte lines with a step always in flight
+    // stream at 26 TB/s (0.33 ms for 8192^3's 8.6 GB), drained each step at 18
+    // TB/s, 64-byte pieces at 15 TB/s; the MFMAs take 0.45 ms at peak.  So a
+    // step has two barriers.  Behind the first (after sub-step 1) every wave
+    // holds the rest of the step's fragments in registers, and the buffer is
+    // refilled with the step after the next: half of its loads under sub-step
+    // 2, half under sub-step 3.  Behind the second (after sub-step 2) the next
+    // step's buffer has landed, with the half just issued still in flight,
+    // and its first fragments are read.  Reads and loads stand between the
+    // MFMAs one by one (a load every second MFMA: the address unit takes 16
+    // cycles for each and serves all waves).  One product at 8192^3 inside
+    // the K loop: 0.57 - 0.70 ms (1.57 - 1.93 PFLOP/s, by the data's power),
+    // before 0.72 - 0.78; the order of
+    // each entry's sum is the same.  An entry's last step refills nothing:
+    // the epilogue may stage through its buffer.
+    //
+    // Load instructions i0 .. i1 - 1 of the step at the cursor into buffer b.
+    // (The step's offset is added to the lane's 32-bit offset, below 256 rows
+    // x 2^24 bytes: a uniform base plus one VGPR per load also where the loop
+    // body is all the compiler sees.)
+    auto issue_plain = [&](int b, int i0, int i1) {
+        uint8_t* la = smem + b * C::BUF_BYTES;
+        uint8_t* lb = la + C::A_BYTES;
+#pragma unroll
+        for (int i = i0; i < i1; ++i) {
+            const int R0 = (wave * C::GA + i) * 8;
+            const uint32_t o = voff_p[i] + (uint32_t)lkt * 128u;
+            __builtin_amdgcn_global_load_lds((glb_cvoid*)((const char*)lxh + o), (lds_void*)(la + R0 * 128), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_cvoid*)((const char*)lyh + o), (lds_void*)(lb + R0 * 128), 16, 0, 0);
+        }
+    };
+    auto issue_split = [&](int b, int i0, int i1) {
+        uint8_t* la = smem + b * C::BUF_BYTES;
+#pragma unroll
+        for (int i = i0; i < i1; ++i) {
+            uint8_t* l0 = la + (wave * C::SA + i) * 16 * 64;
+            const uint32_t o = voff_s[i] + (uint32_t)lkt * 64u;
+            __builtin_amdgcn_global_load_lds((glb_cvoid*)((const char*)lxh + o), (lds_void*)l0, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_cvoid*)((const char*)lxl + o), (lds_void*)(l0 + C::BM * 64), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_cvoid*)((const char*)lyh + o), (lds_void*)(l0 + C::A_BYTES), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_cvoid*)((const char*)lyl + o),
+                                             (lds_void*)(l0 + C::A_BYTES + C::BN * 64), 16, 0, 0);
+        }
+    };
+    // every wave is here with its LDS reads done
+    auto wide_read = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // every load but each wave's newest `keep` (0, 4 or 8) has landed
+    auto wide_landed = [&](int keep) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (keep == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (keep == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        if (keep == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // an entry's second step, into the buffer the last entry's end left free
+    auto second_step = [&]() {
+        if (la_ < nact) {
+            issue(buf ^ 1);
+            advance();
+        }
+    };
+    // One plain p over its nkt64 steps (at least 1; the first is in buf).
+    auto wide_plain = [&](f32x16 (&acc)[WT_M][WT_N]) {
+        bf16x8 fa[4][WT_M], fb[4][WT_N];
+        auto read = [&](int b, int kk) {
+            const uint8_t* pa = smem + b * C::BUF_BYTES + t.wm * WT_M * 32 * 128 + (rd_base ^ (kk << 5));
+            const uint8_t* pb = smem + b * C::BUF_BYTES + C::A_BYTES + t.wn * WT_N * 32 * 128 + (rd_base ^ (kk << 5));
+#pragma unroll
+            for (int j = 0; j < WT_N; ++j) fb[kk][j] = *(const bf16x8*)(pb + j * 32 * 128);
+#pragma unroll
+            for (int i = 0; i < WT_M; ++i) fa[kk][i] = *(const bf16x8*)(pa + i * 32 * 128);
+        };
+        auto mfma = [&](int kk) {
+#pragma unroll
+            for (int i = 0; i < WT_M; ++i)
+#pragma unroll
+                for (int j = 0; j < WT_N; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i], fb[kk][j], acc[i][j], 0, 0, 0);
+        };
+        auto first_half = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            read(buf, 1);
+            read(buf, 2);
+            mfma(0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                MT_SCHED(kSchedMfma, 1);
+                MT_SCHED(kSchedDsRead, 2);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                MT_SCHED(kSchedMfma, 1);
+                MT_SCHED(kSchedDsRead, 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            read(buf, 3);
+            mfma(1);
+#pragma unroll
+            for (int r = 0; r < 6; ++r) {
+                MT_SCHED(kSchedMfma, 1);
+                MT_SCHED(kSchedDsRead, 1);
+            }
+            MT_SCHED(kSchedMfma, 2);
+            wide_read();
+        };
+        second_step();
+        read(buf, 0);
+        int st = 0;
+        // the step after the next belongs to this p
+        for (; st + 2 < nkt64; ++st) {
+            first_half();
+            issue_plain(buf, 0, C::GA / 2);
+            mfma(2);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                MT_SCHED(kSchedMfma, 2);
+                MT_SCHED(kSchedVmemRead, 1);
+            }
+            wide_landed(4);
+            read(buf ^ 1, 0);
+            issue_plain(buf, C::GA / 2, C::GA);
+            mfma(3);
+#pragma unroll
+            for (int r = 0; r < 6; ++r) {
+                MT_SCHED(kSchedMfma, 1);
+                MT_SCHED(kSchedDsRead, 1);
+                if (r >= 2) MT_SCHED(kSchedVmemRead, 1);
+            }
+            MT_SCHED(kSchedMfma, 2);
+            __builtin_amdgcn_sched_barrier(0);
+            ++lkt;
+            buf ^= 1;
+        }
+        if (lkt == lnk) {
+            lkt = 0;
+            ++la_;
+            set_cursor();
+        }
+        // the last two steps: the first of them loads the next p's first step
+#pragma unroll 1
+        for (; st < nkt64; ++st) {
+            first_half();
+            const bool more = st + 1 < nkt64 && la_ < nact;
+            if (more) {
+                issue(buf);
+                advance();
+            }
+            mfma(2);
+            if (more)
+                wide_landed(8);
+            else
+                wide_landed(0);
+            if (st + 1 < nkt64) read(buf ^ 1, 0);
+            mfma(3);
+            buf ^= 1;
+        }
+    };
+    // One split p over its nkt32 steps: per sub-step hi.hi and hi.lo entry by
+    // entry, then lo.hi.
+    auto wide_split = [&](f32x16 (&acc)[WT_M][WT_N]) {
+        bf16x8 ah[2][WT_M], al[2][WT_M], bh[2][WT_N], bl[2][WT_N];
+        auto read = [&](int b, int kk) {
+            const uint8_t* pa = smem + b * C::BUF_BYTES + t.wm * WT_M * 32 * 64 + (rd_split ^ (kk << 5));
+            const uint8_t* pb = smem + b * C::BUF_BYTES + C::A_BYTES + t.wn * WT_N * 32 * 64 + (rd_split ^ (kk << 5));
+#pragma unroll
+            for (int j = 0; j < WT_N; ++j) {
+                bh[kk][j] = *(const bf16x8*)(pb + j * 32 * 64);
+                bl[kk][j] = *(const bf16x8*)(pb + C::BN * 64 + j * 32 * 64);
+            }
+#pragma unroll
+            for (int i = 0; i < WT_M; ++i) ah[kk][i] = *(const bf16x8*)(pa + i * 32 * 64);
+#pragma unroll
+            for (int i = 0; i < WT_M; ++i) al[kk][i] = *(const bf16x8*)(pa + C::BM * 64 + i * 32 * 64);
+        };
+        auto mfma_h = [&](int kk, int i0, int i1) {
+#pragma unroll
+            for (int i = i0; i < i1; ++i)
+#pragma unroll
+                for (int j = 0; j < WT_N; ++j) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[kk][i], bh[kk][j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[kk][i], bl[kk][j], acc[i][j], 0, 0, 0);
+                }
+        };
+        auto mfma_l = [&](int kk) {
+#pragma unroll
+            for (int i = 0; i < WT_M; ++i)
+#pragma unroll
+                for (int j = 0; j < WT_N; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[kk][i], bh[kk][j], acc[i][j], 0, 0, 0);
+        };
+        auto first_half = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            read(buf, 1);
+            mfma_h(0, 0, WT_M);
+            mfma_l(0);
+            // (not from the start: the reads then reuse registers of fragments
+            // that are done with, and nothing is spilled)
+            MT_SCHED(kSchedMfma, 8);
+#pragma unroll
+            for (int r = 0; r < 12; ++r) {
+                MT_SCHED(kSchedMfma, 1);
+                MT_SCHED(kSchedDsRead, 1);
+            }
+            MT_SCHED(kSchedMfma, 4);
+            wide_read();
+        };
+        second_step();
+        read(buf, 0);
+        int st = 0;
+        for (; st + 2 < nkt32; ++st) {
+            first_half();
+            issue_split(buf, 0, C::SA / 2);
+            mfma_h(1, 0, WT_M / 2);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                MT_SCHED(kSchedMfma, 2);
+                MT_SCHED(kSchedVmemRead, 1);
+            }
+            wide_landed(4);
+            read(buf ^ 1, 0);
+            mfma_h(1, WT_M / 2, WT_M);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                MT_SCHED(kSchedMfma, 1);
+                MT_SCHED(kSchedDsRead, 2);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                MT_SCHED(kSchedMfma, 1);
+                MT_SCHED(kSchedDsRead, 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            issue_split(buf, C::SA / 2, C::SA);
+            mfma_l(1);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                MT_SCHED(kSchedMfma, 2);
+                MT_SCHED(kSchedVmemRead, 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            ++lkt;
+            buf ^= 1;
+        }
+        if (lkt == lnk) {
+            lkt = 0;
+            ++la_;
+            set_cursor();
+        }
+#pragma unroll 1
+        for (; st < nkt32; ++st) {
+            first_half();
+            const bool more = st + 1 < nkt32 && la_ < nact;
+            if (more) {
+                issue(buf);
+                advance();
+            }
+            mfma_h(1, 0, WT_M);
+            if (more)
+                wide_landed(8);
+            else
+                wide_landed(0);
+            if (st + 1 < nkt32) read(buf ^ 1, 0);
+            mfma_l(1);
+            buf ^= 1;
+        }
+    };
     set_cursor();
     if (nkt64 > 0 && nact > 0) fill();
     else __syncthreads();
@@ -903,7 +1193,15 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
 #pragma unroll
             for (int j = 0; j < WT_N; ++j) acc[i][j] = f32x16{};
 
-        if (plan.e[e].nseg == 3) {
+        if constexpr (C::WIDE) {
+            if (nkt64 > 0) {
+                if (plan.e[e].nseg == 3)
+                    wide_split(acc);
+                else
+                    wide_plain(acc);
+            }
+            kunits += (int64_t)nkt64 * (plan.e[e].nseg == 3 ? 192 : 64);
+        } else if (plan.e[e].nseg == 3) {
             // split p: hi.hi + hi.lo + lo.hi per K step of 32
             for (int st = 0; st < nkt32; ++st) {
                 step_begin();
@@ -1012,7 +1310,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
                 s_open[ai & 1][wave] = wopen;
             }
         }
-        if (S > 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (S > 2 || C::WIDE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (Epi::kCanStop) {
             int total = 0, open = 0, wave_pre = 0;
