@@ -371,11 +371,12 @@ mt_status apsp_affine_correct(void* D, mt_dtype dtype, int64_t n, const int32_t*
  * n + m - 1 <= 4096: one workgroup per pair transforms in LDS, largest p
  * first, and stops once every index of its pair is decided; no workspace
  * (workspace may be NULL).  4096 < n + m - 1 <= 16384: the pairs go through
- * global buffers in the workspace, one p at a time for the whole batch (no
- * early exit).  Larger lengths and b >= 2^31 return MT_ERR_UNSUPPORTED.
+ * a global buffer in the workspace, several p at a time, largest first; a
+ * pair whose indices are all decided is left out of the p after.  Larger lengths and b >= 2^31 return MT_ERR_UNSUPPORTED.
  * n = 0, m = 0 or b = 0: empty output, nothing written.  Asynchronous on the
- * stream.  Workspace from maxconv_workspace_size (0 bytes up to 4096; about
- * 32 N + 9 (n + m - 1) bytes per pair above, N the transform length).
+ * stream.  Workspace from maxconv_workspace_size (0 bytes up to 4096; above,
+ * about 16 s N + 9 (n + m - 1) bytes per pair, N the transform length, s >= 2
+ * the p at a time, at most |P| and as many as fit in 64 MiB).
  */
 mt_status maxconv_workspace_size(int64_t b, int64_t n, int64_t m, const mt_options* opt, size_t* bytes);
 mt_status maxconv_estimate(const void* x, const void* y, mt_dtype dtype, int64_t b, int64_t n, int64_t m,
@@ -422,7 +423,7 @@ mt_status maxconv_exact(const void* x, const void* y, mt_dtype dtype, int64_t b,
  * reach), their sigma columns in LDS when 40 K + 16 |P| K + 4 k bytes fit in
  * 160 KiB; for larger k one wave per run scans every diagonal.  Workspace
  * from xy_topk_workspace_size (16 (|P| + 1)(2n - 1) + 16 k bytes and
- * alignment, plus 64 |P| N + 2 N bytes for the global buffers when n > 2048,
+ * alignment, plus 32 |P| N + 2 N bytes for the global buffer when n > 2048,
  * N the transform length, plus (24 + 16 |P|) K bytes for the candidates when
  * k <= 4096).  With
  * k = 0 only the ring results are formed: the workspace then starts with

@@ -1192,9 +1192,12 @@ mt_status maxtimes_exact(const void* A, const void* B, mt_dtype dtype, int64_t b
 // Workspace of maxconv_estimate: empty up to n + m - 1 = kMaxConvN, the
 // long-vector buffers above.
 struct MaxconvLayout {
-    size_t tw, rxy, inv, s_sel, code, buf0, buf1, total;
+    size_t tw, rxy, inv, open_at, s_sel, code, buf, total;
+    int slots;
 };
-MaxconvLayout maxconv_layout(int64_t b, int64_t n, int64_t m) {
+// The buffer holds `slots` p of the whole batch: as many as fit in 64 MiB, at
+// least 2, the family cut into chunks of even size.
+MaxconvLayout maxconv_layout(int64_t b, int64_t n, int64_t m, int n_p) {
     MaxconvLayout L{};
     const int64_t len = n + m - 1;
     if (len <= kMaxConvN) return L;
@@ -1206,14 +1209,18 @@ MaxconvLayout maxconv_layout(int64_t b, int64_t n, int64_t m) {
     off += (size_t)round_up(b * 8, kAlign);
     L.inv = off;
     off += (size_t)round_up(2 * b * 8, kAlign);
+    L.open_at = off;
+    off += (size_t)round_up(b * 4, kAlign);
     L.s_sel = off;
     off += (size_t)round_up(b * len * 8, kAlign);
     L.code = off;
     off += (size_t)round_up(b * len, kAlign);
-    L.buf0 = off;
-    off += (size_t)round_up(b * N * 16, kAlign);
-    L.buf1 = off;
-    off += (size_t)round_up(b * N * 16, kAlign);
+    const int64_t fit = ((int64_t)64 << 20) / (b * N * 16);
+    const int64_t most = fit < 2 ? 2 : fit < n_p ? fit : n_p;
+    const int chunks = (int)((n_p + most - 1) / most);
+    L.slots = chunks < 2 ? (n_p < 2 ? 2 : n_p) : (n_p + chunks - 1) / chunks;
+    L.buf = off;
+    off += (size_t)round_up(L.slots * b * N * 16, kAlign);
     L.total = off;
     return L;
 }
@@ -1239,7 +1246,7 @@ mt_status maxconv_workspace_size(int64_t b, int64_t n, int64_t m, const mt_optio
     Family f;
     mt_status s = maxconv_check(b, n, m, opt, &f);
     if (s != MT_OK) return s;
-    *bytes = (b == 0 || n == 0 || m == 0) ? 0 : maxconv_layout(b, n, m).total;
+    *bytes = (b == 0 || n == 0 || m == 0) ? 0 : maxconv_layout(b, n, m, f.n).total;
     return MT_OK;
 }
 
@@ -1253,7 +1260,7 @@ mt_status maxconv_estimate(const void* x, const void* y, mt_dtype dtype, int64_t
     if (dtype != MT_F32 && dtype != MT_F64) return fail(MT_ERR_INVALID_ARG, "unknown dtype %d", (int)dtype);
     if (b == 0 || n == 0 || m == 0) return MT_OK;
     if (!x || !y || !z) return fail(MT_ERR_INVALID_ARG, "x, y or z is NULL");
-    const MaxconvLayout L = maxconv_layout(b, n, m);
+    const MaxconvLayout L = maxconv_layout(b, n, m, f.n);
     s = check_ws(workspace, ws_bytes, L.total);
     if (s != MT_OK) return s;
     MaxconvSpec spec{};
@@ -1264,8 +1271,8 @@ mt_status maxconv_estimate(const void* x, const void* y, mt_dtype dtype, int64_t
     MaxconvWorkspace w{};
     if (L.total) {
         w = MaxconvWorkspace{(double2*)(ws + L.tw), (double*)(ws + L.rxy), (double*)(ws + L.inv),
-                             (double*)(ws + L.s_sel), ws + L.code, (double2*)(ws + L.buf0),
-                             (double2*)(ws + L.buf1)};
+                             (int*)(ws + L.open_at), (double*)(ws + L.s_sel), ws + L.code,
+                             (double2*)(ws + L.buf), L.slots};
     }
     MT_TRY(launch_maxconv(x, y, dtype == MT_F64, b, n, m, spec, z, p_star, w, (hipStream_t)stream),
            "max-convolution");
@@ -1291,7 +1298,7 @@ mt_status maxconv_exact(const void* x, const void* y, mt_dtype dtype, int64_t b,
 // Workspace of xy_topk_estimate: the ring results of both runs, then the
 // second run's values and both runs' diagonals.
 struct XyLayout {
-    size_t sigma, psi, values1, diag0, diag1, tw, mxy, buf0, buf1, cand_m, cand_psi, cand_cols, total;
+    size_t sigma, psi, values1, diag0, diag1, tw, mxy, buf, cand_m, cand_psi, cand_cols, total;
 };
 XyLayout xy_layout(int64_t n, int32_t k, int n_p) {
     XyLayout L{};
@@ -1307,7 +1314,7 @@ XyLayout xy_layout(int64_t n, int32_t k, int n_p) {
     off += (size_t)round_up((int64_t)k * 4, kAlign);
     L.diag1 = off;
     off += (size_t)round_up((int64_t)k * 4, kAlign);
-    L.tw = L.mxy = L.buf0 = L.buf1 = 0;
+    L.tw = L.mxy = L.buf = 0;
     if (len > kMaxConvN) {
         const int logN = maxconv_log_size(n, n);
         const int64_t N = (int64_t)1 << logN;
@@ -1315,9 +1322,7 @@ XyLayout xy_layout(int64_t n, int32_t k, int n_p) {
         off += (size_t)round_up((N / 8 + 1) * 16, kAlign);
         L.mxy = off;
         off += kAlign;
-        L.buf0 = off;
-        off += (size_t)round_up(2 * (int64_t)n_p * N * 16, kAlign);
-        L.buf1 = off;
+        L.buf = off;
         off += (size_t)round_up(2 * (int64_t)n_p * N * 16, kAlign);
     }
     L.cand_m = L.cand_psi = L.cand_cols = 0;
@@ -1381,7 +1386,7 @@ mt_status xy_topk_estimate(const void* x, const void* y, mt_dtype dtype, int64_t
     XyWorkspace w{(double*)(ws + L.sigma), (double*)(ws + L.psi), (double*)(ws + L.values1),
                   (int32_t*)(ws + L.diag0), (int32_t*)(ws + L.diag1),
                   L.tw ? (double2*)(ws + L.tw) : nullptr, L.mxy ? (double*)(ws + L.mxy) : nullptr,
-                  L.buf0 ? (double2*)(ws + L.buf0) : nullptr, L.buf1 ? (double2*)(ws + L.buf1) : nullptr,
+                  L.buf ? (double2*)(ws + L.buf) : nullptr,
                   L.cand_m ? (int32_t*)(ws + L.cand_m) : nullptr, L.cand_psi ? (double*)(ws + L.cand_psi) : nullptr,
                   L.cand_cols ? (double*)(ws + L.cand_cols) : nullptr};
     MT_TRY(launch_xy_topk(x, y, dtype == MT_F64, n, k, spec, paired, values, diag, i_idx, j_idx, w,

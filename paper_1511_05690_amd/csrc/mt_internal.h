@@ -400,10 +400,11 @@ struct MaxconvWorkspace {
     double2* tw;     // twiddle octant, N / 8 + 1
     double* rxy;     // b: max x max y
     double* inv;     // 2b: 1 / max x, 1 / max y
+    int* open_at;    // b: the chunk that starts with open indices of the pair
     double* s_sel;   // b (n + m - 1): S at the selected p
     uint8_t* code;   // b (n + m - 1): its family index, MT_PSTAR_NONE, or open
-    double2* buf0;   // b N
-    double2* buf1;   // b N
+    double2* buf;    // slots x b N
+    int slots;       // p per chunk
 };
 hipError_t launch_maxconv(const void* x, const void* y, int f64, int64_t b, int64_t n, int64_t m,
                           const MaxconvSpec& spec, void* z, uint8_t* pstar, const MaxconvWorkspace& w,
@@ -418,11 +419,10 @@ struct XyWorkspace {
     double* values1;  // k
     int32_t* diag0;   // k
     int32_t* diag1;   // k
-    // only for N > kMaxConvN: twiddle octant, maxima of x and y, two buffers of 2 n_p N
+    // only for N > kMaxConvN: twiddle octant, maxima of x and y, a buffer of 2 n_p N
     double2* tw;
     double* mxy;
-    double2* buf0;
-    double2* buf1;
+    double2* buf;
     // k <= kPairedMaxK: K = min(k, 2n - 1) candidates per run
     int32_t* cand_m;    // 2 x K
     double* cand_psi;   // 2 x K

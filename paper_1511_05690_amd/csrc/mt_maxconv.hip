@@ -34,9 +34,9 @@
 // them by direct sums of x'^p y'^p for the remaining p instead of further
 // transforms.
 //
-// Global path (n + m - 1 <= 16384): the same passes through two buffers in
-// the workspace, one thread per butterfly, kernel boundaries between passes,
-// the whole batch one p at a time.
+// Global path (n + m - 1 <= 16384): a four-step transform through a buffer in
+// the workspace, three kernels per convolution, several p of the whole batch
+// at a time.
 //
 // Top k of x + y: the ring results of both runs (y and y reversed) for every
 // p by either path, the initial estimates, a one-wave NormQueue per run and
@@ -47,6 +47,7 @@
 
 #include <atomic>
 #include <climits>
+#include <type_traits>
 
 #include "mt_internal.h"
 
@@ -1248,9 +1249,28 @@ __global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict_
     }
 }
 
-// Long transforms (N = 8192 or 16384, up to kLongConvN): every transform of
-// the batch in a global buffer [slot][N], the four-step transform below
-// going through two such buffers.
+// Long transforms (N = 8192 or 16384, up to kLongConvN): the batch in one
+// global buffer [slot][N], each direction a four-step transform (N = 128 N2,
+// N2 = 64 or 128): with n = N2 n1 + n2 and k = k1 + 128 k2,
+//   X[k] = sum_n2 W_N2^(n2 k2) W_N^(n2 k1) sum_n1 x[N2 n1 + n2] W_128^(n1 k1),
+// the columns (length 128, stride N2), the twiddles W_N^(n2 k1), then the
+// rows (length N2).  A convolution is three kernels:
+//   columns  forms the operands, transforms them, stores Y[k1 N2 + n2];
+//   middle   the rows k1 of Y, the product, and the inverse's columns;
+//   rows     the inverse's rows, and what is done with the result.
+// The middle kernel can go on because the product at k needs Z[k] and Z[N - k]
+// only, and the inverse's column n2 is made of the elements k = n2 mod N2,
+// whole forward rows: a set of rows closed under k1 -> -k1 (and, for N2 = 64,
+// k1 -> k1 + 64) is a set of whole columns.  It reads and writes the same
+// 1024 elements, so the buffer is transformed in place (f4_place).
+// Bound by the buffer's traffic: 2 reads and 2 writes per element and
+// convolution.  As seven kernels per p (load, two passes, product, two
+// passes, select: 6 reads and 6 writes), one p at a time, 48 pairs at
+// N = 16384 over 7 p took 489 us in 53 launches, now 107 in 7: columns 38,
+// middle 43, rows 28 (4.9 TB/s each way through the buffer in the middle).
+constexpr int kF4Lines = 8;
+constexpr int kF4Threads = 128;
+constexpr int kF4Stride = 137;  // a line of 128 padded by padi, odd: no bank conflicts across lines
 
 // exp(-2 pi i mm / N), 0 <= mm < N, from the octant table (runtime N, N4 = N / 4).
 __device__ __forceinline__ double2 twiddle_rt(const double2* tw, int mm, int N4) {
@@ -1270,184 +1290,27 @@ __device__ __forceinline__ double2 twiddle_rt(const double2* tw, int mm, int N4)
     return make_double2(a, b);
 }
 
-// cos / sin (2 pi k / N), k = 0 .. N / 8; the maxima of x and y in mxy[0], mxy[1].
-template <typename T>
-__global__ __launch_bounds__(1024) void mt_xy_long_setup_kernel(const T* __restrict__ x, const T* __restrict__ y,
-                                                               int64_t n, int N, double2* __restrict__ tw,
-                                                               double* __restrict__ mxy) {
-    __shared__ double red[2][16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int k = tid; k <= N / 8; k += 1024) {
-        double sn, cs;
-        sincospi(2.0 * (double)k / (double)N, &sn, &cs);
-        tw[k] = make_double2(cs, sn);
-    }
-    double mx = -INFINITY, my = -INFINITY;
-    for (int64_t i = tid; i < n; i += 1024) {
-        mx = fmax(mx, (double)x[i]);
-        my = fmax(my, (double)y[i]);
-    }
-    for (int d = 32; d >= 1; d >>= 1) {
-        mx = fmax(mx, __shfl_xor(mx, d));
-        my = fmax(my, __shfl_xor(my, d));
-    }
-    if (lane == 0) {
-        red[0][wave] = mx;
-        red[1][wave] = my;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < 16; ++w) {
-            mx = fmax(mx, red[0][w]);
-            my = fmax(my, red[1][w]);
-        }
-        mxy[0] = mx;
-        mxy[1] = my;
-    }
+// cmul with its contraction written out: where the compiler knows the octant
+// of a twiddle it turns the sign into an addition and fuses the other product.
+__device__ __forceinline__ double2 cmul_fma(double2 a, double2 b) {
+    return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
 }
 
-// cos / sin (2 pi k / N), k = 0 .. N / 8.
-__global__ __launch_bounds__(256) void mt_twiddle_octant_kernel(double2* __restrict__ tw, int N) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+// Block `blk` of the octant table: cos / sin (2 pi k / N), k = 0 .. N / 8.
+__device__ __forceinline__ void twiddle_block(double2* tw, int N, int blk) {
+    const int k = blk * (int)blockDim.x + (int)threadIdx.x;
     if (k > N / 8) return;
     double sn, cs;
     sincospi(2.0 * (double)k / (double)N, &sn, &cs);
     tw[k] = make_double2(cs, sn);
 }
+constexpr int kLongSetupThreads = 1024;
+inline unsigned twiddle_blocks(int N) { return (unsigned)(N / 8 / kLongSetupThreads + 1); }
 
-// buf[slot][t] = (x'^p, y'^p) for slot = run |P| + q, zero for t >= n.
-template <typename T>
-__global__ __launch_bounds__(256) void mt_xy_long_load_kernel(const T* __restrict__ x, const T* __restrict__ y,
-                                                             int64_t n, int logN, MaxconvSpec spec,
-                                                             const double* __restrict__ mxy,
-                                                             double2* __restrict__ buf) {
-    const int N = 1 << logN;
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= (int64_t)2 * spec.n * N) return;
-    const int slot = (int)(g >> logN), t = (int)(g & (N - 1));
-    const int run = slot / spec.n, p = spec.p[slot % spec.n];
-    double a = 0.0, c = 0.0;
-    if (t < n) {
-        a = ipow_d(exp((double)x[t] - mxy[0]), p);
-        c = ipow_d(exp((double)y[run ? n - 1 - t : t] - mxy[1]), p);
-    }
-    buf[g] = make_double2(a, c);
-}
-
-// Four-step transform of the long lengths (N = N1 N2, N1 = 128, N2 = 64 or
-// 128): with n = N2 n1 + n2 and k = k1 + N1 k2,
-//   X[k] = sum_n2 W_N2^(n2 k2) W_N^(n2 k1) sum_n1 x[N2 n1 + n2] W_N1^(n1 k1),
-// so one kernel transforms the N2 columns (length N1, stride N2) and applies
-// W_N^(n2 k1), storing Y[k1 N2 + n2]; a second transforms the N1 rows of Y
-// (length N2, contiguous) and stores X[k1 + N1 k2].  Each workgroup holds
-// kF4Cols transforms of M points in LDS and runs Stockham stages there, so a
-// direction reads and writes the buffer twice instead of once per radix pass.
-constexpr int kF4Cols = 8;
-constexpr int kF4Threads = 128;
-
-template <int M, int R>
-__device__ __forceinline__ void f4_stage(double2* buf, int Ns, int N, const double2* tw) {
-    constexpr int MR = M / R;
-    const int t = threadIdx.x;
-    const bool act = t < kF4Cols * MR;
-    double2 v[16];
-    int c = 0, j = 0, k0 = 0;
-    if (act) {
-        c = t / MR;
-        j = t - c * MR;
-        k0 = j & (Ns - 1);
-#pragma unroll
-        for (int e = 0; e < R; ++e) v[e] = buf[c * (M + 1) + j + e * MR];
-        if (Ns > 1) {
-            const int step = k0 * (N / (Ns * R));
-#pragma unroll
-            for (int e = 1; e < R; ++e) v[e] = cmul(v[e], twiddle_rt(tw, step * e, N / 4));
-        }
-        dft<R>(v, 0, 1);
-    }
-    __syncthreads();
-    if (act) {
-        const int base = (j - k0) * R + k0;
-#pragma unroll
-        for (int e = 0; e < R; ++e) buf[c * (M + 1) + base + e * Ns] = v[oreg<R>(e)];
-    }
-    __syncthreads();
-}
-
-// One step of the four-step transform for every transform of the batch:
-// workgroup g takes transform g / groups_per_tr and its kF4Cols consecutive
-// columns (or rows) from (g % groups_per_tr) kF4Cols.  Element i of line c
-// is in[i s_in + c c_in]; result k of line c goes to out[k s_out + c]
-// (multiplied by W_N^(c k) when twiddle).  Lines are contiguous in memory
-// when c_in = 1 (columns) and elements are when s_in = 1 (rows).
-template <int M>
-__global__ __launch_bounds__(kF4Threads) void mt_fft4_kernel(const double2* __restrict__ in, double2* __restrict__ out,
-                                                    int logN, int groups_per_tr, int s_in, int c_in, int s_out,
-                                                    int twiddle, const double2* __restrict__ tw) {
-    __shared__ double2 buf[kF4Cols * (M + 1)];
-    const int t = threadIdx.x;
-    const int N = 1 << logN;
-    const int64_t tr = blockIdx.x / groups_per_tr;
-    const int c0 = (int)(blockIdx.x - tr * groups_per_tr) * kF4Cols;
-    const double2* src = in + tr * N;
-    double2* dst = out + tr * N;
-    for (int idx = t; idx < kF4Cols * M; idx += kF4Threads) {
-        const int i = c_in == 1 ? idx / kF4Cols : idx % M;
-        const int c = c_in == 1 ? idx % kF4Cols : idx / M;
-        buf[c * (M + 1) + i] = src[i * s_in + (c0 + c) * c_in];
-    }
-    __syncthreads();
-    f4_stage<M, 16>(buf, 1, N, tw);
-    f4_stage<M, M / 16>(buf, 16, N, tw);
-    for (int idx = t; idx < kF4Cols * M; idx += kF4Threads) {
-        const int k = idx / kF4Cols, c = idx % kF4Cols;
-        double2 v = buf[c * (M + 1) + k];
-        if (twiddle) v = cmul(v, twiddle_rt(tw, ((c0 + c) * k) & (N - 1), N / 4));
-        dst[k * s_out + c0 + c] = v;
-    }
-}
-
-// conj(4 W_t) of every transform from Z_t and Z_(N-t) (see convolve_pair).
-__global__ __launch_bounds__(256) void mt_fft_product_kernel(const double2* __restrict__ Z, double2* __restrict__ out,
-                                                            int logN, int64_t total) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= total) return;
-    const int N = 1 << logN;
-    const int64_t base = g & ~(int64_t)(N - 1);
-    const int t = (int)(g & (N - 1));
-    const double2 zk = Z[g], zn = Z[base + ((N - t) & (N - 1))];
-    const double2 a = make_double2(zk.x + zn.x, zk.y - zn.y);
-    const double2 c = make_double2(zk.y + zn.y, zn.x - zk.x);
-    const double2 w = cmul(a, c);
-    out[g] = make_double2(w.x, -w.y);
-}
-
-// sigma[slot][t] = Re(result)[t] * 0.25 / N for t < L.
-__global__ __launch_bounds__(256) void mt_xy_long_store_kernel(const double2* __restrict__ res, int logN, int64_t L,
-                                                              int64_t slots, double* __restrict__ sigma) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= slots * L) return;
-    const int64_t slot = g / L, t = g - slot * L;
-    sigma[g] = res[(slot << logN) + t].x * (0.25 / (double)(1 << logN));
-}
-
-// Max-convolution of long vectors (kMaxConvN < N <= kLongConvN): the batch of
-// pairs through the four-step transforms in global buffers, one p at a time
-// (largest first); every index keeps the S of its first stable p (code = its
-// family index) and the roots are taken at the end.  No early exit.
-constexpr uint8_t kCodeOpen = 254;
-
-// Per pair: rxy[pair] = max x max y, inv[2 pair] = 1 / max x, inv[2 pair + 1] = 1 / max y.
-template <typename T>
-__global__ __launch_bounds__(256) void mt_maxconv_long_scale_kernel(const T* __restrict__ x, const T* __restrict__ y,
-                                                                   int64_t n, int64_t m, double* __restrict__ rxy,
-                                                                   double* __restrict__ inv) {
-    __shared__ double red[2][4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t pair = blockIdx.x;
-    double mx = 0.0, my = 0.0;
-    for (int64_t i = tid; i < n; i += 256) mx = fmax(mx, (double)x[pair * n + i]);
-    for (int64_t i = tid; i < m; i += 256) my = fmax(my, (double)y[pair * m + i]);
+// Maxima of mx and my over the block, in every lane of the first wave.
+__device__ __forceinline__ void block_max2(double& mx, double& my) {
+    __shared__ double red[2][kLongSetupThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int d = 32; d >= 1; d >>= 1) {
         mx = fmax(mx, __shfl_xor(mx, d));
         my = fmax(my, __shfl_xor(my, d));
@@ -1457,67 +1320,296 @@ __global__ __launch_bounds__(256) void mt_maxconv_long_scale_kernel(const T* __r
         red[1][wave] = my;
     }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < 4; ++w) {
-            mx = fmax(mx, red[0][w]);
-            my = fmax(my, red[1][w]);
-        }
+    for (int w = 0; w < kLongSetupThreads / 64; ++w) {
+        mx = fmax(mx, red[0][w]);
+        my = fmax(my, red[1][w]);
+    }
+}
+
+// Block 0: the maxima of x and y in mxy[0], mxy[1]; the others: the twiddles.
+template <typename T>
+__global__ __launch_bounds__(kLongSetupThreads) void mt_xy_long_setup_kernel(const T* __restrict__ x,
+                                                                            const T* __restrict__ y, int64_t n, int N,
+                                                                            double2* __restrict__ tw,
+                                                                            double* __restrict__ mxy) {
+    if (blockIdx.x > 0) {
+        twiddle_block(tw, N, (int)blockIdx.x - 1);
+        return;
+    }
+    double mx = -INFINITY, my = -INFINITY;
+    for (int64_t i = threadIdx.x; i < n; i += kLongSetupThreads) {
+        mx = fmax(mx, (double)x[i]);
+        my = fmax(my, (double)y[i]);
+    }
+    block_max2(mx, my);
+    if (threadIdx.x == 0) {
+        mxy[0] = mx;
+        mxy[1] = my;
+    }
+}
+
+// Block pair < b: rxy[pair] = max x max y, inv[2 pair] = 1 / max x,
+// inv[2 pair + 1] = 1 / max y, open_at[pair] = 0; the others: the twiddles.
+template <typename T>
+__global__ __launch_bounds__(kLongSetupThreads) void mt_maxconv_long_setup_kernel(
+    const T* __restrict__ x, const T* __restrict__ y, int64_t b, int64_t n, int64_t m, int N,
+    double2* __restrict__ tw, double* __restrict__ rxy, double* __restrict__ inv, int* __restrict__ open_at) {
+    const int64_t pair = blockIdx.x;
+    if (pair >= b) {
+        twiddle_block(tw, N, (int)(pair - b));
+        return;
+    }
+    double mx = 0.0, my = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += kLongSetupThreads) mx = fmax(mx, (double)x[pair * n + i]);
+    for (int64_t i = threadIdx.x; i < m; i += kLongSetupThreads) my = fmax(my, (double)y[pair * m + i]);
+    block_max2(mx, my);
+    if (threadIdx.x == 0) {
         rxy[pair] = mx * my;
         inv[2 * pair] = mx > 0.0 ? 1.0 / mx : 0.0;
         inv[2 * pair + 1] = my > 0.0 ? 1.0 / my : 0.0;
+        open_at[pair] = 0;
     }
 }
 
-// buf[pair][t] = (x'^p, y'^p), zero beyond the vectors.
+// The operands of the max-convolution: slot s of a chunk holds family index
+// q_top - s / b of pair s % b, (x'^p, y'^p), zero beyond the vectors.  A pair
+// without an open index after the chunk before (open_at[pair] != chunk) is
+// not transformed.
 template <typename T>
-__global__ __launch_bounds__(256) void mt_maxconv_long_load_kernel(const T* __restrict__ x, const T* __restrict__ y,
-                                                                  int64_t b, int64_t n, int64_t m, int logN, int p,
-                                                                  const double* __restrict__ inv,
-                                                                  double2* __restrict__ buf) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= (b << logN)) return;
-    const int64_t pair = g >> logN;
-    const int64_t t = g & ((1 << logN) - 1);
-    const double a = t < n ? ipow_d((double)x[pair * n + t] * inv[2 * pair], p) : 0.0;
-    const double c = t < m ? ipow_d((double)y[pair * m + t] * inv[2 * pair + 1], p) : 0.0;
-    buf[g] = make_double2(a, c);
+struct MaxconvLoad {
+    const T* x;
+    const T* y;
+    int64_t b, n, m;
+    const double* inv;
+    const int* open_at;
+    int chunk, q_top;
+    MaxconvSpec spec;
+    __device__ __forceinline__ bool live(int64_t s) const { return open_at[s % b] == chunk; }
+    __device__ __forceinline__ double2 at(int64_t s, int t) const {
+        const int64_t pair = s % b;
+        const int p = spec.p[q_top - (int)(s / b)];
+        const double a = t < n ? ipow_d((double)x[pair * n + t] * inv[2 * pair], p) : 0.0;
+        const double c = t < m ? ipow_d((double)y[pair * m + t] * inv[2 * pair + 1], p) : 0.0;
+        return make_double2(a, c);
+    }
+};
+
+// The operands of x + y: slot = run |P| + q holds (x'^p, y'^p), y reversed in
+// run 1, zero for t >= n.
+template <typename T>
+struct XyLoad {
+    const T* x;
+    const T* y;
+    int64_t n;
+    const double* mxy;
+    MaxconvSpec spec;
+    __device__ __forceinline__ bool live(int64_t) const { return true; }
+    __device__ __forceinline__ double2 at(int64_t s, int t) const {
+        const int run = (int)s / spec.n, p = spec.p[(int)s % spec.n];
+        double a = 0.0, c = 0.0;
+        if (t < n) {
+            a = ipow_d(exp((double)x[t] - mxy[0]), p);
+            c = ipow_d(exp((double)y[run ? n - 1 - t : t] - mxy[1]), p);
+        }
+        return make_double2(a, c);
+    }
+};
+
+// The two Stockham stages of a line of M = 64 or 128 points (radix 16, then
+// M / 16).  First: v[e] is element j + e M / 16, j < M / 16; the result goes
+// to the line in LDS.  Second: lane j < 16 of the line; result k = j + 16 e is
+// left in v[oreg<M / 16>(e)].
+__device__ __forceinline__ void f4_first(double2 (&v)[16], double2* line, int j) {
+    dft<16>(v, 0, 1);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) line[padi(16 * j + e)] = v[oreg<16>(e)];
 }
 
-// The p* test of family index q for every index still open.
-__global__ __launch_bounds__(256) void mt_maxconv_long_select_kernel(const double2* __restrict__ res, int logN,
-                                                                    int64_t b, int64_t L, int q, double tau,
-                                                                    double* __restrict__ s_sel,
-                                                                    uint8_t* __restrict__ code) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= b * L) return;
-    if (code[g] != kCodeOpen) return;
-    const int64_t pair = g / L, t = g - pair * L;
-    const double S = res[(pair << logN) + t].x * (0.25 / (double)(1 << logN));
-    const bool stable = S >= tau;
-    if (stable || q == 0) {
-        s_sel[g] = S;
-        code[g] = stable ? (uint8_t)q : (uint8_t)MT_PSTAR_NONE;
+template <int M>
+__device__ __forceinline__ void f4_second(double2 (&v)[16], const double2* line, int j, int N, const double2* tw) {
+    constexpr int R = M / 16;
+#pragma unroll
+    for (int e = 0; e < R; ++e) v[e] = line[padi(j + 16 * e)];
+    const int step = j * (N / M);
+#pragma unroll
+    for (int e = 1; e < R; ++e) v[e] = cmul_fma(v[e], twiddle_rt(tw, step * e, N / 4));
+    dft<R>(v, 0, 1);
+}
+
+// Where the middle kernel leaves element k1 of the inverse's column n2: in
+// the forward rows n2 (and n2 + 64 for N2 = 64) that it read.
+template <int N2>
+__device__ __forceinline__ int f4_place(int n2, int k1) {
+    return (n2 + N2 * (k1 / N2)) * N2 + (k1 & (N2 - 1));
+}
+
+// Workgroup g: transform g / (N2 / 8), columns 8 (g % (N2 / 8)) ...  Lanes run
+// over the 8 columns first: 8 consecutive elements per access.
+template <int N2, typename Load>
+__global__ __launch_bounds__(kF4Threads) void mt_long_columns_kernel(Load ld, double2* __restrict__ buf,
+                                                                    const double2* __restrict__ tw) {
+    __shared__ double2 lds[kF4Lines * kF4Stride];
+    constexpr int N = 128 * N2, kGroups = N2 / kF4Lines;
+    const int64_t slot = blockIdx.x / kGroups;
+    if (!ld.live(slot)) return;
+    const int t = threadIdx.x, c = t & (kF4Lines - 1), j = t / kF4Lines;
+    const int n2 = (int)(blockIdx.x & (kGroups - 1)) * kF4Lines + c;
+    double2 v[16];
+    if (j < 8) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            v[e] = ld.at(slot, (j + 8 * e) * N2 + n2);
+            opaque(v[e]);
+        }
+        f4_first(v, lds + c * kF4Stride, j);
+    }
+    __syncthreads();
+    f4_second<128>(v, lds + c * kF4Stride, j, N, tw);
+    double2* dst = buf + slot * N + n2;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int k1 = j + 16 * e;
+        dst[k1 * N2] = cmul_fma(v[oreg<8>(e)], twiddle_rt(tw, n2 * k1, N / 4));
     }
 }
 
-__global__ __launch_bounds__(256) void mt_fill_u8_kernel(uint8_t* __restrict__ p, int64_t count, uint8_t v) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g < count) p[g] = v;
+// Forward row of line l of group g (see above), the line of the row -k1 and
+// whether that is the line itself.
+template <int N2>
+__device__ __forceinline__ int f4_row(int g, int l) {
+    if constexpr (N2 == 128) {
+        const int j = 4 * g + (l & 3);
+        return l < 4 ? j : (j ? 128 - j : 64);
+    } else {
+        const int j = 2 * g + (l >> 2), r = l & 3;
+        return ((r & 1) ? (j ? 64 - j : 32) : j) + 32 * (r & 2);
+    }
+}
+template <int N2>
+__device__ __forceinline__ int f4_partner(int l, int k1) {
+    if ((k1 & 63) == 0) return l;
+    if constexpr (N2 == 128) return l ^ 4;
+    return k1 == 32 || k1 == 96 ? l ^ 2 : l ^ 3;
 }
 
-// z = max x max y S^(1/p) at the selected p (the smallest p with S clamped
-// at 0 where none was stable), p* = its code.
-template <typename T>
-__global__ __launch_bounds__(256) void mt_maxconv_long_root_kernel(const double* __restrict__ s_sel,
-                                                                  const uint8_t* __restrict__ code,
-                                                                  const double* __restrict__ rxy, int64_t b,
-                                                                  int64_t L, MaxconvSpec spec, T* __restrict__ z,
-                                                                  uint8_t* __restrict__ pstar) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= b * L) return;
-    const uint8_t c = code[g];
-    const int p = spec.p[c == MT_PSTAR_NONE ? 0 : c];
-    const double S = s_sel[g];
+// conj(4 W) at element k2 of row k1 (line l) from Z_k and Z_(N-k) (see
+// convolve_pair).
+template <int N2>
+__device__ __forceinline__ double2 f4_product(const double2* lds, int l, int k1, int k2) {
+    const int kn = k1 ? N2 - 1 - k2 : (N2 - k2) & (N2 - 1);
+    const double2 zk = lds[l * kF4Stride + padi(k2)], zn = lds[f4_partner<N2>(l, k1) * kF4Stride + padi(kn)];
+    const double2 a = make_double2(zk.x + zn.x, zk.y - zn.y);
+    const double2 c = make_double2(zk.y + zn.y, zn.x - zk.x);
+    const double2 w = cmul_fma(a, c);
+    return make_double2(w.x, -w.y);
+}
+
+// Workgroup g: transform g / 16 and its g % 16-th set of 8 forward rows, which
+// are 8 (N2 = 128) or 4 (N2 = 64, every second element from the row + 64)
+// columns of the inverse.  Slots of pairs that are not live are left alone.
+template <int N2>
+__global__ __launch_bounds__(kF4Threads) void mt_long_middle_kernel(double2* __restrict__ buf,
+                                                                   const double2* __restrict__ tw,
+                                                                   const int* __restrict__ open_at, int64_t b,
+                                                                   int chunk) {
+    __shared__ double2 lds[kF4Lines * kF4Stride];
+    constexpr int N = 128 * N2, R = N2 / 16;
+    const int64_t slot = blockIdx.x / 16;
+    if (open_at && open_at[slot % b] != chunk) return;
+    const int g = (int)(blockIdx.x & 15), t = threadIdx.x;
+    double2* z = buf + slot * N;
+    double2 v[16];
+    // forward rows
+    if (t < kF4Lines * R) {
+        const int l = t / R, j = t & (R - 1);
+        const double2* src = z + f4_row<N2>(g, l) * N2 + j;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = src[R * e];
+        f4_first(v, lds + l * kF4Stride, j);
+    }
+    __syncthreads();
+    {
+        const int l = t / 16, j = t & 15;
+        f4_second<N2>(v, lds + l * kF4Stride, j, N, tw);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < R; ++e) lds[l * kF4Stride + padi(j + 16 * e)] = v[oreg<R>(e)];
+    }
+    __syncthreads();
+    // the product, and the inverse's columns
+    constexpr int kCols = N2 / 16;
+    const int cf = t / 8, jf = t & 7;
+    if (cf < kCols) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int n1 = jf + 8 * e;
+            int l = cf, k2 = n1;
+            if constexpr (N2 == 64) {
+                l = 4 * (cf >> 1) + (cf & 1) + 2 * (n1 & 1);
+                k2 = n1 >> 1;
+            }
+            v[e] = f4_product<N2>(lds, l, f4_row<N2>(g, l), k2);
+            opaque(v[e]);
+        }
+    }
+    __syncthreads();
+    if (cf < kCols) f4_first(v, lds + cf * kF4Stride, jf);
+    __syncthreads();
+    const int c = t / 16, j = t & 15;
+    if (c < kCols) {
+        f4_second<128>(v, lds + c * kF4Stride, j, N, tw);
+        const int n2 = f4_row<N2>(g, N2 == 64 ? 4 * (c >> 1) + (c & 1) : c);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int k1 = j + 16 * e;
+            z[f4_place<N2>(n2, k1)] = cmul_fma(v[oreg<8>(e)], twiddle_rt(tw, n2 * k1, N / 4));
+        }
+    }
+}
+
+// The inverse's rows 8 g ... 8 g + 7 of one transform: lane j of line c ends
+// with result t = 8 g + c + 128 (j + 16 e) in v[oreg<N2 / 16>(e)].  Lanes run
+// over the 8 rows first.  lds may be in use by the caller's last call.
+template <int N2>
+__device__ __forceinline__ void f4_inverse_rows(double2 (&v)[16], double2* lds, const double2* z, int g,
+                                                const double2* tw) {
+    constexpr int R = N2 / 16;
+    const int t = threadIdx.x, c = t & (kF4Lines - 1), j = t / kF4Lines;
+    const int k1 = g * kF4Lines + c;
+    if (j < R) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = z[f4_place<N2>(j + R * e, k1)];
+    }
+    __syncthreads();
+    if (j < R) f4_first(v, lds + c * kF4Stride, j);
+    __syncthreads();
+    f4_second<N2>(v, lds + c * kF4Stride, j, 128 * N2, tw);
+    // the imaginary parts stay: without them the last sums contract otherwise
+#pragma unroll
+    for (int e = 0; e < R; ++e) opaque(v[e]);
+}
+
+// sigma[slot][t] = Re(result)[t] * 0.25 / N for t < L.
+template <int N2>
+__global__ __launch_bounds__(kF4Threads) void mt_xy_long_rows_kernel(const double2* __restrict__ buf,
+                                                                    const double2* __restrict__ tw, int64_t L,
+                                                                    double* __restrict__ sigma) {
+    __shared__ double2 lds[kF4Lines * kF4Stride];
+    constexpr int N = 128 * N2, R = N2 / 16;
+    const int64_t slot = blockIdx.x / 16;
+    const int g = (int)(blockIdx.x & 15);
+    double2 v[16];
+    f4_inverse_rows<N2>(v, lds, buf + slot * N, g, tw);
+    const int t0 = g * kF4Lines + (int)(threadIdx.x & (kF4Lines - 1)) + 128 * (int)(threadIdx.x / kF4Lines);
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+        const int t = t0 + 2048 * e;
+        if (t < L) sigma[slot * L + t] = v[oreg<R>(e)].x * (0.25 / (double)N);
+    }
+}
+
+// z = max x max y S^(1/p), S clamped at 0.
+__device__ __forceinline__ double maxconv_root(double S, int p) {
     double root = 0.0;
     if (S > 0.0) {
         if ((p & (p - 1)) == 0) {
@@ -1527,8 +1619,78 @@ __global__ __launch_bounds__(256) void mt_maxconv_long_root_kernel(const double*
             root = exp(log(S) / (double)p);
         }
     }
-    z[g] = (T)(rxy[g / L] * root);
-    if (pstar) pstar[g] = c;
+    return root;
+}
+
+// Max-convolution of long vectors (kMaxConvN < N <= kLongConvN): the p family
+// in chunks of `slots` p, largest first.  Every index keeps the S of its first
+// stable p (code = its family index); a workgroup leaves a chunk once its
+// indices are decided, a pair without open indices is skipped by the chunks
+// after, and the last chunk takes the roots: at the selected p, the smallest
+// p where none was stable.
+constexpr uint8_t kCodeOpen = 254;
+
+template <typename T, int N2>
+__global__ __launch_bounds__(kF4Threads) void mt_maxconv_long_rows_kernel(
+    const double2* __restrict__ buf, const double2* __restrict__ tw, int64_t b, int64_t L, MaxconvSpec spec, int chunk,
+    int q_top, int q_end, double* __restrict__ s_sel, uint8_t* __restrict__ code, int* __restrict__ open_at,
+    const double* __restrict__ rxy, T* __restrict__ z, uint8_t* __restrict__ pstar) {
+    __shared__ double2 lds[kF4Lines * kF4Stride];
+    constexpr int N = 128 * N2, R = N2 / 16;
+    const int64_t pair = blockIdx.x / 16;
+    const int g = (int)(blockIdx.x & 15);
+    const int t0 = g * kF4Lines + (int)(threadIdx.x & (kF4Lines - 1)) + 128 * (int)(threadIdx.x / kF4Lines);
+    double S[R];
+    int cd[R];
+    bool open = false;
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+        const int t = t0 + 2048 * e;
+        S[e] = 0.0;
+        cd[e] = MT_PSTAR_NONE;
+        if (t < L) {
+            cd[e] = kCodeOpen;
+            if (chunk > 0) {
+                cd[e] = code[pair * L + t];
+                S[e] = s_sel[pair * L + t];
+            }
+            open |= cd[e] == kCodeOpen;
+        }
+    }
+    int q = q_top;
+    // a workgroup with an open index belongs to a pair that is live
+    for (; q >= q_end && __syncthreads_or(open); --q) {
+        double2 v[16];
+        f4_inverse_rows<N2>(v, lds, buf + ((int64_t)(q_top - q) * b + pair) * N, g, tw);
+        open = false;
+#pragma unroll
+        for (int e = 0; e < R; ++e) {
+            if (cd[e] != kCodeOpen) continue;
+            const double s = v[oreg<R>(e)].x * (0.25 / (double)N);
+            const bool stable = s >= spec.tau;
+            if (stable || q == 0) {
+                S[e] = s;
+                cd[e] = stable ? q : MT_PSTAR_NONE;
+            } else {
+                open = true;
+            }
+        }
+    }
+    const bool last = q_end == 0;
+    if (!last && open) open_at[pair] = chunk + 1;
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+        const int t = t0 + 2048 * e;
+        if (t >= L) continue;
+        const int64_t at = pair * L + t;
+        if (last) {
+            z[at] = (T)(rxy[pair] * maxconv_root(S[e], spec.p[cd[e] == MT_PSTAR_NONE ? 0 : cd[e]]));
+            if (pstar) pstar[at] = (uint8_t)cd[e];
+        } else {
+            s_sel[at] = S[e];
+            code[at] = (uint8_t)cd[e];
+        }
+    }
 }
 
 template <typename T>
@@ -1632,117 +1794,61 @@ hipError_t launch_xy_sigma_n(const T* x, const T* y, int64_t n, const MaxconvSpe
     return hipGetLastError();
 }
 
-// The convolution step of every transform of a batch held in cur (count
-// transforms of N = 2^logN points, (a, b) packed as a + i b): the forward
-// passes, the product conj(4 X Y) and the inverse passes.  On return cur holds
-// the result (real part 4 N (a * b)); nxt is scratch.
-hipError_t long_convolve(double2*& cur, double2*& nxt, int logN, int64_t count, const double2* tw,
-                         const char* pass_name, const char* product_name, hipStream_t st) {
-    const int64_t total = count << logN;
-    auto blocks = [](int64_t c) { return dim3((unsigned)((c + 255) / 256)); };
-    auto swap = [&]() {
-        double2* t = cur;
-        cur = nxt;
-        nxt = t;
-    };
-    // N = 8192 or 16384: the four-step transform (columns of 128, rows of N2)
-    auto transform4 = [&]() -> hipError_t {
-        const int N2 = 1 << (logN - 7);
-        timing_before(pass_name, st);
-        hipLaunchKernelGGL(mt_fft4_kernel<128>, dim3((unsigned)(count * (N2 / kF4Cols))), dim3(kF4Threads), 0, st, cur,
-                           nxt, logN, N2 / kF4Cols, N2, 1, N2, 1, tw);
-        timing_after(st);
-        hipError_t pe = hipGetLastError();
-        if (pe != hipSuccess) return pe;
-        swap();
-        timing_before(pass_name, st);
-        if (N2 == 128)
-            hipLaunchKernelGGL(mt_fft4_kernel<128>, dim3((unsigned)(count * (128 / kF4Cols))), dim3(kF4Threads), 0, st,
-                               cur, nxt, logN, 128 / kF4Cols, 1, N2, 128, 0, tw);
-        else
-            hipLaunchKernelGGL(mt_fft4_kernel<64>, dim3((unsigned)(count * (128 / kF4Cols))), dim3(kF4Threads), 0, st, cur,
-                               nxt, logN, 128 / kF4Cols, 1, N2, 128, 0, tw);
-        timing_after(st);
-        pe = hipGetLastError();
-        if (pe != hipSuccess) return pe;
-        swap();
-        return hipSuccess;
-    };
-    if (logN != 13 && logN != 14) return hipErrorInvalidValue;
-    hipError_t e = transform4();
-    if (e != hipSuccess) return e;
-    timing_before(product_name, st);
-    hipLaunchKernelGGL(mt_fft_product_kernel, blocks(total), dim3(256), 0, st, cur, nxt, logN, total);
-    timing_after(st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    swap();
-    return transform4();
-}
-
-// Max-convolution of long vectors through the global buffers of ws.
-template <typename T>
+// Max-convolution of long vectors through the buffer of ws: `slots` p of the
+// whole batch per chunk.
+template <typename T, int N2>
 hipError_t launch_maxconv_long(const T* x, const T* y, int64_t b, int64_t n, int64_t m, const MaxconvSpec& spec,
                                T* z, uint8_t* pstar, const MaxconvWorkspace& w, hipStream_t st) {
-    const int logN = maxconv_log_size(n, m);
-    const int N = 1 << logN;
+    constexpr int N = 128 * N2;
     const int64_t L = n + m - 1;
-    auto blocks = [](int64_t c) { return dim3((unsigned)((c + 255) / 256)); };
     timing_before("mt_maxconv_long_setup", st);
-    hipLaunchKernelGGL(mt_twiddle_octant_kernel, blocks(N / 8 + 1), dim3(256), 0, st, w.tw, N);
-    hipLaunchKernelGGL(mt_maxconv_long_scale_kernel<T>, dim3((unsigned)b), dim3(256), 0, st, x, y, n, m, w.rxy,
-                       w.inv);
-    hipLaunchKernelGGL(mt_fill_u8_kernel, blocks(b * L), dim3(256), 0, st, w.code, b * L, kCodeOpen);
+    hipLaunchKernelGGL(mt_maxconv_long_setup_kernel<T>, dim3((unsigned)b + twiddle_blocks(N)),
+                       dim3(kLongSetupThreads), 0, st, x, y, b, n, m, N, w.tw, w.rxy, w.inv, w.open_at);
     timing_after(st);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    for (int q = spec.n - 1; q >= 0; --q) {
-        double2* cur = w.buf0;
-        double2* nxt = w.buf1;
-        timing_before("mt_maxconv_long_load", st);
-        hipLaunchKernelGGL(mt_maxconv_long_load_kernel<T>, blocks(b << logN), dim3(256), 0, st, x, y, b, n, m, logN,
-                           spec.p[q], w.inv, cur);
+    for (int chunk = 0, q_top = spec.n - 1; q_top >= 0 && e == hipSuccess; ++chunk, q_top -= w.slots) {
+        const int q_end = q_top - w.slots + 1 > 0 ? q_top - w.slots + 1 : 0;
+        const int64_t count = (int64_t)(q_top - q_end + 1) * b;
+        const MaxconvLoad<T> ld{x, y, b, n, m, w.inv, w.open_at, chunk, q_top, spec};
+        timing_before("mt_maxconv_long_columns", st);
+        hipLaunchKernelGGL((mt_long_columns_kernel<N2, MaxconvLoad<T>>), dim3((unsigned)(count * (N2 / kF4Lines))),
+                           dim3(kF4Threads), 0, st, ld, w.buf, w.tw);
         timing_after(st);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = long_convolve(cur, nxt, logN, b, w.tw, "mt_maxconv_long_pass", "mt_maxconv_long_product", st)) !=
-            hipSuccess)
-            return e;
-        timing_before("mt_maxconv_long_select", st);
-        hipLaunchKernelGGL(mt_maxconv_long_select_kernel, blocks(b * L), dim3(256), 0, st, cur, logN, b, L, q,
-                           spec.tau, w.s_sel, w.code);
+        timing_before("mt_maxconv_long_middle", st);
+        hipLaunchKernelGGL(mt_long_middle_kernel<N2>, dim3((unsigned)(count * 16)), dim3(kF4Threads), 0, st, w.buf,
+                           w.tw, w.open_at, b, chunk);
         timing_after(st);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        timing_before("mt_maxconv_long_rows", st);
+        hipLaunchKernelGGL((mt_maxconv_long_rows_kernel<T, N2>), dim3((unsigned)(b * 16)), dim3(kF4Threads), 0, st,
+                           w.buf, w.tw, b, L, spec, chunk, q_top, q_end, w.s_sel, w.code, w.open_at, w.rxy, z, pstar);
+        timing_after(st);
+        e = hipGetLastError();
     }
-    timing_before("mt_maxconv_long_root", st);
-    hipLaunchKernelGGL(mt_maxconv_long_root_kernel<T>, blocks(b * L), dim3(256), 0, st, w.s_sel, w.code, w.rxy, b,
-                       L, spec, z, pstar);
-    timing_after(st);
-    return hipGetLastError();
+    return e;
 }
 
-// The ring results of long lists (N > kMaxConvN) through global buffers.
-template <typename T>
+// The ring results of long lists (N > kMaxConvN) through the global buffer.
+template <typename T, int N2>
 hipError_t launch_xy_long(const T* x, const T* y, int64_t n, const MaxconvSpec& spec, const XyWorkspace& w,
                           hipStream_t st) {
-    const int logN = maxconv_log_size(n, n);
-    const int N = 1 << logN;
-    const int64_t slots = 2 * (int64_t)spec.n, total = slots * N, L = 2 * n - 1;
-    auto blocks = [](int64_t count) { return dim3((unsigned)((count + 255) / 256)); };
+    constexpr int N = 128 * N2;
+    const unsigned slots = 2 * (unsigned)spec.n;
     timing_before("mt_xy_sigma_setup", st);
-    hipLaunchKernelGGL(mt_xy_long_setup_kernel<T>, dim3(1), dim3(1024), 0, st, x, y, n, N, w.tw, w.mxy);
+    hipLaunchKernelGGL(mt_xy_long_setup_kernel<T>, dim3(1 + twiddle_blocks(N)), dim3(kLongSetupThreads), 0, st, x, y,
+                       n, N, w.tw, w.mxy);
     timing_after(st);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    timing_before("mt_xy_sigma_load", st);
-    hipLaunchKernelGGL(mt_xy_long_load_kernel<T>, blocks(total), dim3(256), 0, st, x, y, n, logN, spec, w.mxy,
-                       w.buf0);
+    const XyLoad<T> ld{x, y, n, w.mxy, spec};
+    timing_before("mt_xy_sigma_columns", st);
+    hipLaunchKernelGGL((mt_long_columns_kernel<N2, XyLoad<T>>), dim3(slots * (N2 / kF4Lines)), dim3(kF4Threads), 0,
+                       st, ld, w.buf, w.tw);
     timing_after(st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    double2* cur = w.buf0;
-    double2* nxt = w.buf1;
-    if ((e = long_convolve(cur, nxt, logN, slots, w.tw, "mt_xy_sigma_pass", "mt_xy_sigma_product", st)) != hipSuccess)
-        return e;
-    timing_before("mt_xy_sigma_store", st);
-    hipLaunchKernelGGL(mt_xy_long_store_kernel, blocks(slots * L), dim3(256), 0, st, cur, logN, L, slots, w.sigma);
+    timing_before("mt_xy_sigma_middle", st);
+    hipLaunchKernelGGL(mt_long_middle_kernel<N2>, dim3(slots * 16), dim3(kF4Threads), 0, st, w.buf, w.tw,
+                       (const int*)nullptr, (int64_t)1, 0);
+    timing_after(st);
+    timing_before("mt_xy_sigma_rows", st);
+    hipLaunchKernelGGL(mt_xy_long_rows_kernel<N2>, dim3(slots * 16), dim3(kF4Threads), 0, st, w.buf, w.tw, 2 * n - 1,
+                       w.sigma);
     timing_after(st);
     return hipGetLastError();
 }
@@ -1828,8 +1934,8 @@ hipError_t launch_xy_t(const T* x, const T* y, int64_t n, int32_t k, const Maxco
         case 10: e = launch_xy_sigma_n<T, 10>(x, y, n, spec, w.sigma, st); break;
         case 11: e = launch_xy_sigma_n<T, 11>(x, y, n, spec, w.sigma, st); break;
         case 12: e = launch_xy_sigma_n<T, 12>(x, y, n, spec, w.sigma, st); break;
-        case 13:
-        case 14: e = launch_xy_long<T>(x, y, n, spec, w, st); break;
+        case 13: e = launch_xy_long<T, 64>(x, y, n, spec, w, st); break;
+        case 14: e = launch_xy_long<T, 128>(x, y, n, spec, w, st); break;
         default: break;
     }
     if (e != hipSuccess) return e;
@@ -1877,10 +1983,15 @@ hipError_t launch_maxconv(const void* x, const void* y, int f64, int64_t b, int6
     const int logN = maxconv_log_size(n, m);
     if (logN > kLongConvLog) return hipErrorInvalidValue;
     if (logN > kMaxConvLog) {
-        if (f64)
-            return launch_maxconv_long<double>((const double*)x, (const double*)y, b, n, m, spec, (double*)z, pstar,
-                                               w, st);
-        return launch_maxconv_long<float>((const float*)x, (const float*)y, b, n, m, spec, (float*)z, pstar, w, st);
+        auto run = [&](auto one, auto n2) {
+            using T = decltype(one);
+            return launch_maxconv_long<T, decltype(n2)::value>((const T*)x, (const T*)y, b, n, m, spec, (T*)z, pstar,
+                                                               w, st);
+        };
+        using N64 = std::integral_constant<int, 64>;
+        using N128 = std::integral_constant<int, 128>;
+        if (logN == 13) return f64 ? run(0.0, N64{}) : run(0.0f, N64{});
+        return f64 ? run(0.0, N128{}) : run(0.0f, N128{});
     }
     if (f64)
         return launch_maxconv_t<double>((const double*)x, (const double*)y, b, n, m, spec, (double*)z, pstar, st);
