@@ -372,9 +372,9 @@ mt_status apsp_affine_correct(void* D, mt_dtype dtype, int64_t n, const int32_t*
  * first, and stops once every index of its pair is decided; no workspace
  * (workspace may be NULL).  4096 < n + m - 1 <= 16384: the pairs go through
  * a global buffer in the workspace, several p at a time, largest first; a
- * pair whose indices are all decided is left out of the p after.  Larger lengths and b >= 2^31 return MT_ERR_UNSUPPORTED.
- * n = 0, m = 0 or b = 0: empty output, nothing written.  Asynchronous on the
- * stream.  Workspace from maxconv_workspace_size (0 bytes up to 4096; above,
+ * pair whose indices are all decided is left out of the p after.  Larger
+ * lengths and b >= 2^31 return MT_ERR_UNSUPPORTED.  n = 0, m = 0 or b = 0:
+ * empty output, nothing written.  Asynchronous on the stream.  Workspace from maxconv_workspace_size (0 bytes up to 4096; above,
  * about 16 s N + 9 (n + m - 1) bytes per pair, N the transform length, s >= 2
  * the p at a time, at most |P| and as many as fit in 64 MiB).
  */

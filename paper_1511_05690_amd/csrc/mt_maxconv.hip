@@ -45,6 +45,7 @@
 // Exact: z[t] = max_i x[i] y[t - i] by the definition, one thread per output
 // index, products in the input precision.
 
+#include <algorithm>
 #include <atomic>
 #include <climits>
 #include <type_traits>
@@ -875,167 +876,145 @@ __global__ __launch_bounds__(256) void mt_xy_index_kernel(const int32_t* __restr
 constexpr int kSelThreads = 1024;
 constexpr int kSelPer = kLongConvN / kSelThreads;  // covers 2n - 1 < kLongConvN
 
-// Block-wide exclusive sum of v over threads in thread order; every thread
-// of the block calls it.
-__device__ __forceinline__ uint32_t block_sum_before(uint32_t v, uint32_t* wtot) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t inc = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-    }
-    if (lane == 63) wtot[wv] = inc;
-    __syncthreads();
-    uint32_t before = 0;
-#pragma unroll
-    for (int w2 = 0; w2 < kSelThreads / 64; ++w2) before += w2 < wv ? wtot[w2] : 0u;
-    return before + inc - v;
-}
-
 // The K candidates of each run (block = run): the K largest psi, lowest m
-// on ties, written in ascending m with their sigma columns
-// (cand_cols[(run np + q) K + slot]).  psi >= 0, so its bit pattern orders as
-// its value; the K-th largest key is found by an 8-bit radix select, then
-// the keys above it and the first keys equal to it (in m order) are kept.
+// on ties, written in ascending m.  psi >= 0, so its bit pattern orders as
+// its value; the K-th largest key is found by counting the keys (held in
+// registers) at or above a threshold by ballots until exactly K are, then the
+// keys above it and the first keys equal to it (in m order) are kept.  An
+// 8-bit radix select spent its time on LDS atomics of neighbouring
+// keys to the same bin: 42 us at L = 16383,
+// K = 256, |P| = 24, now 21 and 5 for the columns.
 __global__ __launch_bounds__(kSelThreads) void mt_xy_select_kernel(const double* __restrict__ psi, int L, int K,
-                                                                   const double* __restrict__ sigma, int np,
                                                                    int32_t* __restrict__ cand_m,
-                                                                   double* __restrict__ cand_psi,
-                                                                   double* __restrict__ cand_cols) {
-    __shared__ uint32_t hist[256];
-    __shared__ int s_bin, s_above;
+                                                                   double* __restrict__ cand_psi) {
+    __shared__ int wcount[2][kSelThreads / 64];
+    __shared__ uint64_t wtop[kSelThreads / 64];
     __shared__ uint32_t wtot[kSelThreads / 64];
-    __shared__ int taken_m[kPairedMaxK];
-    const int tid = threadIdx.x, run = blockIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, run = blockIdx.x, lane = tid & 63, wave = tid >> 6;
     const double* ps = psi + (int64_t)run * L;
-    if (tid == 0) s_bin = s_above = 0;
     uint64_t key[kSelPer];
-    // thread tid owns m = kSelPer tid + c: thread order is m order
+    // lane l of a wave owns m = m0 + 64 c
+    const int m0 = 64 * kSelPer * wave + lane;
 #pragma unroll
     for (int c = 0; c < kSelPer; ++c) {
-        const int m = kSelPer * tid + c;
+        const int m = m0 + 64 * c;
         key[c] = m < L ? (uint64_t)__double_as_longlong(ps[m]) : 0ull;
     }
-    uint64_t prefix = 0, mask = 0;
-    int need = K;  // keys still to take among those matching prefix
-    for (int d = 7; d >= 0; --d) {
-        const int shift = 8 * d;
-        if (tid < 256) hist[tid] = 0u;
-        __syncthreads();
-        // the high digits of psi's bits are shared by almost every key: when
-        // a wave's counted keys all fall in one bin, one lane adds them
+    // the largest threshold with at least K keys at or above it: from the
+    // largest key down in steps that grow until K keys are there, then bit by
+    // bit up again, until exactly K are
+    uint64_t top = 0;
 #pragma unroll
-        for (int c = 0; c < kSelPer; ++c) {
-            const bool counted = kSelPer * tid + c < L && (key[c] & mask) == prefix;
-            const uint32_t bin = (uint32_t)(key[c] >> shift) & 255u;
-            const uint64_t act = __ballot(counted);
-            if (act == 0) continue;
-            const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)bin, (int)__ffsll((unsigned long long)act) - 1);
-            if (__ballot(counted && bin == b0) == act) {
-                if (lane == 0) atomicAdd(&hist[b0], (uint32_t)__popcll(act));
-            } else if (counted) {
-                atomicAdd(&hist[bin], 1u);
-            }
-        }
-        __syncthreads();
-        if (tid < 64) {
-            // lane l holds bins 255 - 4l .. 252 - 4l (descending)
-            int h[4], tot = 0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                h[u] = (int)hist[255 - 4 * lane - u];
-                tot += h[u];
-            }
-            int inc = tot;
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(inc, o);
-                if (lane >= o) inc += t;
-            }
-            const int exc = inc - tot;
-            if (exc < need && inc >= need) {
-                int cum = exc, b = -1;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (b < 0) {
-                        if (cum + h[u] >= need)
-                            b = 255 - 4 * lane - u;
-                        else
-                            cum += h[u];
-                    }
-                }
-                s_bin = b;
-                s_above = cum;
-            }
-        }
-        __syncthreads();
-        prefix |= (uint64_t)s_bin << shift;
-        mask |= 255ull << shift;
-        need -= s_above;
-        __syncthreads();
+    for (int c = 0; c < kSelPer; ++c) top = key[c] > top ? key[c] : top;
+    for (int d = 32; d >= 1; d >>= 1) {
+        const uint64_t o = (uint64_t)__shfl_xor((unsigned long long)top, d);
+        top = o > top ? o : top;
     }
+    if (lane == 0) wtop[wave] = top;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSelThreads / 64; ++w) top = wtop[w] > top ? wtop[w] : top;
+    uint64_t at = 0;
+    bool exact = false;
+    int step = 0;
+    auto enough = [&](uint64_t cand) {
+        int n = 0;
+#pragma unroll
+        for (int c = 0; c < kSelPer; ++c) n += (int)__popcll(__ballot(m0 + 64 * c < L && key[c] >= cand));
+        int* counts = wcount[step++ & 1];
+        if (lane == 0) counts[wave] = n;
+        __syncthreads();
+        n = 0;
+#pragma unroll
+        for (int w = 0; w < kSelThreads / 64; ++w) n += counts[w];
+        if (n >= K) at = cand;
+        exact = n == K;
+        return n >= K;
+    };
+    // psi >= 0 as bits: one part in 2^7 of a value is 2^45 ... 2^46
+    int bit = 46;
+    while (bit < 64 && top >> bit != 0 && !enough(top + 1 - (1ull << bit))) bit += 2;
+    // at + 2^bit - 1 >= top, so the threshold is in the bits below
+    for (bit = bit < 64 ? bit : 64; bit > 0 && !exact;) {
+        --bit;
+        const uint64_t cand = at + (1ull << bit);
+        if (cand > at && cand <= top) enough(cand);
+    }
+    // exactly K keys from the threshold up: all of them, none left to ties
+    const uint64_t prefix = exact && at > 0 ? at - 1 : at;
     // keys above the threshold, and the first `need` keys equal to it in m
-    // order: one block scan of the per-thread counts (above | equal << 16)
-    uint32_t n_gt = 0, n_eq = 0;
+    // order: the waves' counts (above | equal << 16), then ballots
+    uint32_t count = 0;
 #pragma unroll
     for (int c = 0; c < kSelPer; ++c) {
-        const bool ok = kSelPer * tid + c < L;
-        n_gt += ok && key[c] > prefix ? 1u : 0u;
-        n_eq += ok && key[c] == prefix ? 1u : 0u;
+        const bool ok = m0 + 64 * c < L;
+        count += (uint32_t)__popcll(__ballot(ok && key[c] > prefix)) |
+                 (uint32_t)__popcll(__ballot(ok && key[c] == prefix)) << 16;
     }
-    const uint32_t before = block_sum_before(n_gt | (n_eq << 16), wtot);
-    const int gt_before = (int)(before & 0xffffu), eq_before = (int)(before >> 16);
-    int pos = gt_before + (eq_before < need ? eq_before : need), eq_rank = eq_before;
+    if (lane == 0) wtot[wave] = count;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kSelThreads / 64; ++w) {
+        before += w < wave ? wtot[w] : 0u;
+        total += wtot[w];
+    }
+    const int need = K - (int)(total & 0xffffu);
+    int gt_before = (int)(before & 0xffffu), eq_before = (int)(before >> 16);
+    const uint64_t below = (1ull << lane) - 1;
 #pragma unroll
     for (int c = 0; c < kSelPer; ++c) {
-        const int m = kSelPer * tid + c;
+        const int m = m0 + 64 * c;
         const bool ok = m < L;
         const bool gt = ok && key[c] > prefix, eq = ok && key[c] == prefix;
-        const bool take = gt || (eq && eq_rank < need);
-        eq_rank += eq ? 1 : 0;
-        if (take && pos < K) {
+        const uint64_t gts = __ballot(gt), eqs = __ballot(eq);
+        const int eq_rank = eq_before + (int)__popcll(eqs & below);
+        const int pos = gt_before + (int)__popcll(gts & below) + (eq_rank < need ? eq_rank : need);
+        if ((gt || (eq && eq_rank < need)) && pos < K) {
             cand_m[(int64_t)run * K + pos] = m;
-            cand_psi[(int64_t)run * K + pos] = __longlong_as_double((long long)key[c]);
-            taken_m[pos] = m;
+            cand_psi[(int64_t)run * K + pos] = ps[m];
         }
-        pos += take ? 1 : 0;
+        gt_before += (int)__popcll(gts);
+        eq_before += (int)__popcll(eqs);
     }
-    __syncthreads();
-    // the candidates' columns, every thread gathering (q, slot) cells
-    const double* sg = sigma + (int64_t)run * np * L;
-    double* cc = cand_cols + (int64_t)run * np * K;
-    for (int u = tid; u < np * K; u += kSelThreads) {
-        const int q = u / K, slot = u - q * K;
-        cc[u] = sg[(int64_t)q * L + taken_m[slot]];
-    }
+}
+
+// The candidates' columns, cand_cols[(run np + q) K + slot]: a kernel of its
+// own, for the cells lie a cache line apart each and one compute unit has too
+// few of them on their way.
+__global__ __launch_bounds__(256) void mt_xy_gather_kernel(const double* __restrict__ sigma, int L, int K, int np,
+                                                           const int32_t* __restrict__ cand_m,
+                                                           double* __restrict__ cand_cols) {
+    const int u = blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= 2 * np * K) return;
+    const int row = u / K, slot = u - row * K;
+    cand_cols[u] = sigma[(int64_t)row * L + cand_m[(row >= np ? K : 0) + slot]];
 }
 
 __device__ __forceinline__ int diag_len(int m, int n) { return (m < 2 * n - 2 - m ? m : 2 * n - 2 - m) + 1; }
 
 // A lane's candidate slots held in registers (slot u * 32 + q of its run in
-// entry u, q = lane % 32): the largest log psi, the first valid slot on ties
-// and all -inf.
+// entry u, q = lane % 32; entries beyond K are -inf): the largest log psi,
+// the first slot on ties and all -inf (K on a lane without slots).
 template <int kS>
 __device__ __forceinline__ void slots_best(const double (&rv)[kS], const int (&rm)[kS], int q, int K, double& bv,
                                            int& bs, int& bm) {
-    bv = -INFINITY;
-    bs = K;
-    bm = 0;
+    bv = rv[0];
+    bs = q < K ? q : K;
+    bm = rm[0];
 #pragma unroll
-    for (int u = 0; u < kS; ++u) {
-        const int s = u * 32 + q;
-        if (s < K && (bs == K || rv[u] > bv)) {
-            bv = rv[u];
-            bs = s;
-            bm = rm[u];
-        }
+    for (int u = 1; u < kS; ++u) {
+        const bool more = rv[u] > bv;
+        bv = more ? rv[u] : bv;
+        bs = more ? u * 32 + q : bs;
+        bm = more ? rm[u] : bm;
     }
 }
 
 template <int kS>
 __device__ __forceinline__ void slots_set(double (&rv)[kS], int u, double e) {
 #pragma unroll
-    for (int w = 0; w < kS; ++w)
-        if (w == u) rv[w] = e;
+    for (int w = 0; w < kS; ++w) rv[w] = w == u ? e : rv[w];
 }
 
 // The largest v of each half wave (lanes 0..31 and 32..63) and, among the
@@ -1043,12 +1022,18 @@ __device__ __forceinline__ void slots_set(double (&rv)[kS], int u, double e) {
 // each row's maximum in its lane 15, row_bcast:15 into rows 1 and 3 brings
 // the two rows of a half together in lanes 31 and 63.  v must not be NaN.
 __device__ __forceinline__ void half_argmax(double v, int s, double& a0, int& s0, double& a1, int& s1) {
+    // fmax without its quieting of the operands
+    auto max2 = [](double a, double b) {
+        double r;
+        asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+        return r;
+    };
     double m = v;
-    m = fmax(m, dpp_f64<0x111, 0xf>(m));
-    m = fmax(m, dpp_f64<0x112, 0xf>(m));
-    m = fmax(m, dpp_f64<0x114, 0xf>(m));
-    m = fmax(m, dpp_f64<0x118, 0xf>(m));
-    m = fmax(m, dpp_f64<0x142, 0xa>(m));
+    m = max2(m, dpp_f64<0x111, 0xf>(m));
+    m = max2(m, dpp_f64<0x112, 0xf>(m));
+    m = max2(m, dpp_f64<0x114, 0xf>(m));
+    m = max2(m, dpp_f64<0x118, 0xf>(m));
+    m = max2(m, dpp_f64<0x142, 0xa>(m));
     a0 = readlane_f64(m, 31);
     a1 = readlane_f64(m, 63);
     const bool tie = v == ((threadIdx.x & 32) ? a1 : a0);
@@ -1088,8 +1073,17 @@ __device__ __forceinline__ void half_argmax(double v, int s, double& a0, int& s0
 // and diagonals, stay in registers.  The log diagonal lengths of the paired
 // acceptance test are kept in LDS when they fit (kLenLds), else taken from
 // the popped diagonals each rank (the same values).
+//
+// A rank is one dependent chain (argmax, x_i and y_j, exp, log, rescan) on one
+// wave, so it costs its latencies: the chain has no branches (selects instead,
+// results stored every 64 ranks, the first 64 kDoneRegs reported pairs
+// compared in registers).  The other waves of the block only help to fill
+// LDS.  n = 8192, K = k = 256, |P| = 24, paired: 498 -> 289 us, of which
+// filling LDS was 80 with one wave.
+constexpr int kLockThreads = 512;
+constexpr int kDoneRegs = 4;  // x 64 lanes
 template <typename T, bool kPaired, bool kColsLds, int kRegS, bool kLenLds>
-__global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict__ x, const T* __restrict__ y,
+__global__ __launch_bounds__(kLockThreads) void mt_xy_lockstep_kernel(const T* __restrict__ x, const T* __restrict__ y,
                                                           int64_t n, MaxconvSpec spec,
                                                           const int32_t* __restrict__ cand_m,
                                                           const double* __restrict__ cand_psi,
@@ -1103,7 +1097,7 @@ __global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict_
     // exp(p log psi) and the new root exp(log S / p) then need no log or exp
     // of their own.
     extern __shared__ double cv[];
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int np = spec.n, nn = (int)n;
     constexpr int kLen = kPaired && kLenLds ? 1 : 0;
     double* cl = cv + 2 * K;  // used when kLen
@@ -1112,7 +1106,8 @@ __global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict_
     int* done = cm + 2 * K;  // paired only
     int n_done = 0;
     double mx = -INFINITY, my = -INFINITY;
-    for (int i = lane; i < nn; i += 64) {
+#pragma unroll 8
+    for (int i = tid; i < nn; i += kLockThreads) {
         mx = fmax(mx, (double)x[i]);
         my = fmax(my, (double)y[i]);
     }
@@ -1120,8 +1115,19 @@ __global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict_
         mx = fmax(mx, __shfl_xor(mx, d));
         my = fmax(my, __shfl_xor(my, d));
     }
+    constexpr int kWaves = kLockThreads / 64;
+    if (lane == 0) {
+        cv[tid >> 6] = mx;
+        cv[kWaves + (tid >> 6)] = my;
+    }
+    __syncthreads();
+    for (int w = 0; w < kWaves; ++w) {
+        mx = fmax(mx, cv[w]);
+        my = fmax(my, cv[kWaves + w]);
+    }
+    __syncthreads();
     const double shift = mx + my;
-    for (int s = lane; s < 2 * K; s += 64) {
+    for (int s = tid; s < 2 * K; s += kLockThreads) {
         const double e = cand_psi[s];
         const int m = cand_m[s];
         cv[s] = e > 0.0 ? log(e) : -INFINITY;
@@ -1129,8 +1135,10 @@ __global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict_
         cm[s] = m;
     }
     if (kColsLds)
-        for (int s = lane; s < 2 * np * K; s += 64) cols[s] = cand_cols[s];
+#pragma unroll 8
+        for (int s = tid; s < 2 * np * K; s += kLockThreads) cols[s] = cand_cols[s];
     __syncthreads();
+    if (tid >= 64) return;
     const int half = lane >> 5, q = lane & 31;
     const int S = (K + 31) / 32;
     // the lane's largest log psi of its run and its slot (the first valid
@@ -1170,6 +1178,13 @@ __global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict_
     const bool mine = q < np;
     // this lane's power and its reciprocal; a rank picks other lanes' by readlane
     const double pw = mine ? (double)spec.p[q] : 1.0, ipw = 1.0 / pw;
+    // the reported pairs: the first 64 kDoneRegs in registers, the rest in LDS
+    int dr[kDoneRegs];
+#pragma unroll
+    for (int w = 0; w < kDoneRegs; ++w) dr[w] = -1;
+    // rank r's results wait in lane r % 64 for the last of 64 ranks
+    double out_v = 0.0;
+    int out_m1 = 0, out_m2 = 0, out_i = -1, out_j = -1;
     for (int r = 0; r < k; ++r) {
         double a0, a1;
         int s0, s1;
@@ -1178,21 +1193,21 @@ __global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict_
         const int sd = m1 + m2 - (nn - 1);
         const int i = sd >> 1, j = m1 - i;
         bool valid = (sd & 1) == 0 && sd >= 0 && i < nn && j >= 0 && j < nn;
-        double* cp = cols + (half * np + q) * K + (half ? s1 : s0);
-        double cell = 0.0;
-        if (mine) cell = *cp;
+        double xi = 0.0, yj = 0.0, lv = 0.0;
+        if (kPaired) {
+            xi = (double)x[valid ? i : 0];
+            yj = (double)y[valid ? j : 0];
+        }
+        double* cp = cols + (half * np + (mine ? q : 0)) * K + (half ? s1 : s0);
+        const double cell = *cp;
         const double la0 = a0, la1 = a1;
         bool acc = false;
-        double xi = 0.0, yj = 0.0, lv = 0.0;
         const int id = i * nn + j;
         if (kPaired) {
-            if (valid) {
-                xi = (double)x[i];
-                yj = (double)y[j];
-            }
             bool seen = false;
-            if (valid)
-                for (int u = lane; u < n_done; u += 64) seen |= done[u] == id;
+#pragma unroll
+            for (int w = 0; w < kDoneRegs; ++w) seen |= dr[w] == id;
+            for (int u = 64 * kDoneRegs + lane; u < n_done; u += 64) seen |= done[u] == id;
             valid = valid && __ballot(seen) == 0;
             const uint64_t st = __ballot(mine && cell >= spec.tau);
             const uint32_t lo_b = (uint32_t)st, hi_b = (uint32_t)(st >> 32);
@@ -1201,50 +1216,57 @@ __global__ __launch_bounds__(64) void mt_xy_lockstep_kernel(const T* __restrict_
             lv = (xi - mx) + (yj - my);
             const double ll0 = kLen ? cl[s0] : log((double)diag_len(m1, nn));
             const double ll1 = kLen ? cl[K + s1] : log((double)diag_len(m2, nn));
-            acc = valid && q0 >= 0 && q1 >= 0 && lv >= la0 - ll0 * readlane_f64(ipw, q0 >= 0 ? q0 : 0) &&
-                  lv >= la1 - ll1 * readlane_f64(ipw, q1 >= 0 ? 32 + q1 : 32);
+            const double i0 = readlane_f64(ipw, q0 >= 0 ? q0 : 0), i1 = readlane_f64(ipw, q1 >= 0 ? 32 + q1 : 32);
+            acc = valid & (q0 >= 0) & (q1 >= 0) & (lv >= la0 - ll0 * i0) & (lv >= la1 - ll1 * i1);
         }
         const double la = acc ? lv : (half ? la1 : la0);
-        double s = 0.0;
-        bool ns = false;
-        if (mine) {
-            s = cell - exp(la * pw);
-            *cp = s;
-            ns = s >= spec.tau;
-        }
-        const uint64_t nm = __ballot(ns);
+        const double s = cell - exp(la * pw);
+        if (mine) *cp = s;
+        const uint64_t nm = __ballot(mine && s >= spec.tau);
         const uint32_t nlo = (uint32_t)nm, nhi = (uint32_t)(nm >> 32);
         const int h0 = nlo ? 31 - __clz(nlo) : -1, h1 = nhi ? 31 - __clz(nhi) : -1;
         const int l0 = h0 >= 0 ? h0 : 0, l1 = h1 >= 0 ? 32 + h1 : 32;
         // both runs' new roots in one log: half 0 takes run 0's sum, half 1 run 1's
-        const double sh = half ? readlane_f64(s, l1) : readlane_f64(s, l0);
-        const double ih = half ? readlane_f64(ipw, l1) : readlane_f64(ipw, l0);
+        double sv0 = readlane_f64(s, l0), sv1 = readlane_f64(s, l1);
+        double iv0 = readlane_f64(ipw, l0), iv1 = readlane_f64(ipw, l1);
+        asm volatile("" : "+v"(sv0), "+v"(sv1), "+v"(iv0), "+v"(iv1));  // selects, no branches
+        const double sh = half ? sv1 : sv0, ih = half ? iv1 : iv0;
         const double lr = log(sh) * ih;
-        const double e0 = h0 >= 0 ? readlane_f64(lr, 0) : -INFINITY;
-        const double e1 = h1 >= 0 ? readlane_f64(lr, 32) : -INFINITY;
-        if (lane == 0) {
-            values[r] = acc ? xi + yj : shift + la0;
-            if (diag) diag[r] = m1;
-            anti[r] = m2;
-            const bool give = kPaired ? acc : valid;
-            if (ii) ii[r] = give ? i : -1;
-            if (jj) jj[r] = give ? j : -1;
-            if (kPaired && acc) done[n_done] = id;
+        const double e = (half ? h1 : h0) >= 0 ? lr : -INFINITY;
+        const bool give = kPaired ? acc : valid;
+        if (lane == (r & 63)) {
+            out_v = acc ? xi + yj : shift + la0;
+            out_m1 = m1;
+            out_m2 = m2;
+            out_i = give ? i : -1;
+            out_j = give ? j : -1;
+        }
+        if ((r & 63) == 63 || r == k - 1) {
+            const int at = r - (r & 63) + lane;
+            if (at <= r) {
+                values[at] = out_v;
+                if (diag) diag[at] = out_m1;
+                anti[at] = out_m2;
+                if (ii) ii[at] = out_i;
+                if (jj) jj[at] = out_j;
+            }
+        }
+        if (kPaired && acc && n_done >= 64 * kDoneRegs && lane == 0) done[n_done] = id;
+        if (kPaired && acc) {
+#pragma unroll
+            for (int w = 0; w < kDoneRegs; ++w) dr[w] = n_done == 64 * w + lane ? id : dr[w];
         }
         n_done += acc ? 1 : 0;
         // the owner of each popped slot (one lane per half) takes its new
         // estimate and rescans its slots
         const int so = half ? s1 : s0;
-        if (q == (so & 31)) {
-            const double e = half ? e1 : e0;
-            if (kRegS > 0) {
-                slots_set(rv, so >> 5, e);
-                slots_best(rv, rm, q, K, bv, bs, bm);
-            } else {
-                cv[half * K + so] = e;
-                lane_best(bv, bs);
-                bm = cm[half * K + bs];
-            }
+        if (kRegS > 0) {
+            slots_set(rv, q == (so & 31) ? so >> 5 : -1, e);
+            slots_best(rv, rm, q, K, bv, bs, bm);
+        } else if (q == (so & 31)) {
+            cv[half * K + so] = e;
+            lane_best(bv, bs);
+            bm = cm[half * K + bs];
         }
     }
 }
@@ -1868,7 +1890,9 @@ hipError_t launch_lockstep(const T* x, const T* y, int64_t n, int32_t k, int K, 
                            double* values, int32_t* diag, int32_t* ii, int32_t* jj, const XyWorkspace& w,
                            hipStream_t st) {
     auto queue = mt_xy_lockstep_kernel<T, kPaired, kColsLds, kRegS, kLenLds>;
-    const size_t lds = lockstep_lds(K, k, spec.n, kPaired, kColsLds, kLenLds);
+    // at least the waves' maxima
+    const size_t lds = std::max(lockstep_lds(K, k, spec.n, kPaired, kColsLds, kLenLds),
+                                (size_t)(2 * kLockThreads / 64) * sizeof(double));
     if (lds > kLdsBytes) return hipErrorInvalidValue;
     static std::atomic<uint64_t> attr_set{0};
     int dev = 0;
@@ -1881,7 +1905,7 @@ hipError_t launch_lockstep(const T* x, const T* y, int64_t n, int32_t k, int K, 
         attr_set.fetch_or(bit);
     }
     timing_before(kPaired ? "mt_xy_paired" : "mt_xy_queue", st);
-    hipLaunchKernelGGL(queue, dim3(1), dim3(64), lds, st, x, y, n, spec, w.cand_m,
+    hipLaunchKernelGGL(queue, dim3(1), dim3(kLockThreads), lds, st, x, y, n, spec, w.cand_m,
                        w.cand_psi, w.cand_cols, K, k, values, diag, w.diag1, ii, jj);
     timing_after(st);
     return hipGetLastError();
@@ -1896,8 +1920,9 @@ hipError_t launch_xy_candidates(const T* x, const T* y, int64_t n, int32_t k, co
     const int L = (int)(2 * n - 1), K = k < L ? k : L;
     if (k > kPairedMaxK || L >= kLongConvN || spec.n > 32) return hipErrorInvalidValue;
     timing_before("mt_xy_select", st);
-    hipLaunchKernelGGL(mt_xy_select_kernel, dim3(2), dim3(kSelThreads), 0, st, w.psi, L, K, w.sigma, spec.n,
-                       w.cand_m, w.cand_psi, w.cand_cols);
+    hipLaunchKernelGGL(mt_xy_select_kernel, dim3(2), dim3(kSelThreads), 0, st, w.psi, L, K, w.cand_m, w.cand_psi);
+    hipLaunchKernelGGL(mt_xy_gather_kernel, dim3((unsigned)(2 * spec.n * K + 255) / 256), dim3(256), 0, st, w.sigma,
+                       L, K, spec.n, w.cand_m, w.cand_cols);
     timing_after(st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
