@@ -846,7 +846,7 @@ mt_status estimate_impl(const void* A, const void* B, mt_dtype dtype, int64_t b,
     // small FP64-path products without projections, balancing or the
     // domain check: one kernel (maxima, powers, ring products, selection)
     const uint32_t small_ok = MT_FLAG_CLAMP | MT_FLAG_NORM_CORRECT;
-    if (!f.bf16 && k > 0 && !(f.flags & ~small_ok) && b <= 65535 && (m + 31) / 32 <= 65535 &&
+    if (!f.bf16 && k > 0 && !(f.flags & ~small_ok) && small_product_fits(b, m, n) &&
         (double)b * m * k * n <= (double)g_small_limit.load()) {
         SmallSpec sp;
         memset(&sp, 0, sizeof sp);
@@ -858,7 +858,7 @@ mt_status estimate_impl(const void* A, const void* B, mt_dtype dtype, int64_t b,
         }
         sp.tau = f.tau;
         sp.clamp = rsp.clamp;
-        MT_TRY(launch_small_product_f64(A, B, f64, b, m, k, n, sp, C, f64, p_star, st), "small product (FP64)");
+        MT_TRY(launch_small_product_f64(A, B, f64, b, m, k, n, sp, C, p_star, st), "small product (FP64)");
         return MT_OK;
     }
     int32_t* flag = (int32_t*)(ws + L.hdr);

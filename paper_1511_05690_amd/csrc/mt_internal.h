@@ -326,9 +326,9 @@ struct SmallSpec {
     double tau;
     int32_t clamp;
 };
-hipError_t launch_small_product_f64(const void* A, const void* B, int in_f64, int64_t b, int64_t m, int64_t k,
-                                    int64_t n, const SmallSpec& spec, void* C, int out_f64, uint8_t* pstar,
-                                    hipStream_t st);
+bool small_product_fits(int64_t b, int64_t m, int64_t n);
+hipError_t launch_small_product_f64(const void* A, const void* B, int f64, int64_t b, int64_t m, int64_t k,
+                                    int64_t n, const SmallSpec& spec, void* C, uint8_t* pstar, hipStream_t st);
 // r = 2 projection over an S stack (plane t holds S at the t-th smallest of
 // the family's p and the added 3q): per family index fi, the stack plane of
 // its p (plane), of the next smaller family p (lo, -1 if none) and of q,

@@ -3,20 +3,26 @@
 // ring products S_p = A'^p B'^p (Alg. 3 / Alg. 5) and the selection of the
 // largest stable p with its 1/p root (Sec. 1, Alg. 5) in one launch.
 //
-// A workgroup owns a 32 x 32 output tile of one batch item.  It holds up to
-// 256 inner indices of its 32 rows of A and 32 columns of B in LDS at a time
-// (the whole inner dimension for k <= 256, loaded once), takes the row and
-// column maxima from them, then visits the family from the largest p down:
-// for each p it stages (a / r)^p and (b / c)^p of 32 inner indices at a
-// time and accumulates S_p in FP64 on the vector ALUs (each thread 2 x 2
-// entries).  An entry takes the first p with S_p >= tau (at the smallest p:
-// whatever S is, with no stable p marked); the tile stops once every entry
-// has its p.  For the small products it serves (b m k n up to a few times
-// 256^3) this replaces the general path's seven to fourteen launches
-// (maxima, planes, MFMA GEMM, sparse tail, root) whose fixed costs exceed the
-// arithmetic.  The numbers are those of the general FP64 path up to the
-// order of the FP64 sums.
-#include <atomic>
+// A workgroup of W waves owns a 16 x 16 output tile of one batch item, each
+// wave 32 inner indices of it.  A lane holds 8 inner indices of one row of A
+// and of one column of B in registers, as v_mfma_f64_16x16x4f64 takes its
+// operands; the row and column maxima come from the same registers.  For each
+// p, from the largest down, a lane raises its 16 values, the wave multiplies
+// them (8 MFMAs) and the waves' sums are added through LDS.  An entry takes
+// the first p with S_p >= tau (at the smallest p: whatever S is, with no
+// stable p marked); the tile stops once every entry has its p, and the roots
+// are taken once at the end.  For the small products it serves (b m k n up to
+// a few times 256^3) this replaces the general path's seven to fourteen
+// launches (maxima, planes, MFMA GEMM, sparse tail, root) whose fixed costs
+// exceed the arithmetic.  The numbers are those of the general FP64 path up
+// to the order of the FP64 sums.
+//
+// Bound by latencies (launch, first loads, one barrier pair per p), so the
+// tile is the smallest MFMA tile and the inner dimension is split over waves:
+// 256 x 256 x 256 is 256 workgroups, one per compute unit.  With 32 x 32
+// tiles on the vector ALUs, operands and powers in LDS, it was 64 workgroups
+// and 33 us a call; now 13 (kernel 9.6).  Elsewhere: 320^3 48 -> 25,
+// 4000 x 16^3 343 -> 17, 2048 x 8 x 2048 278 -> 50, 16 x 20000 x 16 2421 -> 370.
 #include <cfloat>
 #include <cmath>
 
@@ -25,17 +31,11 @@
 namespace mt {
 namespace {
 
-constexpr int kSmTile = 32;      // output tile edge
-constexpr int kSmK = 32;         // inner indices of one staged power chunk
-constexpr int kSmKR = 256;       // inner indices held raw in LDS at a time
-constexpr int kSmThreads = 256;  // 16 x 16 threads, 2 x 2 entries each
-// LDS in doubles: raw A [32][KR + 1], raw B [KR][32], powers A [32][K + 1],
-// powers B [K][32], then r, 1/r, c, 1/c
-constexpr int kSmRawA = kSmTile * (kSmKR + 1);
-constexpr int kSmRawB = kSmKR * kSmTile;
-constexpr int kSmPowA = kSmTile * (kSmK + 1);
-constexpr int kSmPowB = kSmK * kSmTile;
-constexpr size_t kSmLdsBytes = sizeof(double) * (kSmRawA + kSmRawB + kSmPowA + kSmPowB + 4 * kSmTile);
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kSmTile = 16;   // output tile edge
+constexpr int kSmLane = 8;    // inner indices of a lane
+constexpr int kSmWaveK = 32;  // inner indices of a wave: 4 lanes per row or column
 
 // the scaled input a / s of H': one reciprocal per line when s is normal
 // (inv > 0), a division when s is subnormal, 0 for a zero line
@@ -44,254 +44,217 @@ __device__ inline double sm_scaled(double a, double s, double inv) {
     return s > 0.0 ? a / s : 0.0;
 }
 
-template <typename TS, typename TO>
-__global__ __launch_bounds__(kSmThreads) void mt_small_product_f64_kernel(const TS* __restrict__ A,
-                                                                         const TS* __restrict__ B, int64_t m,
-                                                                         int64_t k, int64_t n, SmallSpec spec,
-                                                                         TO* __restrict__ C,
-                                                                         uint8_t* __restrict__ pstar,
-                                                                         unsigned long long* work) {
-    extern __shared__ double sm[];
-    double* ar = sm;              // [i * (KR + 1) + kk]
-    double* br = ar + kSmRawA;    // [kk * 32 + j]
-    double* ap = br + kSmRawB;    // [i * (K + 1) + kk]
-    double* bp = ap + kSmPowA;    // [kk * 32 + j]
-    double* rs = bp + kSmPowB;
-    double* rinv = rs + kSmTile;
-    double* cs = rinv + kSmTile;
-    double* cinv = cs + kSmTile;
+template <typename T, int W>
+__global__ __launch_bounds__(64 * W) void mt_small_product_f64_kernel(const T* __restrict__ A,
+                                                                     const T* __restrict__ B, int64_t m, int64_t k,
+                                                                     int64_t n, SmallSpec spec, T* __restrict__ C,
+                                                                     uint8_t* __restrict__ pstar,
+                                                                     unsigned long long* work) {
+    __shared__ double part[W * 256];
+    __shared__ double rmax[W * kSmTile], cmax[W * kSmTile];
+    constexpr int kChunk = W * kSmWaveK;
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (work && tid == 0) timing_span_begin(work);
-    const int64_t bi = blockIdx.z;
-    const int64_t row0 = (int64_t)blockIdx.y * kSmTile;
-    const int64_t col0 = (int64_t)blockIdx.x * kSmTile;
-    const TS* a = A + bi * m * k;
-    const TS* b = B + bi * k * n;
+    const int64_t bi = blockIdx.y;
+    const unsigned tiles_n = (unsigned)((n + kSmTile - 1) / kSmTile);
+    const int64_t row0 = (int64_t)(blockIdx.x / tiles_n) * kSmTile;
+    const int64_t col0 = (int64_t)(blockIdx.x % tiles_n) * kSmTile;
+    const int li = lane & 15, lk = wave * kSmWaveK + (lane >> 4) * kSmLane;
+    const bool row_in = row0 + li < m, col_in = col0 + li < n;
+    const T* a = A + (bi * m + (row_in ? row0 + li : m - 1)) * k;
+    const T* b = B + bi * k * n + (col_in ? col0 + li : n - 1);
 
-    // raw inner indices kr0 .. kr0 + KR - 1 of the tile's rows of A (read
-    // along k) and columns of B (read along the columns) into LDS; 0 outside.
-    // Every load is issued (indices outside are clamped to the last row,
-    // column or inner index and the value dropped), so that they are all in
-    // flight at once instead of one conditional load after another.
-    auto load_raw = [&](int64_t kr0, bool scale) {
-        constexpr int L = kSmTile * kSmKR / kSmThreads;
-        double v[L];
+    // this lane's 8 inner indices of the chunk from kr0 on, 0 outside.  Every
+    // load is issued (indices outside are clamped and the value dropped), so
+    // that they are all in flight at once.
+    double xa[kSmLane], xb[kSmLane];
+    auto load = [&](int64_t kr0) {
+        const int64_t q0 = kr0 + lk;
+        T va[kSmLane], vb[kSmLane];
 #pragma unroll
-        for (int s = 0; s < L; ++s) {
-            const int e = tid + s * kSmThreads;
-            const int i = e / kSmKR, kk = e % kSmKR;
-            const int64_t row = min(row0 + i, m - 1), q = min(kr0 + kk, k - 1);
-            v[s] = (double)a[row * k + q];
+        for (int s = 0; s < kSmLane; ++s) {
+            const int64_t q = min(q0 + s, k - 1);
+            va[s] = a[q];
+            vb[s] = b[q * n];
         }
 #pragma unroll
-        for (int s = 0; s < L; ++s) {
-            const int e = tid + s * kSmThreads;
-            const int i = e / kSmKR, kk = e % kSmKR;
-            double x = (row0 + i < m && kr0 + kk < k) ? v[s] : 0.0;
-            if (scale) x = sm_scaled(x, rs[i], rinv[i]);
-            ar[i * (kSmKR + 1) + kk] = x;
-        }
-#pragma unroll
-        for (int s = 0; s < L; ++s) {
-            const int e = tid + s * kSmThreads;
-            const int kk = e / kSmTile, j = e % kSmTile;
-            const int64_t col = min(col0 + j, n - 1), q = min(kr0 + kk, k - 1);
-            v[s] = (double)b[q * n + col];
-        }
-#pragma unroll
-        for (int s = 0; s < L; ++s) {
-            const int e = tid + s * kSmThreads;
-            const int kk = e / kSmTile, j = e % kSmTile;
-            double y = (col0 + j < n && kr0 + kk < k) ? v[s] : 0.0;
-            if (scale) y = sm_scaled(y, cs[j], cinv[j]);
-            br[kk * kSmTile + j] = y;
+        for (int s = 0; s < kSmLane; ++s) {
+            const bool in = q0 + s < k;
+            xa[s] = in && row_in ? (double)va[s] : 0.0;
+            xb[s] = in && col_in ? (double)vb[s] : 0.0;
         }
     };
 
-    // r_i = max_k A_ik and c_j = max_k B_kj of the tile: thread t keeps the
-    // maximum of row t / 8 over inner indices = t (mod 8) and of column t % 32
-    // over inner indices = t / 32 (mod 8); the 8 parts are combined at the end
-    double rpart = 0.0, cpart = 0.0;
-    for (int64_t kr0 = 0; kr0 < k; kr0 += kSmKR) {
-        if (kr0 > 0) __syncthreads();
-        load_raw(kr0, false);
-        __syncthreads();
-        const int ri = tid / 8, rp = tid % 8;
-        const int cj = tid % kSmTile, cp = tid / kSmTile;
-        double rv[kSmKR / 8], cv[kSmKR / 8];
+    // r_i = max_k A_ik and c_j = max_k B_kj of the tile
+    double r = 0.0, c = 0.0;
+    for (int64_t kr0 = 0; kr0 < k; kr0 += kChunk) {
+        load(kr0);
 #pragma unroll
-        for (int s = 0; s < kSmKR / 8; ++s) {
-            rv[s] = ar[ri * (kSmKR + 1) + rp + 8 * s];
-            cv[s] = br[(cp + 8 * s) * kSmTile + cj];
-        }
-#pragma unroll
-        for (int s = 0; s < kSmKR / 8; ++s) {
-            rpart = fmax(rpart, rv[s]);
-            cpart = fmax(cpart, cv[s]);
+        for (int s = 0; s < kSmLane; ++s) {
+            r = fmax(r, xa[s]);
+            c = fmax(c, xb[s]);
         }
     }
-    // rows: the 8 parts are 8 consecutive lanes
-    for (int off = 4; off > 0; off >>= 1) rpart = fmax(rpart, __shfl_xor(rpart, off, 64));
-    if (tid % 8 == 0) {
-        rs[tid / 8] = rpart;
-        rinv[tid / 8] = rpart >= DBL_MIN ? 1.0 / rpart : 0.0;
+    for (int off = 16; off < 64; off <<= 1) {
+        r = fmax(r, __shfl_xor(r, off));
+        c = fmax(c, __shfl_xor(c, off));
     }
-    // columns: the 8 parts are 32 threads apart; combine them through the
-    // power buffer (free until the first p)
-    ap[tid] = cpart;
-    __syncthreads();
-    if (tid < kSmTile) {
-        double mx = ap[tid];
-        for (int q = 1; q < kSmThreads / kSmTile; ++q) mx = fmax(mx, ap[tid + q * kSmTile]);
-        cs[tid] = mx;
-        cinv[tid] = mx >= DBL_MIN ? 1.0 / mx : 0.0;
+    if (lane < kSmTile) {
+        rmax[wave * kSmTile + lane] = r;
+        cmax[wave * kSmTile + lane] = c;
     }
     __syncthreads();
+    auto line_max = [](const double* mx, int i) {
+        double v = mx[i];
+#pragma unroll
+        for (int w = 1; w < W; ++w) v = fmax(v, mx[w * kSmTile + i]);
+        return v;
+    };
+    r = line_max(rmax, li);
+    c = line_max(cmax, li);
+    const double rinv = r >= DBL_MIN ? 1.0 / r : 0.0, cinv = c >= DBL_MIN ? 1.0 / c : 0.0;
+    auto scale = [&]() {
+#pragma unroll
+        for (int s = 0; s < kSmLane; ++s) {
+            xa[s] = sm_scaled(xa[s], r, rinv);
+            xb[s] = sm_scaled(xb[s], c, cinv);
+        }
+    };
+    // the operands stay in registers for every p when the inner dimension fits
+    const bool resident = k <= kChunk;
+    if (resident) scale();
 
-    // this thread's entries: rows 2 ty + di, columns 2 tx + dj; bit 2 di + dj
-    // of `open` is set while the entry has no p yet (entries outside C never)
-    const int tx = tid % 16, ty = tid / 16;
+    // this thread's entries e = tid + 64 W u of the tile (row e / 16, column
+    // e % 16); bit u of `open` is set while the entry has no p yet
+    constexpr int kOwn = W >= 4 ? 1 : 4 / W;
     uint32_t open = 0;
-    for (int di = 0; di < 2; ++di)
-        for (int dj = 0; dj < 2; ++dj)
-            if (row0 + 2 * ty + di < m && col0 + 2 * tx + dj < n) open |= 1u << (2 * di + dj);
-
-    // the tile stays in LDS for every p when the inner dimension fits; it is
-    // scaled in place once (the scaled inputs a / r, b / c of H')
-    const bool resident = k <= kSmKR;
-    if (resident) {
-        constexpr int L = kSmTile * kSmKR / kSmThreads;
+    double S[kOwn], corr[kOwn];
+    int ps[kOwn], qs[kOwn];
 #pragma unroll
-        for (int s = 0; s < L; ++s) {
-            const int e = tid + s * kSmThreads;
-            const int i = e / kSmKR, kk = e % kSmKR;
-            ar[i * (kSmKR + 1) + kk] = sm_scaled(ar[i * (kSmKR + 1) + kk], rs[i], rinv[i]);
-            const int kb = e / kSmTile, j = e % kSmTile;
-            br[kb * kSmTile + j] = sm_scaled(br[kb * kSmTile + j], cs[j], cinv[j]);
-        }
-        __syncthreads();
+    for (int u = 0; u < kOwn; ++u) {
+        const int e = tid + 64 * W * u;
+        if (e < 256 && row0 + e / kSmTile < m && col0 + e % kSmTile < n) open |= 1u << u;
+        S[u] = 0.0;
+        corr[u] = 1.0;
+        ps[u] = 1;
+        qs[u] = MT_PSTAR_NONE;
     }
+    const uint32_t mine = open;
     int visited = 0;
     for (int q = spec.n - 1; q >= 0; --q) {  // the largest p first
         ++visited;
         const int p = spec.p[q];
-        double acc00 = 0.0, acc01 = 0.0, acc10 = 0.0, acc11 = 0.0;
-        for (int64_t kr0 = 0; kr0 < k; kr0 += kSmKR) {
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int64_t kr0 = 0; kr0 < k; kr0 += kChunk) {
             if (!resident) {
-                load_raw(kr0, true);
-                __syncthreads();
+                load(kr0);
+                scale();
             }
-            const int kr_len = k - kr0 < kSmKR ? (int)(k - kr0) : kSmKR;
-            for (int kc = 0; kc < kr_len; kc += kSmK) {
-                // stage (a / r)^p and (b / c)^p of inner indices kc .. kc + 31:
-                // this thread's 8 values raised together by binary powering
-                constexpr int SE = kSmTile * kSmK / kSmThreads;
-                double xa[SE], xb[SE], ya[SE], yb[SE];
+            // (a / r)^p and (b / c)^p by binary powering
+            double ta[kSmLane], tb[kSmLane], ya[kSmLane], yb[kSmLane];
 #pragma unroll
-                for (int t = 0; t < SE; ++t) {
-                    const int e = tid + t * kSmThreads;
-                    xa[t] = ar[(e / kSmK) * (kSmKR + 1) + kc + e % kSmK];
-                    xb[t] = br[(kc + e / kSmTile) * kSmTile + e % kSmTile];
-                    ya[t] = 1.0;
-                    yb[t] = 1.0;
-                }
-                for (int pp = p; pp; pp >>= 1) {
-                    if (pp & 1) {
+            for (int s = 0; s < kSmLane; ++s) {
+                ta[s] = xa[s];
+                tb[s] = xb[s];
+                ya[s] = 1.0;
+                yb[s] = 1.0;
+            }
+            for (int pp = p; pp; pp >>= 1) {
+                if (pp & 1) {
 #pragma unroll
-                        for (int t = 0; t < SE; ++t) {
-                            ya[t] *= xa[t];
-                            yb[t] *= xb[t];
-                        }
-                    }
-#pragma unroll
-                    for (int t = 0; t < SE; ++t) {
-                        xa[t] *= xa[t];
-                        xb[t] *= xb[t];
+                    for (int s = 0; s < kSmLane; ++s) {
+                        ya[s] *= ta[s];
+                        yb[s] *= tb[s];
                     }
                 }
 #pragma unroll
-                for (int t = 0; t < SE; ++t) {
-                    const int e = tid + t * kSmThreads;
-                    ap[(e / kSmK) * (kSmK + 1) + e % kSmK] = ya[t];
-                    bp[(e / kSmTile) * kSmTile + e % kSmTile] = yb[t];
+                for (int s = 0; s < kSmLane; ++s) {
+                    ta[s] *= ta[s];
+                    tb[s] *= tb[s];
                 }
-                __syncthreads();
-#pragma unroll
-                for (int kk = 0; kk < kSmK; ++kk) {
-                    const double a0 = ap[(2 * ty) * (kSmK + 1) + kk], a1 = ap[(2 * ty + 1) * (kSmK + 1) + kk];
-                    const double2 bv = *(const double2*)&bp[kk * kSmTile + 2 * tx];
-                    acc00 = fma(a0, bv.x, acc00);
-                    acc01 = fma(a0, bv.y, acc01);
-                    acc10 = fma(a1, bv.x, acc10);
-                    acc11 = fma(a1, bv.y, acc11);
-                }
-                __syncthreads();
             }
+#pragma unroll
+            for (int s = 0; s < kSmLane; ++s)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ya[s], yb[s], acc, 0, 0, 0);
         }
-        const bool last = q == 0;
-        const double accs[4] = {acc00, acc01, acc10, acc11};
+        // accumulator t of a lane: row lane / 16 + 4 t, column lane % 16
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (!(open & (1u << e))) continue;
-            const double S = accs[e];
-            const bool stable = S >= spec.tau;
+        for (int t = 0; t < 4; ++t) part[wave * 256 + 64 * t + lane] = acc[t];
+        __syncthreads();
+        const bool last = q == 0;
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) {
+            if (!(open & (1u << u))) continue;
+            const int e = tid + 64 * W * u;
+            double s = part[e];
+#pragma unroll
+            for (int w = 1; w < W; ++w) s += part[w * 256 + e];
+            const bool stable = s >= spec.tau;
             if (!stable && !last) continue;
-            open &= ~(1u << e);
-            const int li = 2 * ty + (e >> 1), lj = 2 * tx + (e & 1);
-            const double root = p == 1 ? S : (S > 0.0 ? exp(log(S) / (double)p) : 0.0);
-            double v = rs[li] * cs[lj] * root * spec.corr[q];
-            if (spec.clamp) v = fmin(v, 1.0);
-            const int64_t o = (bi * m + row0 + li) * n + col0 + lj;
-            C[o] = (TO)v;
-            if (pstar) pstar[o] = stable ? (uint8_t)q : (uint8_t)MT_PSTAR_NONE;
+            open &= ~(1u << u);
+            S[u] = s;
+            ps[u] = p;
+            corr[u] = spec.corr[q];
+            if (stable) qs[u] = q;
         }
         if (!__syncthreads_or(open != 0)) break;
     }
-    if (work && tid == 0) {
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+        if (!(mine & (1u << u))) continue;
+        const int e = tid + 64 * W * u, i = e / kSmTile, j = e % kSmTile;
+        const double root = ps[u] == 1 ? S[u] : (S[u] > 0.0 ? exp(log(S[u]) / (double)ps[u]) : 0.0);
+        double v = line_max(rmax, i) * line_max(cmax, j) * root * corr[u];
+        if (spec.clamp) v = fmin(v, 1.0);
+        const int64_t o = (bi * m + row0 + i) * n + col0 + j;
+        C[o] = (T)v;
+        if (pstar) pstar[o] = (uint8_t)qs[u];
+    }
+    if (work) {
         // timed launch: 2 k flops per output entry of the tile and p visited,
-        // and the end (every wave has passed the last vote)
-        const int64_t rows = m - row0 < kSmTile ? m - row0 : kSmTile;
-        const int64_t cols = n - col0 < kSmTile ? n - col0 : kSmTile;
-        atomicAdd(work, (unsigned long long)(2 * rows * cols * k * visited));
-        timing_span_end(work);
+        // and the end
+        __syncthreads();
+        if (tid == 0) {
+            const int64_t rows = m - row0 < kSmTile ? m - row0 : kSmTile;
+            const int64_t cols = n - col0 < kSmTile ? n - col0 : kSmTile;
+            atomicAdd(work, (unsigned long long)(2 * rows * cols * k * visited));
+            timing_span_end(work);
+        }
     }
 }
 
 }  // namespace
 
-hipError_t launch_small_product_f64(const void* A, const void* B, int in_f64, int64_t b, int64_t m, int64_t k,
-                                    int64_t n, const SmallSpec& spec, void* C, int out_f64, uint8_t* pstar,
-                                    hipStream_t st) {
+bool small_product_fits(int64_t b, int64_t m, int64_t n) {
+    // a launch has fewer than 2^32 threads in x, at most 1024 per tile
+    return b <= 65535 && ((m + kSmTile - 1) / kSmTile) * ((n + kSmTile - 1) / kSmTile) < ((int64_t)1 << 22);
+}
+
+hipError_t launch_small_product_f64(const void* A, const void* B, int f64, int64_t b, int64_t m, int64_t k,
+                                    int64_t n, const SmallSpec& spec, void* C, uint8_t* pstar, hipStream_t st) {
     if (b <= 0 || m <= 0 || n <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((n + kSmTile - 1) / kSmTile), (unsigned)((m + kSmTile - 1) / kSmTile),
-                    (unsigned)b);
-    // the dynamic-LDS limit is a per-device attribute of each instance
-    static std::atomic<uint64_t> attr_set[4];
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    const uint64_t bit = 1ull << (dev & 63);
-    const int inst = (in_f64 ? 2 : 0) + (out_f64 ? 1 : 0);
-    if (!(attr_set[inst].load() & bit)) {
-        const void* fn = in_f64 ? (out_f64 ? (const void*)mt_small_product_f64_kernel<double, double>
-                                           : (const void*)mt_small_product_f64_kernel<double, float>)
-                                : (out_f64 ? (const void*)mt_small_product_f64_kernel<float, double>
-                                           : (const void*)mt_small_product_f64_kernel<float, float>);
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmLdsBytes);
-        if (e != hipSuccess) return e;
-        attr_set[inst].fetch_or(bit);
-    }
+    const dim3 grid((unsigned)(((m + kSmTile - 1) / kSmTile) * ((n + kSmTile - 1) / kSmTile)), (unsigned)b);
     timing_before("mt_small_product_f64", st);
     unsigned long long* work = timing_work_slot();
-#define MT_SMALL(TS, TO)                                                                             \
-    hipLaunchKernelGGL((mt_small_product_f64_kernel<TS, TO>), grid, dim3(kSmThreads), kSmLdsBytes, st,    \
-                       (const TS*)A, (const TS*)B, m, k, n, spec, (TO*)C, pstar, work)
-    if (in_f64) {
-        if (out_f64) MT_SMALL(double, double); else MT_SMALL(double, float);
+    // waves: one per 32 inner indices, up to 16 (512 indices in registers;
+    // longer inner dimensions go round in chunks of 512: fewer waves would
+    // only have fewer loads on their way)
+#define MT_SMALL(T, W)                                                                                         \
+    hipLaunchKernelGGL((mt_small_product_f64_kernel<T, W>), grid, dim3(64 * W), 0, st, (const T*)A, (const T*)B, \
+                       m, k, n, spec, (T*)C, pstar, work)
+#define MT_SMALL_K(T)                 \
+    if (k <= 32) MT_SMALL(T, 1);       \
+    else if (k <= 64) MT_SMALL(T, 2);  \
+    else if (k <= 128) MT_SMALL(T, 4); \
+    else if (k <= 256) MT_SMALL(T, 8); \
+    else MT_SMALL(T, 16)
+    if (f64) {
+        MT_SMALL_K(double);
     } else {
-        if (out_f64) MT_SMALL(float, double); else MT_SMALL(float, float);
+        MT_SMALL_K(float);
     }
+#undef MT_SMALL_K
 #undef MT_SMALL
     timing_after(st);
     return hipGetLastError();
