@@ -543,10 +543,13 @@ void product_fills(const Family& f, const Layout& L, uint8_t* ws, int32_t s0, bo
 // The product pipeline on already-validated arguments (and the workspace set
 // up by product_fills; pilot: uses_pilot).  X-mode (APSP):
 // A = B = X (n x n, r = c = 1 by construction), the output goes back to X.
+// sym (X-mode on the BF16 path, nullable): tells on the device whether X is
+// symmetric.
 mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64_t m, int64_t k,
                       int64_t n, const Family& f, const PlaneSpec& ps, const Geom& g,
                       const Layout& L, uint8_t* ws, bool scale, int mode, int clamp, void* out,
-                      int out_f64, uint8_t* pstar, hipStream_t st, bool pilot, bool fuse_rowmax = false) {
+                      int out_f64, uint8_t* pstar, hipStream_t st, bool pilot, bool fuse_rowmax = false,
+                      const int32_t* sym = nullptr) {
     double* r = scale ? (double*)(ws + L.r) : nullptr;
     double* c = scale ? (double*)(ws + L.c) : nullptr;
     void* ap = ws + L.ap;
@@ -659,6 +662,7 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
         epi.out = out;
         epi.out_f64 = out_f64;
         epi.pstar = pstar;
+        epi.sym = sym;
         if (defer) {
             epi.low_need = &hdr->low_need;
             epi.low_missed = &hdr->low_missed;
@@ -970,8 +974,18 @@ mt_status apsp_estimate(const float* W, int64_t n, double s_scale, int32_t n_squ
     uint8_t* ws = (uint8_t*)workspace;
     void* X = ws + L.x;
     int32_t* flag = (int32_t*)(ws + L.hdr);
-    MT_TRY(launch_fill_zero_u32(flag, 1, st), "clear domain flag");
+    WsHeader* hdr = (WsHeader*)flag;
+    // An undirected graph's X is symmetric, and stays so: half of the tiles.
+    // Where the 128-wide tiles of the whole matrix fit one per CU, half of
+    // them would take as long.
+    const int64_t t128 = (n + kBf16SmallBM - 1) / kBf16SmallBM;
+    const bool sym = f.bf16 && T > 0 && t128 * t128 > 256;
+    FillList start;
+    start.add(&hdr->domain_flag, 1);
+    if (sym) start.add(&hdr->sym, 1, 1u);
+    MT_TRY(launch_fills(start, st), "clear domain flag");
     MT_TRY(launch_apsp_transform(W, n, s_scale, X, x_f64, flag, st), "exp transform");
+    if (sym) MT_TRY(launch_symmetric((const float*)X, n, &hdr->sym, st), "symmetry of X");
     if (f.flags & MT_FLAG_VALIDATE) {
         if ((s = read_domain_flag(ws + L.hdr, st)) != MT_OK) return s;
     }
@@ -984,7 +998,7 @@ mt_status apsp_estimate(const float* W, int64_t n, double s_scale, int32_t n_squ
     for (int t = 0; t < T; ++t) {
         MT_TRY(launch_fills(fills, st), "clear product state");
         s = run_product(X, X, x_f64, 1, n, n, n, f, ps, g, L, ws, false, EPI_APSP_X, 1, X, x_f64,
-                        t == T - 1 ? p_star_last : nullptr, st, pilot);
+                        t == T - 1 ? p_star_last : nullptr, st, pilot, false, sym ? &hdr->sym : nullptr);
         if (s != MT_OK) return s;
     }
     MT_TRY(launch_apsp_to_dist(X, x_f64, n, s_scale, D, d_dtype == MT_F64,

@@ -637,6 +637,31 @@ __global__ __launch_bounds__(kThreads) void mt_apsp_transform_kernel(const float
     if (bad) atomicOr(flag, 1);
 }
 
+// Block = a pair of mirrored 64 x 64 blocks of X (block row bi >= block column
+// bj): one is read into LDS, the other compared with its transpose.  Bound by
+// one read of X.
+constexpr int kSymTile = 64;
+__global__ __launch_bounds__(kThreads) void mt_symmetric_kernel(const float* __restrict__ X, int64_t n,
+                                                               int32_t* __restrict__ sym) {
+    __shared__ float t[kSymTile][kSymTile + 1];
+    if (blockIdx.x > blockIdx.y) return;
+    const int64_t i0 = (int64_t)blockIdx.y * kSymTile, j0 = (int64_t)blockIdx.x * kSymTile;
+    const int c = threadIdx.x % kSymTile, r0 = threadIdx.x / kSymTile;
+    constexpr int kStep = kThreads / kSymTile;
+    float v[kSymTile / kStep];
+#pragma unroll
+    for (int u = 0; u < kSymTile / kStep; ++u) {
+        const int64_t r = r0 + u * kStep;
+        t[r][c] = j0 + r < n && i0 + c < n ? X[(j0 + r) * n + i0 + c] : 0.f;
+        v[u] = i0 + r < n && j0 + c < n ? X[(i0 + r) * n + j0 + c] : 0.f;
+    }
+    __syncthreads();
+    bool differ = false;
+#pragma unroll
+    for (int u = 0; u < kSymTile / kStep; ++u) differ |= !(v[u] == t[c][r0 + u * kStep]);
+    if (differ) *sym = 0;
+}
+
 // D = -log(X) / s in FP64; X = 0 -> +inf.
 // raw != 0: D = X (the (x, max) matrix itself, converted to D's type).
 template <typename TX, typename TD>
@@ -992,6 +1017,15 @@ hipError_t launch_rowmax_planes_colmax(const float* A, const float* B, int64_t b
         if (wave_row) MT_ROWPLANES(false, true); else MT_ROWPLANES(false, false);
     }
 #undef MT_ROWPLANES
+    timing_after(st);
+    return hipGetLastError();
+}
+
+hipError_t launch_symmetric(const float* X, int64_t n, int32_t* sym, hipStream_t st) {
+    const unsigned blocks = (unsigned)((n + kSymTile - 1) / kSymTile);
+    if (blocks > 65535) return hipErrorInvalidValue;
+    timing_before("mt_symmetric", st);
+    hipLaunchKernelGGL(mt_symmetric_kernel, dim3(blocks, blocks), dim3(kThreads), 0, st, X, n, sym);
     timing_after(st);
     return hipGetLastError();
 }

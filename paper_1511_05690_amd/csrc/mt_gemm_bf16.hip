@@ -129,6 +129,9 @@ struct TileCtx {
     int64_t row0, col0;
 };
 
+// The tiles a launch runs: every one, those on and above the diagonal, none.
+enum TileSet : int { kAllTiles, kUpperTiles, kNoTiles };
+
 // ------------------------------------------------------------ selection epilogue
 template <class C, int MODE, typename TO, bool R1, bool RERUN = false>
 struct SelectEpi {
@@ -154,6 +157,10 @@ struct SelectEpi {
     int64_t out_lane;
     int32_t rows_left, cols_left, diag_off;
     int32_t n_eval;  // plan entries whose planes this launch may read
+    // a tile off the diagonal of a symmetric X: outputs go to the mirrored
+    // place too, (row, col) of the tile's first entry
+    bool mirror;
+    int64_t mir_row, mir_col;
 
     // Row offset, from this lane's first row lr0, of accumulator element q
     // of sub-tile row i (the 32 x 32 MFMA layout: element q of lane l is row
@@ -169,6 +176,19 @@ struct SelectEpi {
     // end.
     __device__ int down_end(const FamilyPlan& plan) const { return min(plan.n, n_eval); }
     static __device__ bool skip_tile(const Args& a, int64_t tile) { return RERUN && a.missed_tile[tile] == 0u; }
+    // A symmetric X (a.sym): does this launch run the upper triangle's tiles
+    // alone, or no tile?
+    static __device__ TileSet tile_set(const Args& a) {
+        if (MODE != EPI_APSP_X || a.sym == nullptr) return kAllTiles;
+        const bool s = __builtin_amdgcn_readfirstlane(*a.sym) != 0;
+        if (a.sym_mode == kSymOnly) return s ? kUpperTiles : kNoTiles;
+        return !s ? kAllTiles : a.sym_mode == kSymLeave ? kNoTiles : kUpperTiles;
+    }
+    // A tile that no launch runs has handed nothing over (tile id of a block
+    // in row-major order).
+    static __device__ void leave_tile(const Args& a, int64_t tile) {
+        if (a.tile_count != nullptr) a.tile_count[tile] = 0u;
+    }
     // The tile's number of handed-over entries (0 first).
     __device__ void record_count(int64_t tile, uint32_t n) const {
         if (!RERUN && a.tile_count != nullptr) a.tile_count[tile] = n;
@@ -263,6 +283,9 @@ struct SelectEpi {
         lr0 = t.wm * WT_M * 32 + (t.lane >> 5) * 4;
         lc0 = t.wn * WT_N * 32 + (t.lane & 31);
         out_lane = ((int64_t)t.bi * m + t.row0 + lr0) * n + t.col0 + lc0;
+        mirror = MODE == EPI_APSP_X && t.row0 != t.col0 && tile_set(a) == kUpperTiles;
+        mir_row = t.row0;
+        mir_col = t.col0;
         rows_left = (int32_t)min<int64_t>(m - (t.row0 + lr0), 1 << 30);
         cols_left = (int32_t)min<int64_t>(n - (t.col0 + lc0), 1 << 30);
         diag_off = (int32_t)((t.col0 + lc0) - (t.row0 + lr0));
@@ -410,10 +433,20 @@ struct SelectEpi {
                     if (take) {
                         const int64_t o = (int64_t)roff * n + j * 32;
                         out[o] = w;
-                        if (ps) ps[o] = ((stab >> q) & 1u) ? pcode : (uint8_t)MT_PSTAR_NONE;
+                        if (ps) set_p(ps, roff, j, o, ((stab >> q) & 1u) ? pcode : (uint8_t)MT_PSTAR_NONE);
+                        if (MODE == EPI_APSP_X && mirror && !((park >> q) & 1u)) ((TO*)a.out)[mirrored(roff, j)] = w;
                     }
                 }
             }
+    }
+
+    // Where the mirrored entry of (roff, j) lies in `out` and `pstar`.
+    __device__ __forceinline__ int64_t mirrored(int roff, int j) const {
+        return (mir_col + lc0 + j * 32) * n + mir_row + lr0 + roff;
+    }
+    __device__ __forceinline__ void set_p(uint8_t* ps, int roff, int j, int64_t o, uint8_t code) {
+        ps[o] = code;
+        if (MODE == EPI_APSP_X && mirror) a.pstar[mirrored(roff, j)] = code;
     }
 
     // Final output of entry (roff, j) from its ring result S at a p with
@@ -425,6 +458,7 @@ struct SelectEpi {
         if (MODE == EPI_APSP_X || a.clamp) w = w < TO(1) ? w : TO(1);
         if (MODE == EPI_APSP_X && roff - j * 32 == diag_off) w = TO(1);
         out[o] = w;
+        if (MODE == EPI_APSP_X && mirror) ((TO*)a.out)[mirrored(roff, j)] = w;
     }
 
     // stage: a free pipeline buffer (C::NW staging tiles of STG floats).
@@ -464,7 +498,7 @@ struct SelectEpi {
                                   else
                                       put(out, roff, j, o, Sh, false, prev_inv_p, 1.f);
                               } else if (!(dec & mask) && (stable || last)) {
-                                  if (ps) ps[o] = stable ? pcode : (uint8_t)MT_PSTAR_NONE;
+                                  if (ps) set_p(ps, roff, j, o, stable ? pcode : (uint8_t)MT_PSTAR_NONE);
                                   if (stable && defer) {
                                       out[o] = (TO)S;
                                       pnd |= mask;
@@ -495,7 +529,7 @@ struct SelectEpi {
                 const bool stable = S >= tau_f;
                 const int64_t o = (int64_t)roff * n + j * 32;
                 if (stable) {
-                    if (ps) ps[o] = pcode;
+                    if (ps) set_p(ps, roff, j, o, pcode);
                     if (e > 0 && S >= rise_thr) {
                         out[o] = (TO)S;  // stable here too, and maybe above
                         return;
@@ -541,6 +575,8 @@ struct AdjointEpi {
     __device__ bool active(int e, const FamilyPlan& plan) const { return a.hist[plan.e[e].pidx] > 0; }
     __device__ int down_end(const FamilyPlan& plan) const { return plan.n; }
     static __device__ bool skip_tile(const Args&, int64_t) { return false; }
+    static __device__ TileSet tile_set(const Args&) { return kAllTiles; }
+    static __device__ void leave_tile(const Args&, int64_t) {}
     __device__ void record_tile(int64_t, bool) const {}
     __device__ void counts(int& open, int& parked) const { open = parked = 0; }
     __device__ int32_t start_index() const { return 0; }
@@ -710,16 +746,41 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
     int id = blockIdx.x;
     const int nwg = gridDim.x;
     if ((nwg & 7) == 0) id = (id & 7) * (nwg >> 3) + (id >> 3);
+    // A symmetric X's upper triangle: the same bands, each from its first
+    // row's diagonal tile on, spread evenly over the XCDs.
     const int per_batch = g.tiles_m * g.tiles_n;
-    t.bi = id / per_batch;
-    const int tt = id - t.bi * per_batch;
     constexpr int GROUP = 4;
-    const int group = tt / (GROUP * g.tiles_n);
-    const int first_m = group * GROUP;
-    const int gsz = min(GROUP, g.tiles_m - first_m);
-    const int in_g = tt - group * GROUP * g.tiles_n;
-    const int tm = first_m + in_g % gsz;
-    const int tn = in_g / gsz;
+    const TileSet tiles = Epi::tile_set(args);
+    int tm, tn;
+    if (tiles == kAllTiles) {
+        t.bi = id / per_batch;
+        const int tt = id - t.bi * per_batch;
+        const int group = tt / (GROUP * g.tiles_n);
+        const int first_m = group * GROUP;
+        const int gsz = min(GROUP, g.tiles_m - first_m);
+        const int in_g = tt - group * GROUP * g.tiles_n;
+        tm = first_m + in_g % gsz;
+        tn = in_g / gsz;
+    } else {
+        const int wm = (int)blockIdx.x / g.tiles_n, wn = (int)blockIdx.x % g.tiles_n;
+        if (tid == 0 && (tiles == kNoTiles || wn < wm)) Epi::leave_tile(args, blockIdx.x);
+        if (tiles == kNoTiles) return;
+        int total = 0;
+        for (int f = 0; f < g.tiles_m; f += GROUP) total += min(GROUP, g.tiles_m - f) * (g.tiles_n - f);
+        const int share = (total + 7) / 8, slot = (int)blockIdx.x >> 3;
+        int in_g = ((int)blockIdx.x & 7) * share + slot;
+        if (slot >= share || in_g >= total) return;
+        int first_m = 0, gsz = min(GROUP, g.tiles_m);
+        while (in_g >= gsz * (g.tiles_n - first_m)) {
+            in_g -= gsz * (g.tiles_n - first_m);
+            first_m += GROUP;
+            gsz = min(GROUP, g.tiles_m - first_m);
+        }
+        t.bi = 0;
+        tm = first_m + in_g % gsz;
+        tn = first_m + in_g / gsz;
+        if (tn < tm) return;
+    }
     t.row0 = (int64_t)tm * C::BM;
     t.col0 = (int64_t)tn * C::BN;
     const int64_t tile_id = (int64_t)t.bi * per_batch + (int64_t)tm * g.tiles_n + tn;
@@ -1478,6 +1539,7 @@ __global__ __launch_bounds__(256) void mt_tail_bf16_kernel(GemmGeom g, FamilyPla
     // for the rerun launch instead
     int n_eval = MT_MAX_P;
     if (a.low_need != nullptr && __builtin_amdgcn_readfirstlane(*a.low_need) == 0) n_eval = a.n_eval;
+    const bool upper = MODE == EPI_APSP_X && a.sym != nullptr && __builtin_amdgcn_readfirstlane(*a.sym) != 0;
     for (int64_t w = w0; w < w1;) {
         TailEntry te[G];
         te[0] = a.tail_sorted[w];
@@ -1505,13 +1567,26 @@ __global__ __launch_bounds__(256) void mt_tail_bf16_kernel(GemmGeom g, FamilyPla
             e_first[q] = t.e_next;
             Sh[q] = (live[q] && state != kTailOpen) ? (float)out[o[q]] : 0.f;
         }
+        // the mirrored place of entry q of a symmetric X (its own otherwise)
+        auto mirrored = [&](int q) {
+            return MODE == EPI_APSP_X && upper && te[q].i / a.sym_bm != te[q].j / a.sym_bm
+                       ? (int64_t)te[q].j * g.cols + te[q].i
+                       : o[q];
+        };
+        auto set_p = [&](int q, uint8_t code) {
+            a.pstar[o[q]] = code;
+            if (MODE == EPI_APSP_X && upper) a.pstar[mirrored(q)] = code;
+        };
         // final value of entry q: the scales, clamp and APSP diagonal
         auto put = [&](int q, float v) {
             const ScaleSplit c_j = split_scale(a.c ? a.c[(int64_t)te[q].bi * g.cols + te[q].j] : 1.0);
             TO w = scale_out<TO>(v * r_i.m * c_j.m, r_i.e + c_j.e);
             if (MODE == EPI_APSP_X || a.clamp) w = w < TO(1) ? w : TO(1);
             if (MODE == EPI_APSP_X && te[q].i == te[q].j) w = TO(1);
-            if (lane == 0) out[o[q]] = w;
+            if (lane == 0) {
+                out[o[q]] = w;
+                if (MODE == EPI_APSP_X && upper) out[mirrored(q)] = w;
+            }
             live[q] = false;
         };
         if (!R1 && state == kTailRise) {
@@ -1548,7 +1623,7 @@ __global__ __launch_bounds__(256) void mt_tail_bf16_kernel(GemmGeom g, FamilyPla
                 for (int q = 0; q < G; ++q) {
                     if (!act[q]) continue;
                     const bool stable = S[q] >= tau_f;
-                    if (stable && lane == 0 && a.pstar) a.pstar[o[q]] = (uint8_t)pe.pidx;
+                    if (stable && lane == 0 && a.pstar) set_p(q, (uint8_t)pe.pidx);
                     if (stable && e > 0 && S[q] >= pe.rise_thr_f) {
                         if (!paired) {
                             Sh[q] = S[q];
@@ -1558,7 +1633,7 @@ __global__ __launch_bounds__(256) void mt_tail_bf16_kernel(GemmGeom g, FamilyPla
                         // the doubled p, plan entry e - 1, from the squared terms
                         const PlanEntry& pu = plan.e[e - 1];
                         const bool stable_u = S2[q] >= tau_f;
-                        if (stable_u && lane == 0 && a.pstar) a.pstar[o[q]] = (uint8_t)pu.pidx;
+                        if (stable_u && lane == 0 && a.pstar) set_p(q, (uint8_t)pu.pidx);
                         if (stable_u && e - 1 > 0 && S2[q] >= pu.rise_thr_f) {
                             Sh[q] = S2[q];
                             nxt[q] = e - 2;
@@ -1622,7 +1697,7 @@ __global__ __launch_bounds__(256) void mt_tail_bf16_kernel(GemmGeom g, FamilyPla
                     }
                     const bool stable = S[q] >= tau_f;
                     if (!(stable || e == plan.n - 1)) continue;
-                    if (lane == 0 && a.pstar) a.pstar[o[q]] = stable ? (uint8_t)pe.pidx : (uint8_t)MT_PSTAR_NONE;
+                    if (lane == 0 && a.pstar) set_p(q, stable ? (uint8_t)pe.pidx : (uint8_t)MT_PSTAR_NONE);
                     if (R1 && stable && pe.inv_dp > 0.f) {
                         Sh[q] = S[q];
                         pend[q] = true;
@@ -1717,6 +1792,48 @@ GemmGeom make_geom(const uint16_t* X, const uint16_t* Y, int64_t rows, int64_t c
     return g;
 }
 
+// APSP's squaring (X in FP32, one batch item).  Where X is symmetric, on and
+// above the diagonal only: with the launch's own tiles, or in a launch beside
+// it with 128-wide tiles where those of the triangle fit two per CU and the
+// whole matrix' do not.  Undirected geometric graphs, r = 1, whole call: n =
+// 3500 16.5 ms on 196 tiles of 256 x 256, 12.5 on 406 of 128 x 128 (the same
+// tiles' triangle is one round of 105 either way); n = 4500 49.2 -> 24.0 (171
+// tiles of 256 x 256 instead of 324), n = 6000 95 -> 57, n = 2500 (210 of 400
+// tiles of 128 x 128) 8.1 -> 7.7.  A directed graph pays the look at X (12 us
+// once at n = 3500) and, with the launch beside, 5 us per squaring.
+constexpr int64_t kSymSmallTiles = 512;
+
+template <bool R1>
+hipError_t launch_apsp_gemm(const GemmGeom& g, const FamilyPlan& plan, const EpiArgs& epi, bool deep, int64_t cap,
+                            hipStream_t st) {
+    const char* name = "mt_pfamily_gemm_bf16";
+    EpiArgs a = epi;
+    const int64_t t128 = (int64_t)g.tiles_m * (g.bm / kBf16SmallBM);
+    const bool beside = epi.sym != nullptr && g.bm == kBf16BM && t128 * (t128 + 1) / 2 <= kSymSmallTiles;
+    a.sym_mode = beside ? kSymLeave : kSymUpper;
+    a.sym_bm = beside ? kBf16SmallBM : g.bm;
+    hipError_t e =
+        g.bm == kBf16BM ? launch_gemm<FwdCfg, SelectEpi<FwdCfg, EPI_APSP_X, float, R1>>(g, 1, plan, a, name, st)
+        : deep ? launch_gemm<FwdDeepCfg, SelectEpi<FwdDeepCfg, EPI_APSP_X, float, R1>>(g, 1, plan, a, name, st)
+               : launch_gemm<FwdSmallCfg, SelectEpi<FwdSmallCfg, EPI_APSP_X, float, R1>>(g, 1, plan, a, name, st);
+    if (e == hipSuccess && beside) {
+        // its entries go straight to the list the tail runs: the sort, whose
+        // tiles have handed over nothing, leaves them there
+        EpiArgs s = a;
+        s.sym_mode = kSymOnly;
+        s.tail = epi.tail_sorted;
+        s.tile_count = nullptr;
+        s.tail_max = epi.tail_max / 4;
+        GemmGeom gs = g;
+        gs.tiles_m = gs.tiles_n = (int32_t)t128;
+        gs.bm = kBf16SmallBM;
+        e = launch_gemm<FwdSmallCfg, SelectEpi<FwdSmallCfg, EPI_APSP_X, float, R1>>(gs, 1, plan, s,
+                                                                                "mt_triangle_gemm_bf16", st);
+    }
+    if (e == hipSuccess && epi.tail) e = launch_tail<EPI_APSP_X, float, R1>(g, 1, plan, a, cap, st);
+    return e;
+}
+
 }  // namespace
 
 hipError_t launch_pfamily_gemm_bf16(const uint16_t* Ap, const uint16_t* Bp, int64_t b, int64_t m,
@@ -1743,7 +1860,9 @@ hipError_t launch_pfamily_gemm_bf16(const uint16_t* Ap, const uint16_t* Bp, int6
 #define MT_SEL2(MODE, TO) \
     if (plan.r1) MT_SEL(MODE, TO, true) else MT_SEL(MODE, TO, false)
     if (epi.mode == EPI_APSP_X) {
-        if (epi.out_f64) MT_SEL2(EPI_APSP_X, double) else MT_SEL2(EPI_APSP_X, float)
+        if (epi.out_f64) return hipErrorInvalidValue;  // this path keeps X in FP32
+        if (plan.r1) return launch_apsp_gemm<true>(g, plan, epi, deep, cap, st);
+        return launch_apsp_gemm<false>(g, plan, epi, deep, cap, st);
     }
     if (epi.low_need != nullptr) {
         // deferred planes (plain products, no r = 1 projection)

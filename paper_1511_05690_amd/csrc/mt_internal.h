@@ -38,7 +38,8 @@ struct WsHeader {
     int32_t start;       // plan index the forward's p search starts at
     int32_t low_missed;  // deferred planes: some tile or tail entry reached them unwritten
     int32_t low_need;    // deferred planes: the pilot saw sampled entries that need them
-    int32_t pad[3];
+    int32_t sym;         // APSP: X equals its transpose
+    int32_t pad[2];
     int32_t hist[MT_MAX_P + 1];
 };
 
@@ -124,6 +125,18 @@ struct EpiArgs {
     int32_t* low_missed;
     uint32_t* missed_tile;  // b x tiles_m x tiles_n: 1 where the tile must run again
     int32_t n_eval;         // plan entries whose planes are always written
+    // APSP on the BF16 path: *sym tells (on the device) whether X is symmetric,
+    // as the X of an undirected graph is.  Then only the tiles on and above the
+    // diagonal run, and every output is written to its mirrored place too
+    // (outside the diagonal tiles of sym_bm rows, which run whole).
+    const int32_t* sym;  // nullable
+    int32_t sym_mode;
+    int32_t sym_bm;
+};
+enum SymMode : int32_t {
+    kSymUpper,  // every tile, or where X is symmetric those of the upper triangle
+    kSymLeave,  // every tile, or none where X is symmetric (another launch runs them)
+    kSymOnly,   // that launch: the upper triangle, none where X is not symmetric
 };
 
 // Adjoint epilogue: out = sum over the p that some entry uses of
@@ -228,6 +241,8 @@ hipError_t launch_colmax(const void* B, int f64, int64_t b, int64_t k, int64_t n
 // Inner-index balancing factors d = sqrt(b / a) (1 where a or b is 0) and 1 / d.
 hipError_t launch_balance(const double* a, const double* b, int64_t count, double* d, double* dinv,
                           hipStream_t st);
+// *sym (1 before) = 0 where some X_ij differs from X_ji.
+hipError_t launch_symmetric(const float* X, int64_t n, int32_t* sym, hipStream_t st);
 hipError_t launch_apsp_transform(const float* W, int64_t n, double s, void* X, int x_f64,
                                  int32_t* flag, hipStream_t st);
 hipError_t launch_apsp_to_dist(const void* X, int x_f64, int64_t n, double s, void* D,
