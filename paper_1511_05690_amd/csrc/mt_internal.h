@@ -209,6 +209,7 @@ struct PilotArgs {
 // plan entry, the last if none); stop[s][u]: waiting at start s and decided
 // at plan entry u < s on the way up.
 struct PilotCounts {
+    int32_t blocks;  // that have added theirs
     int32_t es_hist[MT_MAX_P];
     int32_t stop[MT_MAX_P][MT_MAX_P];
 };

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(64) void pilot_mfma_bf16_kernel(PilotArgs pa, Famil
     const int ko = (lane >> 5) * 8;
     f32x16 acc = f32x16{};
     const bf16x8 zero = bf16x8{};
-    constexpr int U = 4;
+    constexpr int U = 8;
     int64_t k = k_lo;
     auto ld = [&](const uint16_t* p, bool ok, int64_t kk) { return ok ? *(const bf16x8*)(p + kk + ko) : zero; };
     for (; k + (U - 1) * 16 < k_hi; k += U * 16) {
@@ -234,96 +234,26 @@ __global__ __launch_bounds__(64) void pilot_mfma_bf16_kernel(PilotArgs pa, Famil
     }
 }
 
-// One thread per sampled entry: its S_e (the K parts summed in order), its
-// e* (first stable plan entry; the smallest p if none) and, for every start
-// s where it would wait, the plan entry u where it is decided on the way up.
-// Histograms of e* and of (s, u) per wave (ballots), then per block (LDS)
-// and over the grid (global atomics): integer counts, so the choice does not
-// depend on the order of the atomics.
-template <bool F64>
-__global__ __launch_bounds__(kPilotThreads) void pilot_count_kernel(PilotArgs pa, FamilyPlan plan) {
-    using T = typename std::conditional<F64, double, float>::type;
-    __shared__ PilotCounts sc;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int n = plan.n;
-    for (int i = tid; i < (int)(sizeof(PilotCounts) / 4); i += kPilotThreads) ((int32_t*)&sc)[i] = 0;
-    __syncthreads();
-    const T tau = F64 ? (T)plan.tau : (T)plan.tau_f;
-    const int q = blockIdx.x * kPilotThreads + tid;
-    const bool in = q < pa.nr * pa.nc;
-    const int r = in ? q / pa.nc : 0, c = in ? q % pa.nc : 0;
-    T S[MT_MAX_P];
-    int es = n - 1;
-#pragma unroll
-    for (int e = MT_MAX_P - 1; e >= 0; --e) {
-        T v = 0;
-        if (e < pa.n_eval && in) {
-            T pv[kMaxPilotKParts];
-#pragma unroll
-            for (int kp = 0; kp < kMaxPilotKParts; ++kp)
-                pv[kp] = kp < pa.kparts ? ((const T*)pa.part)[((int64_t)kp * n + e) * kMaxPilotSide * kMaxPilotSide +
-                                                             r * kMaxPilotSide + c]
-                                        : (T)0;
-#pragma unroll
-            for (int kp = 0; kp < kMaxPilotKParts; ++kp) v += pv[kp];
-            if (v >= tau) es = e;
-        }
-        S[e] = v;
-    }
-    for (int e = 0; e < n; ++e) {
-        const int cnt = __popcll(__ballot(in && es == e));
-        if (lane == 0 && cnt) atomicAdd(&sc.es_hist[e], cnt);
-    }
-#pragma unroll
-    for (int s = 1; s < MT_MAX_P; ++s) {
-        if (s >= n) break;
-        const T thr = F64 ? (T)plan.e[s].rise_thr : (T)plan.e[s].rise_thr_f;
-        const bool parked = in && S[s] >= tau && S[s] >= thr;
-        int u = s - 1;  // decided at plan entry u going up
-        bool up = parked;
-#pragma unroll
-        for (int uu = MT_MAX_P - 2; uu > 0; --uu) {
-            if (uu >= s) continue;
-            const T tu = F64 ? (T)plan.e[uu].rise_thr : (T)plan.e[uu].rise_thr_f;
-            if (up && S[uu] >= tau && S[uu] >= tu) u = uu - 1;
-            else up = false;
-        }
-        for (int v = 0; v < s; ++v) {
-            const int cnt = __popcll(__ballot(parked && u == v));
-            if (lane == 0 && cnt) atomicAdd(&sc.stop[s][v], cnt);
-        }
-    }
-    __syncthreads();
-    PilotCounts* gc = (PilotCounts*)pa.counts;
-    for (int i = tid; i < (int)(sizeof(PilotCounts) / 4); i += kPilotThreads) {
-        const int32_t v = ((int32_t*)&sc)[i];
-        if (v) atomicAdd(&((int32_t*)gc)[i], v);
-    }
-}
-
 // The cost model on the counts, one lane per start s.  Costs are in dense
 // tile-entry units (one plain p of the family over one tile; a split p
 // counts 3) plus kappa per tail dot product (a split p's dot reads four
 // plane rows and counts 2).
 template <bool F64>
-__global__ __launch_bounds__(64) void pilot_choose_kernel(PilotArgs pa, FamilyPlan plan, int32_t* start) {
+__device__ void choose_start(const PilotArgs& pa, const FamilyPlan& plan, const PilotCounts& sc, int32_t* start) {
     __shared__ float cost[MT_MAX_P];
-    __shared__ PilotCounts sc;
     __shared__ float Wc[MT_MAX_P], Wd[MT_MAX_P];
-    for (int i = threadIdx.x; i < (int)(sizeof(PilotCounts) / 4); i += 64)
-        ((int32_t*)&sc)[i] = ((const int32_t*)pa.counts)[i];
     const int n = plan.n;
-    if (threadIdx.x == 0) {
+    const int s = threadIdx.x;
+    if (s < n) Wd[s] = !F64 && plan.e[s].nseg == 3 ? 3.f : 1.f;
+    __syncthreads();
+    if (s == 0) {
         float w = 0.f;
         for (int e = 0; e < n; ++e) {
-            const bool sp = !F64 && plan.e[e].nseg == 3;
-            w += sp ? 2.f : 1.f;
+            w += Wd[e] > 1.f ? 2.f : 1.f;
             Wc[e] = w;
-            Wd[e] = sp ? 3.f : 1.f;
         }
     }
     __syncthreads();
-    const int s = threadIdx.x;
     // W(e): dot weight of plan entries 0 .. e; wdense(e): dense cost of entry e
     auto W = [&](int e) { return Wc[e]; };
     auto wdense = [&](int e) { return Wd[e]; };
@@ -349,7 +279,7 @@ __global__ __launch_bounds__(64) void pilot_choose_kernel(PilotArgs pa, FamilyPl
             // one runs the next p densely.  (Taken as none, half of the 8192^2
             // log-normal products started at p = 16, where 0.03 % of the
             // entries need p = 4: its three products for every tile and a way
-            // up, 6 dense products and 5.85 ms per call against 3 and MEAS.)
+            // up, 6 dense products and 5.85 ms per call against 3 and 4.0.)
             float open = 0.f, odots = 0.f;
             if (d < n - 1) {
                 open = 0.5f;
@@ -405,6 +335,90 @@ __global__ __launch_bounds__(64) void pilot_choose_kernel(PilotArgs pa, FamilyPl
     }
 }
 
+// One thread per sampled entry: its S_e (the K parts summed in order), its
+// e* (first stable plan entry; the smallest p if none) and, for every start
+// s where it would wait, the plan entry u where it is decided on the way up.
+// Histograms of e* and of (s, u) per wave (ballots), then per block (LDS)
+// and over the grid (global atomics): integer counts, so the choice does not
+// depend on the order of the atomics.  The block that adds its counts last
+// makes the choice.  Latency alone (16 blocks): with the S of an entry in
+// registers and every loop unrolled to MT_MAX_P the code did not fit the
+// instruction cache, and the choice was a launch of its own: 25 + 13 us at
+// 8192^2 (BF16), 17 now; 24 + 11 -> 15 at 2048^2 (FP64).
+template <bool F64>
+__global__ __launch_bounds__(kPilotThreads) void pilot_count_kernel(PilotArgs pa, FamilyPlan plan, int32_t* start) {
+    using T = typename std::conditional<F64, double, float>::type;
+    __shared__ PilotCounts sc;
+    __shared__ bool last;
+    __shared__ T thr[MT_MAX_P];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int n = plan.n;
+    for (int i = tid; i < (int)(sizeof(PilotCounts) / 4); i += kPilotThreads) ((int32_t*)&sc)[i] = 0;
+    if (tid < n) thr[tid] = F64 ? (T)plan.e[tid].rise_thr : (T)plan.e[tid].rise_thr_f;
+    __syncthreads();
+    const T tau = F64 ? (T)plan.tau : (T)plan.tau_f;
+    const int q = blockIdx.x * kPilotThreads + tid;
+    const bool in = q < pa.nr * pa.nc;
+    const int r = in ? q / pa.nc : 0, c = in ? q % pa.nc : 0;
+    const T* part = (const T*)pa.part + r * kMaxPilotSide + c;
+    int es = n - 1;
+    uint32_t rises = 0;  // plan entries where this one, stable, may be stable above too
+    // the next entry's parts are loaded before this one's are added
+    T pv[2][kMaxPilotKParts];
+    auto load = [&](T (&to)[kMaxPilotKParts], int e) {
+#pragma unroll
+        for (int kp = 0; kp < kMaxPilotKParts; ++kp)
+            to[kp] = part[((int64_t)min(kp, pa.kparts - 1) * n + e) * kMaxPilotSide * kMaxPilotSide];
+    };
+    auto look = [&](const T (&from)[kMaxPilotKParts], int e) {
+        T v = 0;
+#pragma unroll
+        for (int kp = 0; kp < kMaxPilotKParts; ++kp) v += kp < pa.kparts ? from[kp] : (T)0;
+        if (in && v >= tau) {
+            es = e;
+            if (v >= thr[e]) rises |= 1u << e;
+        }
+    };
+    load(pv[0], pa.n_eval - 1);
+    for (int e = pa.n_eval - 1; e >= 0; e -= 2) {
+        if (e >= 1) load(pv[1], e - 1);
+        look(pv[0], e);
+        if (e < 1) break;
+        if (e >= 2) load(pv[0], e - 2);
+        look(pv[1], e - 1);
+    }
+    for (int e = 0; e < n; ++e) {
+        const int cnt = __popcll(__ballot(in && es == e));
+        if (lane == 0 && cnt) atomicAdd(&sc.es_hist[e], cnt);
+    }
+    for (int s = 1; s < n; ++s) {
+        const bool parked = (rises >> s) & 1u;
+        if (__ballot(parked) == 0) continue;
+        // going up it is decided at the first entry it does not rise from (or 0)
+        const int u = 31 - __clz((int)((~rises | 1u) & ((1u << s) - 1u)));
+        for (int v = 0; v < s; ++v) {
+            const int cnt = __popcll(__ballot(parked && u == v));
+            if (lane == 0 && cnt) atomicAdd(&sc.stop[s][v], cnt);
+        }
+    }
+    __syncthreads();
+    PilotCounts* gc = (PilotCounts*)pa.counts;
+    for (int i = tid; i < (int)(sizeof(PilotCounts) / 4); i += kPilotThreads) {
+        const int32_t v = ((int32_t*)&sc)[i];
+        if (v) atomicAdd(&((int32_t*)gc)[i], v);
+    }
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) last = atomicAdd(&gc->blocks, 1) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    for (int i = tid; i < (int)(sizeof(PilotCounts) / 4); i += kPilotThreads)
+        ((int32_t*)&sc)[i] = __hip_atomic_load((int32_t*)gc + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    choose_start<F64>(pa, plan, sc, start);
+}
+
 }  // namespace
 
 hipError_t launch_choose_start(const PilotArgs& pa, const FamilyPlan& plan, int32_t* start, int f64,
@@ -424,12 +438,10 @@ hipError_t launch_choose_start(const PilotArgs& pa, const FamilyPlan& plan, int3
     timing_before("mt_pilot", st);
     if (f64) {
         hipLaunchKernelGGL(pilot_kernel<true>, grid, dim3(kPilotThreads), 0, st, pa, plan);
-        hipLaunchKernelGGL(pilot_count_kernel<true>, cgrid, dim3(kPilotThreads), 0, st, pa, plan);
-        hipLaunchKernelGGL(pilot_choose_kernel<true>, dim3(1), dim3(64), 0, st, pa, plan, start);
+        hipLaunchKernelGGL(pilot_count_kernel<true>, cgrid, dim3(kPilotThreads), 0, st, pa, plan, start);
     } else {
         hipLaunchKernelGGL(pilot_mfma_bf16_kernel, dim3(4, (unsigned)pa.n_eval, (unsigned)pa.kparts), dim3(64), 0, st, pa, plan);
-        hipLaunchKernelGGL(pilot_count_kernel<false>, cgrid, dim3(kPilotThreads), 0, st, pa, plan);
-        hipLaunchKernelGGL(pilot_choose_kernel<false>, dim3(1), dim3(64), 0, st, pa, plan, start);
+        hipLaunchKernelGGL(pilot_count_kernel<false>, cgrid, dim3(kPilotThreads), 0, st, pa, plan, start);
     }
     timing_after(st);
     return hipGetLastError();
