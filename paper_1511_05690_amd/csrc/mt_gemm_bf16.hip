@@ -23,10 +23,12 @@
 //
 // Tiling: 512 threads = 8 waves (two per SIMD, so one wave's barrier and LDS
 // waits overlap the other's MFMAs) in 2 x 4; each wave owns WT_M x WT_N MFMA
-// tiles of 32 x 32 (v_mfma_f32_32x32x16_bf16).  The operand tiles of a step
-// are copied global -> LDS by the direct-to-LDS loads
-// (global_load_lds_dwordx4), double buffered, so the next step's loads fly
-// while the current step's MFMAs run.  Every step moves the same bytes:
+// tiles of 32 x 32 (v_mfma_f32_32x32x16_bf16): 256 x 256 tiles, or 128 x 128
+// for products that have too few of those.  The operand tiles of a step are
+// copied global -> LDS by the direct-to-LDS loads (global_load_lds_dwordx4)
+// into two buffers (two or four with 128 x 128 tiles), so the next steps'
+// loads fly while the current step's MFMAs run.  Every step moves the same
+// bytes:
 //   plain p: X and Y tiles, K step 64, 128-byte LDS rows, 16-byte chunk
 //            index XOR-swizzled with (row >> 1) & 7;
 //   split p: X hi, X lo, Y hi, Y lo tiles, K step 32, 64-byte LDS rows,
@@ -45,8 +47,6 @@ namespace mt {
 namespace {
 
 __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
-
-
 
 // A row or column scale as mantissa x 2^exp, mantissa in [0.5, 1) (0 for a
 // zero scale).  The epilogues multiply the FP32 mantissas with the root and
