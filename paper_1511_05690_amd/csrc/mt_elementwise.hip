@@ -360,6 +360,19 @@ __device__ __forceinline__ void power_planes_block(const TS* __restrict__ src, i
     const int64_t u0 = bx * PT::U;  // plane column
     const TS* s = src + bi * rows * cols;
 
+    // Scales by plane column (the backward's power planes): the reciprocals
+    // of the tile's columns once, 0 where one would not be normal.  A division
+    // per element made the passes VALU-bound: 64 x 512^3, one power, hi and lo,
+    // 70 us for the untransposed operand, now 35.
+    __shared__ double col_scale[PT::U], col_inv[PT::U];
+    if (scale_cols != nullptr) {
+        for (int i = threadIdx.x; i < PT::U; i += kThreads) {
+            const double d = u0 + i < cols ? scale_cols[bi * cols + u0 + i] : 0.0;
+            col_scale[i] = d;
+            col_inv[i] = d >= DBL_MIN && d <= 1.0 / DBL_MIN ? 1.0 / d : 0.0;
+        }
+        if (!kTranspose) __syncthreads();
+    }
     if (kTranspose) {
         // src[u][t]: read U (u) x T (t) coalesced along t.
         for (int e = threadIdx.x; e < PT::T * PT::U; e += kThreads) {
@@ -373,6 +386,23 @@ __device__ __forceinline__ void power_planes_block(const TS* __restrict__ src, i
     typedef typename std::conditional<kBf16, float, double>::type TC;
     const int64_t plane_elems = rows_pad * cols_pad;
     const uint32_t mask = plane_mask(spec);
+    // 8 consecutive source values of plane row t inside the operand
+    // (untransposed: 16-byte aligned)
+    auto load_chunk = [&](int64_t t, int tt, int64_t u, int ch, TS (&v)[8]) {
+        if (kTranspose) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = tile[tt][ch * 8 + i];
+        } else {
+            typedef TS vec4 __attribute__((ext_vector_type(4)));
+            const vec4 a0 = *(const vec4*)(s + t * cols + u);
+            const vec4 a1 = *(const vec4*)(s + t * cols + u + 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = a0[i];
+                v[4 + i] = a1[i];
+            }
+        }
+    };
     for (int rep = 0; rep < PT::TASKS / kThreads; ++rep) {
         const int task = threadIdx.x + rep * kThreads;
         const int tt = task / PT::CHUNKS, ch = task % PT::CHUNKS;
@@ -383,26 +413,26 @@ __device__ __forceinline__ void power_planes_block(const TS* __restrict__ src, i
         double sc = 1.0;
         if (scale_rows != nullptr && t < rows) sc = scale_rows[bi * rows + t];
         const bool zero_row = (t >= rows) || (sc == 0.0);
-        if (scale_cols == nullptr && !zero_row && sc >= DBL_MIN && u + 8 <= cols &&
-            (kTranspose || (cols & 3) == 0)) {
+        const bool whole = !zero_row && u + 8 <= cols && (kTranspose || (cols & 3) == 0);
+        if (scale_cols != nullptr && scale_rows == nullptr && col_mul == nullptr && whole) {
+            TS v[8];
+            load_chunk(t, tt, u, ch, v);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const double d = col_scale[ch * 8 + i], inv = col_inv[ch * 8 + i], a = (double)v[i];
+                // the quotient from the reciprocal and its remainder
+                const double q = a * inv;
+                double w = fma(fma(-q, d, a), inv, q);
+                if (__builtin_expect(!(inv > 0.0), 0)) w = d > 0.0 ? a / d : 0.0;
+                x[i] = (TC)w;
+            }
+        } else if (scale_cols == nullptr && sc >= DBL_MIN && whole) {
             // whole chunk inside the row and (untransposed) 16-byte aligned:
             // vector loads and one reciprocal per row instead of 8 divisions
             // (the scaled value may differ from src / scale by one FP64 ulp;
             // a subnormal scale, whose reciprocal overflows, divides below)
             TS v[8];
-            if (kTranspose) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = tile[tt][ch * 8 + i];
-            } else {
-                typedef TS vec4 __attribute__((ext_vector_type(4)));
-                const vec4 a0 = *(const vec4*)(s + t * cols + u);
-                const vec4 a1 = *(const vec4*)(s + t * cols + u + 4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    v[i] = a0[i];
-                    v[4 + i] = a1[i];
-                }
-            }
+            load_chunk(t, tt, u, ch, v);
             const double inv = sc > 0.0 ? 1.0 / sc : 0.0;
             if (col_mul != nullptr) {
                 // balanced input: (src d_u) / scale_rows, the product first
