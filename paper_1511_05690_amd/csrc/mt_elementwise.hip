@@ -285,7 +285,7 @@ __device__ __forceinline__ void write_power_chunk(const TC (&x)[8], const PlaneS
                                                   int64_t pos) {
     TC pw[8];
     int prev = 0;
-    for (int q = 0; (mask >> q) != 0u; ++q) {
+    each_power(mask, [&](int q, bool wanted) {
         const int p = spec.p[q];
         if (prev > 0 && p == 2 * prev) {
 #pragma unroll
@@ -297,10 +297,7 @@ __device__ __forceinline__ void write_power_chunk(const TC (&x)[8], const PlaneS
         prev = p;
         // powers whose planes are not wanted are still formed: the next
         // power may square them
-        if (!((mask >> q) & 1u)) {
-            if (q == 31) break;
-            continue;
-        }
+        if (!wanted) return;
         const int64_t pl = spec.first_plane[q];
         const int64_t off = (bi * spec.n_planes + pl) * plane_elems + pos;
         if (kBf16) {
@@ -328,7 +325,7 @@ __device__ __forceinline__ void write_power_chunk(const TC (&x)[8], const PlaneS
                 *(double2*)(base + off + i) = v2;
             }
         }
-    }
+    });
 }
 
 // A workgroup covers PlaneTile::T plane rows x PlaneTile::U plane columns:

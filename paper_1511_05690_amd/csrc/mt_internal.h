@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "maxtimes.h"
+#include "mt_masks.h"
 
 namespace mt {
 
@@ -274,7 +275,7 @@ __device__ __forceinline__ uint32_t plane_mask(const PlaneSpec& spec) {
     if (spec.use != nullptr)
         for (int q = 0; q < spec.n_p; ++q)
             if (spec.use[q] <= 0) mask &= ~(1u << q);
-    return spec.n_p < 32 ? mask & ((1u << spec.n_p) - 1u) : mask;
+    return mask & family_bits(spec.n_p);
 }
 // Row maxima r of a row-major FP32 operand A (b x rows x cols) and its power
 // planes in one pass, the same values as launch_rowmax followed by
