@@ -31,8 +31,10 @@ __device__ inline float bf16_to_float(uint16_t h) { return __uint_as_float(((uin
 // (l holds what the product h rounded off), so that the result is good to
 // about one rounding whatever e: at e = 63 some 60 FP64 operations, where
 // exp(-e log x), whose error grows as |e log x| 2^-53, took about 200.
-// Beyond the FP64 range the result is infinite, as exp's was.
+// Beyond the FP64 range the power is infinite, and it is 0 at an infinite x
+// (an entry of C that overflowed its type); an infinite g stays infinite.
 __device__ inline double times_pow_neg(double g, double x, int e) {
+    if (!(x <= DBL_MAX)) return e > 0 ? g * 0.0 : g;
     double xh = 1.0 / x;
     double xl = fma(-x, xh, 1.0) * xh;
     double yh = 1.0, yl = 0.0;
@@ -49,6 +51,7 @@ __device__ inline double times_pow_neg(double g, double x, int e) {
         xh = h;
     }
     if (!(yh <= DBL_MAX)) return g * HUGE_VAL;
+    if (!(fabs(g) <= DBL_MAX)) return g * yh;
     return fma(g, yh, g * yl);
 }
 
