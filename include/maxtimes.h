@@ -492,11 +492,12 @@ mt_status maxtimes_timing_span(const char* prefix, double* total_ms, int64_t* la
  * entry that goes up from p to 2p (both without the hi/lo split) takes S_2p
  * from the same dot product, each term squared, so its 2p terms are rounded
  * as squares of BF16 p-th powers instead of BF16 2p-th powers.  0 disables it; the
- * default is 512 (per 256 x 256 outputs on the BF16 path, in proportion for its
- * smaller tiles).  The workspace sizes grow by 32 bytes x max_entries per
- * output tile (the list and its copy sorted by row), so query them after
- * changing the threshold (a workspace sized before is reported too small).  Process-wide; not synchronised with calls
- * in flight on other threads.
+ * default is 512.  A 128 x 128 tile of the BF16 path takes a quarter of it
+ * (of a value other than the default at least 256, or all of it).  The workspace sizes grow by
+ * 16 bytes x max_entries per output tile (32 where the list is sorted by row:
+ * planes of one power above 32 MiB), so query them after changing the threshold
+ * (a workspace sized before is reported too small).  Process-wide; not
+ * synchronised with calls in flight on other threads.
  */
 mt_status maxtimes_set_tail_threshold(int32_t max_entries);
 int32_t maxtimes_tail_threshold(void);

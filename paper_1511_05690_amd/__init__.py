@@ -560,7 +560,9 @@ def timing_read(prefix):
 
 def set_tail_threshold(max_entries):
     """A forward tile with at most ``max_entries`` undecided entries hands
-    them to the sparse-tail kernel (0: never).  Process-wide."""
+    them to the sparse-tail kernel (0: never; the default is 512).  A 128-wide
+    BF16 tile takes a quarter (of a value other than the default at least
+    256, or all of it).  Process-wide."""
     _check(load_library().maxtimes_set_tail_threshold(int(max_entries)))
 
 

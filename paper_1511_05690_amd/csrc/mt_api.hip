@@ -5,6 +5,7 @@
 // mt_elementwise.hip, mt_gemm_bf16.hip, mt_gemm_f64.hip and mt_backward.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -355,21 +356,38 @@ Geom product_geom(const Family& f, int64_t b, int64_t m, int64_t k, int64_t n) {
 struct Layout {
     size_t hdr, r, c, bal, ap, bp, s, s2, code, tail, tail_sorted, tile_count, pilot, missed, x, total;
     int32_t tail_max;  // sparse-tail threshold the layout was sized for (0: no tail)
+    bool tail_sort;    // the tail's list is sorted by row
 };
 
 // A tile with at most this many undecided entries hands them to the sparse
 // tail (0 disables it).  512 of a 256 x 256 BF16 tile is 0.8 %.
-// Unless the caller sets a threshold, which holds for any tile, a smaller
-// BF16 tile takes its share of the 512 (kTailUnset).
-constexpr int32_t kTailDefault = 512, kTailUnset = -1;
-std::atomic<int32_t> g_tail_max{kTailUnset};
-// The threshold of a tile of side bm: a tail dot product costs about as much
-// as 1 / 250 of a dense tile entry at 256 x 256 BF16 outputs, so the share
-// goes with the tile's area.
+constexpr int32_t kTailDefault = 512;
+std::atomic<int32_t> g_tail_max{kTailDefault};
+// The threshold of a tile of side bm, at most its entries.  A 128 x 128 tile of
+// the BF16 path takes a quarter of a 256 x 256 one's, the share of its area: a
+// tail dot product costs about as much as 1 / 250 of a dense entry of the
+// larger tile, and the smaller one's dense p costs a quarter (the default's
+// 512 per 128-wide tile against 128: 700 x 3000 x 900 log-normal 233 and 211
+// us, 4 x 300 x 500 x 300 103 and 92, a 2000-vertex APSP 3.67 and 3.50 ms,
+// other shapes even).  Of a threshold that is not the default it takes up to
+// 256 whole, so that a small one still holds for a whole tile; a larger one's
+// list is no longer than that of 256-wide tiles.
 int32_t tail_threshold_of(bool bf16, int bm) {
     const int32_t v = g_tail_max.load();
-    if (v != kTailUnset) return v;
-    return bf16 ? kTailDefault / ((kBf16BM / bm) * (kBf16BM / bm)) : kTailDefault;
+    if (!bf16 || bm == kBf16BM) return std::min(v, bm * bm);
+    return v == kTailDefault ? v / 4 : std::min(v, std::max(256, v / 4));
+}
+
+// The tail's list is sorted by row where one power's planes of both operands
+// exceed this: entries of a row then share the loads of its plane row.
+// Smaller planes stay in the caches whatever the order, and the sort's launch
+// (5 us and more) costs more than the sharing gives.
+constexpr int64_t kTailSortBytes = (int64_t)32 << 20;
+
+bool sorts_tail(const Geom& g, int32_t tail_max, int64_t b) {
+    // (a tile's place in the list is a 32-bit index)
+    return tail_max > 0 && b * (g.mp + g.np) * g.kp * (int64_t)g.esize > kTailSortBytes &&
+           b * (g.mp / g.bm) * (g.np / g.bm) * tail_max <= (int64_t)0xffffffff;
 }
 // Products with b m k n up to this many multiply-adds take the one-kernel
 // FP64 path (mt_small.hip) when their options allow it; 0: never.
@@ -413,15 +431,21 @@ Layout product_layout(const Family& f, const PlaneSpec& ps, const Geom& g, int64
     // has a single p: nothing would be left to run; none for the r = 2
     // projection, which keeps every ring result)
     L.tail_max = f.n > 1 && !r2 ? tail_threshold_of(f.bf16, g.bm) : 0;
+    L.tail_sort = sorts_tail(g, L.tail_max, b);
     const int64_t tiles = b * (g.mp / g.bm) * (g.np / g.bm);
-    const size_t list_bytes = align_up((size_t)tiles * (size_t)L.tail_max * sizeof(TailEntry));
+    const int64_t handed = tiles * L.tail_max;
+    // APSP: the smaller tiles of the launch beside hand theirs to the list
+    // the tail runs
+    int64_t run = handed;
+    if (x_bytes > 0 && f.bf16 && L.tail_max > 0)
+        run = std::max(run, triangle_beside(g.bm, g.mp / g.bm) * tail_threshold_of(true, kBf16SmallBM));
     L.tail = off;
-    off += list_bytes;
-    // the list with the entries of a row together, and each tile's count
-    L.tail_sorted = off;
-    off += L.tail_max > 0 ? list_bytes : 0;
+    off += align_up((size_t)(L.tail_sort ? handed : run) * sizeof(TailEntry));
+    // sorted: the list with the entries of a row together, and each tile's count
+    L.tail_sorted = L.tail_sort ? off : L.tail;
+    off += L.tail_sort ? align_up((size_t)run * sizeof(TailEntry)) : 0;
     L.tile_count = off;
-    off += L.tail_max > 0 ? align_up((size_t)tiles * 4) : 0;
+    off += L.tail_sort ? align_up((size_t)tiles * 4) : 0;
     // pilot partial sums (float on the BF16 path, double on FP64)
     L.pilot = off;
     off += f.n > 1 ? align_up((size_t)kPilotKParts * f.n * kMaxPilotSide * kMaxPilotSide * (f.bf16 ? 4 : 8)) +
@@ -515,18 +539,6 @@ bool uses_pilot(const Family& f, const Layout& L, int32_t s0, int64_t b, int64_t
 
 size_t pilot_part_bytes(const Family& f) {
     return align_up((size_t)kPilotKParts * f.n * kMaxPilotSide * kMaxPilotSide * (f.bf16 ? 4 : 8));
-}
-
-// The tail's list is sorted by row where one power's planes of both operands
-// exceed this: entries of a row then share the loads of its plane row.
-// Smaller planes stay in the caches whatever the order, and the sort's launch
-// (5 us and more) costs more than the sharing gives.
-constexpr int64_t kTailSortBytes = (int64_t)32 << 20;
-
-bool sorts_tail(const Geom& g, const Layout& L, int64_t b) {
-    // (a tile's place in the list is a 32-bit index)
-    return b * (g.mp + g.np) * g.kp * (int64_t)g.esize > kTailSortBytes &&
-           b * (g.mp / g.bm) * (g.np / g.bm) * L.tail_max <= (int64_t)0xffffffff;
 }
 
 // What run_product's kernels expect set in the workspace before them: the
@@ -655,9 +667,9 @@ mt_status run_product(const void* A, const void* B, int in_f64, int64_t b, int64
         epi.tail = (TailEntry*)(ws + L.tail);
         epi.tail_count = &hdr->tail_count;
         epi.tail_max = L.tail_max;
-        const bool sorted = sorts_tail(g, L, b);
-        epi.tail_sorted = sorted ? (TailEntry*)(ws + L.tail_sorted) : epi.tail;
-        epi.tile_count = sorted ? (uint32_t*)(ws + L.tile_count) : nullptr;
+        epi.tail_max_beside = f.bf16 ? tail_threshold_of(true, kBf16SmallBM) : 0;
+        epi.tail_sorted = (TailEntry*)(ws + L.tail_sorted);
+        epi.tile_count = L.tail_sort ? (uint32_t*)(ws + L.tile_count) : nullptr;
     }
     if (f.bf16) {
         epi.mode = mode;
@@ -1476,10 +1488,7 @@ mt_status maxtimes_set_tail_threshold(int32_t max_entries) {
     return MT_OK;
 }
 
-int32_t maxtimes_tail_threshold(void) {
-    const int32_t v = g_tail_max.load();
-    return v == kTailUnset ? kTailDefault : v;
-}
+int32_t maxtimes_tail_threshold(void) { return g_tail_max.load(); }
 
 mt_status maxtimes_set_search_start(int32_t entry) {
     g_last_error.clear();

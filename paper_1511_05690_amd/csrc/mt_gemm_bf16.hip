@@ -1794,22 +1794,14 @@ GemmGeom make_geom(const uint16_t* X, const uint16_t* Y, int64_t rows, int64_t c
 
 // APSP's squaring (X in FP32, one batch item).  Where X is symmetric, on and
 // above the diagonal only: with the launch's own tiles, or in a launch beside
-// it with 128-wide tiles where those of the triangle fit two per CU and the
-// whole matrix' do not.  Undirected geometric graphs, r = 1, whole call: n =
-// 3500 16.5 ms on 196 tiles of 256 x 256, 12.5 on 406 of 128 x 128 (the same
-// tiles' triangle is one round of 105 either way); n = 4500 49.2 -> 24.0 (171
-// tiles of 256 x 256 instead of 324), n = 6000 95 -> 57, n = 2500 (210 of 400
-// tiles of 128 x 128) 8.1 -> 7.7.  A directed graph pays the look at X (12 us
-// once at n = 3500) and, with the launch beside, 5 us per squaring.
-constexpr int64_t kSymSmallTiles = 512;
-
+// it (triangle_beside).  A directed graph pays the look at X (12 us once at n =
+// 3500) and, with the launch beside, 5 us per squaring.
 template <bool R1>
 hipError_t launch_apsp_gemm(const GemmGeom& g, const FamilyPlan& plan, const EpiArgs& epi, bool deep, int64_t cap,
                             hipStream_t st) {
     const char* name = "mt_pfamily_gemm_bf16";
     EpiArgs a = epi;
-    const int64_t t128 = (int64_t)g.tiles_m * (g.bm / kBf16SmallBM);
-    const bool beside = epi.sym != nullptr && g.bm == kBf16BM && t128 * (t128 + 1) / 2 <= kSymSmallTiles;
+    const bool beside = epi.sym != nullptr && triangle_beside(g.bm, g.tiles_m) > 0;
     a.sym_mode = beside ? kSymLeave : kSymUpper;
     a.sym_bm = beside ? kBf16SmallBM : g.bm;
     hipError_t e =
@@ -1823,9 +1815,9 @@ hipError_t launch_apsp_gemm(const GemmGeom& g, const FamilyPlan& plan, const Epi
         s.sym_mode = kSymOnly;
         s.tail = epi.tail_sorted;
         s.tile_count = nullptr;
-        s.tail_max = epi.tail_max / 4;
+        s.tail_max = epi.tail_max_beside;
         GemmGeom gs = g;
-        gs.tiles_m = gs.tiles_n = (int32_t)t128;
+        gs.tiles_m = gs.tiles_n = g.tiles_m * (kBf16BM / kBf16SmallBM);
         gs.bm = kBf16SmallBM;
         e = launch_gemm<FwdSmallCfg, SelectEpi<FwdSmallCfg, EPI_APSP_X, float, R1>>(gs, 1, plan, s,
                                                                                 "mt_triangle_gemm_bf16", st);

@@ -105,6 +105,7 @@ struct EpiArgs {
     TailEntry* tail;     // nullable: sparse-tail list (capacity tail_max per tile)
     uint32_t* tail_count;
     int32_t tail_max;    // a tile with 1..tail_max undecided entries hands them over
+    int32_t tail_max_beside;  // the same for the 128-wide tiles of APSP's launch beside
     const int32_t* start;  // nullable: plan index the p search starts at (0: largest p)
     // With tile_count (one word per output tile) each tile hands over into its
     // own tail_max slots of `tail` and writes its count there; the tail sort
@@ -134,6 +135,19 @@ struct EpiArgs {
     int32_t sym_mode;
     int32_t sym_bm;
 };
+// The 128-wide tiles of the launch beside (kSymOnly) that runs a symmetric X's
+// upper triangle in place of tiles_m rows of tiles of side bm; 0: those tiles
+// run it themselves.  The launch beside is for 256-wide tiles whose triangle
+// in 128-wide ones fits two per CU.  Undirected geometric graphs, r = 1, whole
+// call: n = 3500 16.5 ms on 196 tiles of 256 x 256, 12.5 on 406 of 128 x 128
+// (the same tiles' triangle is one round of 105 either way); n = 4500 49.2 ->
+// 24.0 (171 tiles of 256 x 256 instead of 324), n = 6000 95 -> 57, n = 2500
+// (210 of 400 tiles of 128 x 128) 8.1 -> 7.7.
+constexpr int64_t kSymSmallTiles = 512;
+inline int64_t triangle_beside(int bm, int64_t tiles_m) {
+    const int64_t t128 = tiles_m * (bm / kBf16SmallBM), tri = t128 * (t128 + 1) / 2;
+    return bm == kBf16BM && tri <= kSymSmallTiles ? tri : 0;
+}
 enum SymMode : int32_t {
     kSymUpper,  // every tile, or where X is symmetric those of the upper triangle
     kSymLeave,  // every tile, or none where X is symmetric (another launch runs them)
