@@ -157,8 +157,8 @@ struct SelectEpi {
     int64_t out_lane;
     int32_t rows_left, cols_left, diag_off;
     int32_t n_eval;  // plan entries whose planes this launch may read
-    // a tile off the diagonal of a symmetric X: outputs go to the mirrored
-    // place too, (row, col) of the tile's first entry
+    // a symmetric X: outputs go to the mirrored place too, (row, col) of the
+    // tile's first entry
     bool mirror;
     int64_t mir_row, mir_col;
 
@@ -283,14 +283,18 @@ struct SelectEpi {
         lr0 = t.wm * WT_M * 32 + (t.lane >> 5) * 4;
         lc0 = t.wn * WT_N * 32 + (t.lane & 31);
         out_lane = ((int64_t)t.bi * m + t.row0 + lr0) * n + t.col0 + lc0;
-        mirror = MODE == EPI_APSP_X && t.row0 != t.col0 && tile_set(a) == kUpperTiles;
+        mirror = MODE == EPI_APSP_X && tile_set(a) == kUpperTiles;
         mir_row = t.row0;
         mir_col = t.col0;
         rows_left = (int32_t)min<int64_t>(m - (t.row0 + lr0), 1 << 30);
         cols_left = (int32_t)min<int64_t>(n - (t.col0 + lc0), 1 << 30);
         diag_off = (int32_t)((t.col0 + lc0) - (t.row0 + lr0));
         // Entries outside the matrix count as decided from the start, so a
-        // tile whose every entry is decided can be skipped as a whole.
+        // tile whose every entry is decided can be skipped as a whole; of a
+        // symmetric X's diagonal tile so do those below the diagonal, which
+        // are mirrored from above it (a split p sums its cross terms in
+        // another order there, and X would not stay its own transpose).
+        const bool half = mirror && t.row0 == t.col0;
 #pragma unroll
         for (int i = 0; i < NDEC; ++i) decided[i] = pending[i] = 0u;
 #pragma unroll
@@ -301,7 +305,8 @@ struct SelectEpi {
                 uint32_t bits = 0u;
 #pragma unroll
                 for (int q = 0; q < 16; ++q)
-                    if (!(j * 32 < cols_left && roff_of(i, q) < rows_left)) bits |= 1u << q;
+                    if (!(j * 32 < cols_left && roff_of(i, q) < rows_left) || (half && roff_of(i, q) - j * 32 > diag_off))
+                        bits |= 1u << q;
                 decided[tix >> 1] |= bits << ((tix & 1) * 16);
             }
     }
@@ -1569,9 +1574,7 @@ __global__ __launch_bounds__(256) void mt_tail_bf16_kernel(GemmGeom g, FamilyPla
         }
         // the mirrored place of entry q of a symmetric X (its own otherwise)
         auto mirrored = [&](int q) {
-            return MODE == EPI_APSP_X && upper && te[q].i / a.sym_bm != te[q].j / a.sym_bm
-                       ? (int64_t)te[q].j * g.cols + te[q].i
-                       : o[q];
+            return MODE == EPI_APSP_X && upper ? (int64_t)te[q].j * g.cols + te[q].i : o[q];
         };
         auto set_p = [&](int q, uint8_t code) {
             a.pstar[o[q]] = code;
@@ -1803,7 +1806,6 @@ hipError_t launch_apsp_gemm(const GemmGeom& g, const FamilyPlan& plan, const Epi
     EpiArgs a = epi;
     const bool beside = epi.sym != nullptr && triangle_beside(g.bm, g.tiles_m) > 0;
     a.sym_mode = beside ? kSymLeave : kSymUpper;
-    a.sym_bm = beside ? kBf16SmallBM : g.bm;
     hipError_t e =
         g.bm == kBf16BM ? launch_gemm<FwdCfg, SelectEpi<FwdCfg, EPI_APSP_X, float, R1>>(g, 1, plan, a, name, st)
         : deep ? launch_gemm<FwdDeepCfg, SelectEpi<FwdDeepCfg, EPI_APSP_X, float, R1>>(g, 1, plan, a, name, st)

@@ -129,11 +129,10 @@ struct EpiArgs {
     int32_t n_eval;         // plan entries whose planes are always written
     // APSP on the BF16 path: *sym tells (on the device) whether X is symmetric,
     // as the X of an undirected graph is.  Then only the tiles on and above the
-    // diagonal run, and every output is written to its mirrored place too
-    // (outside the diagonal tiles of sym_bm rows, which run whole).
+    // diagonal run, and every output on and above it is written to its mirrored
+    // place too, so that X stays its own transpose to the last bit.
     const int32_t* sym;  // nullable
     int32_t sym_mode;
-    int32_t sym_bm;
 };
 // The 128-wide tiles of the launch beside (kSymOnly) that runs a symmetric X's
 // upper triangle in place of tiles_m rows of tiles of side bm; 0: those tiles
