@@ -374,9 +374,11 @@ mt_status apsp_affine_correct(void* D, mt_dtype dtype, int64_t n, const int32_t*
  * a global buffer in the workspace, several p at a time, largest first; a
  * pair whose indices are all decided is left out of the p after.  Larger
  * lengths and b >= 2^31 return MT_ERR_UNSUPPORTED.  n = 0, m = 0 or b = 0:
- * empty output, nothing written.  Asynchronous on the stream.  Workspace from maxconv_workspace_size (0 bytes up to 4096; above,
- * about 16 s N + 9 (n + m - 1) bytes per pair, N the transform length, s >= 2
- * the p at a time, at most |P| and as many as fit in 64 MiB).
+ * empty output, nothing written.  Asynchronous on the stream.  Workspace from
+ * maxconv_workspace_size (0 bytes up to 4096; above, about 16 s N + 9 (n + m - 1)
+ * bytes per pair, N the transform length, s >= 2 the p at a time, at most |P|
+ * and as many as fit in 64 MiB).  One sized for any other family serves too
+ * (with fewer p at a time where it is smaller): the least is that of one p.
  */
 mt_status maxconv_workspace_size(int64_t b, int64_t n, int64_t m, const mt_options* opt, size_t* bytes);
 mt_status maxconv_estimate(const void* x, const void* y, mt_dtype dtype, int64_t b, int64_t n, int64_t m,

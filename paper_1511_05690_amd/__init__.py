@@ -429,13 +429,15 @@ def maxconv(x, y, P=(1, 2, 4, 8, 16, 32, 64), tau=None, return_pstar=False, work
     o = _options(P, "fp64", tau, None, 0)
     need = ctypes.c_size_t(0)
     _check(lib.maxconv_workspace_size(b, n, m, ctypes.byref(o), ctypes.byref(need)))
-    ws = _workspace(need.value, x.device, workspace) if need.value else None
+    # (a given workspace may be smaller: one sized for another family serves)
+    given = workspace is not None and need.value > 0
+    ws = workspace if given else torch.empty(need.value, dtype=torch.uint8, device=x.device)
     L = n + m - 1 if n and m else 0
     shape = (b, L) if batched else (L,)
     z = torch.empty(shape, dtype=x.dtype, device=x.device)
     ps = torch.empty(shape, dtype=torch.uint8, device=x.device) if return_pstar else None
     _check(lib.maxconv_estimate(_ptr(x), _ptr(y), _dtype_code(x), b, n, m, ctypes.byref(o), _ptr(z), _ptr(ps),
-                                _ptr(ws), need.value, _stream(x.device)))
+                                _ptr(ws), ws.numel() * ws.element_size(), _stream(x.device)))
     return (z, ps) if return_pstar else z
 
 

@@ -1224,9 +1224,17 @@ struct MaxconvLayout {
     size_t tw, rxy, inv, open_at, s_sel, code, buf, total;
     int slots;
 };
-// The buffer holds `slots` p of the whole batch: as many as fit in 64 MiB, at
+constexpr int kMaxconvMinSlots = 2;
+// The p of the whole batch that the buffer holds: as many as fit in 64 MiB, at
 // least 2, the family cut into chunks of even size.
-MaxconvLayout maxconv_layout(int64_t b, int64_t n, int64_t m, int n_p) {
+int maxconv_slots(int64_t b, int64_t n, int64_t m, int n_p) {
+    const int64_t N = (int64_t)1 << maxconv_log_size(n, m);
+    const int64_t fit = ((int64_t)64 << 20) / (b * N * 16);
+    const int64_t most = fit < kMaxconvMinSlots ? kMaxconvMinSlots : fit < n_p ? fit : n_p;
+    const int chunks = (int)((n_p + most - 1) / most);
+    return std::max(kMaxconvMinSlots, (n_p + chunks - 1) / chunks);
+}
+MaxconvLayout maxconv_layout(int64_t b, int64_t n, int64_t m, int slots) {
     MaxconvLayout L{};
     const int64_t len = n + m - 1;
     if (len <= kMaxConvN) return L;
@@ -1244,10 +1252,7 @@ MaxconvLayout maxconv_layout(int64_t b, int64_t n, int64_t m, int n_p) {
     off += (size_t)round_up(b * len * 8, kAlign);
     L.code = off;
     off += (size_t)round_up(b * len, kAlign);
-    const int64_t fit = ((int64_t)64 << 20) / (b * N * 16);
-    const int64_t most = fit < 2 ? 2 : fit < n_p ? fit : n_p;
-    const int chunks = (int)((n_p + most - 1) / most);
-    L.slots = chunks < 2 ? (n_p < 2 ? 2 : n_p) : (n_p + chunks - 1) / chunks;
+    L.slots = slots;
     L.buf = off;
     off += (size_t)round_up(L.slots * b * N * 16, kAlign);
     L.total = off;
@@ -1275,7 +1280,7 @@ mt_status maxconv_workspace_size(int64_t b, int64_t n, int64_t m, const mt_optio
     Family f;
     mt_status s = maxconv_check(b, n, m, opt, &f);
     if (s != MT_OK) return s;
-    *bytes = (b == 0 || n == 0 || m == 0) ? 0 : maxconv_layout(b, n, m, f.n).total;
+    *bytes = (b == 0 || n == 0 || m == 0) ? 0 : maxconv_layout(b, n, m, maxconv_slots(b, n, m, f.n)).total;
     return MT_OK;
 }
 
@@ -1289,7 +1294,11 @@ mt_status maxconv_estimate(const void* x, const void* y, mt_dtype dtype, int64_t
     if (dtype != MT_F32 && dtype != MT_F64) return fail(MT_ERR_INVALID_ARG, "unknown dtype %d", (int)dtype);
     if (b == 0 || n == 0 || m == 0) return MT_OK;
     if (!x || !y || !z) return fail(MT_ERR_INVALID_ARG, "x, y or z is NULL");
-    const MaxconvLayout L = maxconv_layout(b, n, m, f.n);
+    // A workspace sized for another family may hold fewer p at a time than
+    // this one would take: any that holds the fewest serves.
+    int slots = maxconv_slots(b, n, m, f.n);
+    while (slots > kMaxconvMinSlots && maxconv_layout(b, n, m, slots).total > ws_bytes) --slots;
+    const MaxconvLayout L = maxconv_layout(b, n, m, slots);
     s = check_ws(workspace, ws_bytes, L.total);
     if (s != MT_OK) return s;
     MaxconvSpec spec{};
