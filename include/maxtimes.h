@@ -170,7 +170,8 @@ typedef struct {
     uint32_t flags;          /* MT_FLAG_* */
 } mt_options;
 
-/* Workspace bytes needed by maxtimes_estimate for these sizes and options. */
+/* Workspace bytes needed by maxtimes_estimate for these sizes and options (on
+ * the BF16 path MT_FLAG_PROJECT_R1 does not change them, here and for APSP). */
 mt_status maxtimes_workspace_size(int64_t b, int64_t m, int64_t k, int64_t n,
                                   const mt_options* opt, size_t* bytes);
 

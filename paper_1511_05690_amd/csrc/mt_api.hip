@@ -460,6 +460,17 @@ Layout product_layout(const Family& f, const PlaneSpec& ps, const Geom& g, int64
     return L;
 }
 
+// What the caller provides: one size for the plain estimate and the r = 1
+// projection on the BF16 path, whose tiles may differ (the pilot steers only
+// the plain one), so that a workspace sized for either serves both.
+size_t product_bytes(const Family& f, const PlaneSpec& ps, int64_t b, int64_t m, int64_t k, int64_t n,
+                     size_t x_bytes) {
+    Family other = f;
+    if (f.bf16) other.flags ^= MT_FLAG_PROJECT_R1;
+    return std::max(product_layout(f, ps, product_geom(f, b, m, k, n), b, m, k, n, x_bytes).total,
+                    product_layout(other, ps, product_geom(other, b, m, k, n), b, m, k, n, x_bytes).total);
+}
+
 mt_status check_dims(int64_t b, int64_t m, int64_t k, int64_t n) {
     if (b < 0 || m < 0 || k < 0 || n < 0)
         return fail(MT_ERR_INVALID_ARG, "negative size (b=%lld m=%lld k=%lld n=%lld)", (long long)b,
@@ -761,9 +772,7 @@ mt_status maxtimes_workspace_size(int64_t b, int64_t m, int64_t k, int64_t n, co
     if (s != MT_OK) return s;
     if ((s = check_dims(b, m, k, n)) != MT_OK) return s;
     if ((s = check_bf16_inner(f, k)) != MT_OK) return s;
-    const PlaneSpec ps = plane_spec(f);
-    const Geom g = product_geom(f, b, m, k, n);
-    *bytes = product_layout(f, ps, g, b, m, k, n, 0).total;
+    *bytes = product_bytes(f, plane_spec(f), b, m, k, n, 0);
     return MT_OK;
 }
 
@@ -848,16 +857,17 @@ mt_status estimate_impl(const void* A, const void* B, mt_dtype dtype, int64_t b,
     const PlaneSpec ps = plane_spec(f);
     const Geom g = product_geom(f, b, m, k, n);
     const Layout L = product_layout(f, ps, g, b, m, k, n, 0);
+    const size_t need = product_bytes(f, ps, b, m, k, n, 0);
     if (use_scratch) {
-        if (L.total > kScratchBytes)
+        if (need > kScratchBytes)
             return fail(MT_ERR_WORKSPACE,
                         "this product needs %zu bytes of workspace; the static scratch of "
                         "maxtimes_estimate_noalloc holds %zu (call maxtimes_estimate with a workspace)",
-                        L.total, kScratchBytes);
+                        need, kScratchBytes);
         if ((s = scratch_of_current_device(&workspace)) != MT_OK) return s;
         ws_bytes = kScratchBytes;
     }
-    if ((s = check_ws(workspace, ws_bytes, L.total)) != MT_OK) return s;
+    if ((s = check_ws(workspace, ws_bytes, need)) != MT_OK) return s;
 
     hipStream_t st = (hipStream_t)stream;
     uint8_t* ws = (uint8_t*)workspace;
@@ -950,9 +960,7 @@ mt_status apsp_workspace_size(int64_t n, const mt_options* opt, size_t* bytes) {
     if ((s = check_dims(1, n, n, n)) != MT_OK) return s;
     if ((s = check_bf16_inner(f, n)) != MT_OK) return s;
     if (f.flags & MT_FLAG_BALANCE) return fail(MT_ERR_INVALID_ARG, "MT_FLAG_BALANCE is for maxtimes_estimate");
-    const PlaneSpec ps = plane_spec(f);
-    const Geom g = product_geom(f, 1, n, n, n);
-    *bytes = product_layout(f, ps, g, 1, n, n, n, (size_t)(n * n) * (f.bf16 ? 4 : 8)).total;
+    *bytes = product_bytes(f, plane_spec(f), 1, n, n, n, (size_t)(n * n) * (f.bf16 ? 4 : 8));
     return MT_OK;
 }
 
@@ -982,8 +990,9 @@ mt_status apsp_estimate(const float* W, int64_t n, double s_scale, int32_t n_squ
     const PlaneSpec ps = plane_spec(f);
     const Geom g = product_geom(f, 1, n, n, n);
     const int x_f64 = f.bf16 ? 0 : 1;
-    const Layout L = product_layout(f, ps, g, 1, n, n, n, (size_t)(n * n) * (x_f64 ? 8 : 4));
-    if ((s = check_ws(workspace, ws_bytes, L.total)) != MT_OK) return s;
+    const size_t x_bytes = (size_t)(n * n) * (x_f64 ? 8 : 4);
+    const Layout L = product_layout(f, ps, g, 1, n, n, n, x_bytes);
+    if ((s = check_ws(workspace, ws_bytes, product_bytes(f, ps, 1, n, n, n, x_bytes))) != MT_OK) return s;
 
     hipStream_t st = (hipStream_t)stream;
     uint8_t* ws = (uint8_t*)workspace;
