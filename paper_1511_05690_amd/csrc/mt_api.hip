@@ -335,10 +335,12 @@ Geom product_geom(const Family& f, int64_t b, int64_t m, int64_t k, int64_t n) {
         // against one round of 256-wide tiles on half the CUs or fewer), and
         // wherever the padding to 256 would be most of the tile.  Products it
         // steers are large or batched, and their tiles' share of the search
-        // is planned in 256-wide tiles.
+        // is planned in 256-wide tiles.  (A launch holds fewer than 2^32
+        // threads, 512 a tile.)
         const int64_t tiles128 = b * ((m + 127) / 128) * ((n + 127) / 128);
         const bool pilot_size = !(f.flags & (MT_FLAG_PROJECT_R1 | MT_FLAG_PROJECT_R2)) && b * m * n >= kPilotMinOutputs;
-        g.bm = !pilot_size && (tiles128 <= 512 || m <= 128 || n <= 128) ? kBf16SmallBM : kBf16BM;
+        const bool small = tiles128 <= 512 || ((m <= 128 || n <= 128) && tiles128 < ((int64_t)1 << 23));
+        g.bm = !pilot_size && small ? kBf16SmallBM : kBf16BM;
         g.kp = round_up(k, kBf16BK);
         g.esize = 2;
     } else {
