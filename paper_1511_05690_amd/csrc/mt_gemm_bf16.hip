@@ -294,7 +294,7 @@ struct SelectEpi {
         // symmetric X's diagonal tile so do those below the diagonal, which
         // are mirrored from above it (a split p sums its cross terms in
         // another order there, and X would not stay its own transpose).
-        const bool half = mirror && t.row0 == t.col0;
+        const int32_t below = mirror && t.row0 == t.col0 ? diag_off : 1 << 30;
 #pragma unroll
         for (int i = 0; i < NDEC; ++i) decided[i] = pending[i] = 0u;
 #pragma unroll
@@ -305,8 +305,7 @@ struct SelectEpi {
                 uint32_t bits = 0u;
 #pragma unroll
                 for (int q = 0; q < 16; ++q)
-                    if (!(j * 32 < cols_left && roff_of(i, q) < rows_left) || (half && roff_of(i, q) - j * 32 > diag_off))
-                        bits |= 1u << q;
+                    if (!(j * 32 < cols_left && roff_of(i, q) < min(rows_left, below + j * 32 + 1))) bits |= 1u << q;
                 decided[tix >> 1] |= bits << ((tix & 1) * 16);
             }
     }
