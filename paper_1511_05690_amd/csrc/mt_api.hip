@@ -483,10 +483,8 @@ mt_status check_dims(int64_t b, int64_t m, int64_t k, int64_t n) {
     return MT_OK;
 }
 
-// The BF16 GEMM addresses a 256-row block of a plane with 32-bit byte
-// offsets: the inner (contracted) dimension stays at or below 2^23.
 mt_status check_bf16_inner(const Family& f, int64_t inner) {
-    if (f.bf16 && inner > ((int64_t)1 << 23))
+    if (f.bf16 && inner > kBf16MaxInner)
         return fail(MT_ERR_UNSUPPORTED, "the BF16 path contracts at most 2^23 terms per entry (got %lld)",
                     (long long)inner);
     return MT_OK;

@@ -813,7 +813,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
     // holding logical chunk (l%4) ^ ((row >> 2) & 3) = (l%4) ^ ((l >> 4) & 3).
     // As byte offsets from the plane row block of the step (X and Y load the
     // same row pattern: GA == GB, SA == SB), 32-bit so that each load is a
-    // uniform base plus one VGPR (kp < 2^22 keeps them in range).
+    // uniform base plus one VGPR (kp <= kBf16MaxInner keeps them in range).
     static_assert(C::GA == C::GB && C::SA == C::SB, "X and Y share the load offsets");
     const uint32_t kpb = (uint32_t)g.kp * 2u;
     const uint32_t ld_even = (lane >> 3) * kpb + (((lane & 7) ^ (lane >> 4)) * 16);
@@ -908,7 +908,8 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
     //
     // More stages: a step begins with a wait that leaves the loads of the
     // later steps in flight and a barrier (which also ends the reads of the
-    // buffer that is refilled next), then issues the loads of STAGES - 1
+    // buffer that is refilled next: the wait is for them too), then issues the
+    // loads of STAGES - 1
     // steps ahead.  __syncthreads would wait for every load (its fence), so
     // these barriers are bare; the memory clobbers keep the LDS reads on
     // their side.
@@ -943,9 +944,9 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
     auto step_begin = [&]() {
         if constexpr (S > 2) {
             if (ahead >= S - 1)
-                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * C::LOADS) : "memory");
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * C::LOADS) : "memory");
             else
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         }
@@ -984,9 +985,9 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
     // the epilogue may stage through its buffer.
     //
     // Load instructions i0 .. i1 - 1 of the step at the cursor into buffer b.
-    // (The step's offset is added to the lane's 32-bit offset, below 256 rows
-    // x 2^24 bytes: a uniform base plus one VGPR per load also where the loop
-    // body is all the compiler sees.)
+    // (The step's offset is added to the lane's 32-bit offset, the sum below
+    // 256 rows x 2 kp <= 2^32 bytes: a uniform base plus one VGPR per load also
+    // where the loop body is all the compiler sees.)
     auto issue_plain = [&](int b, int i0, int i1) {
         uint8_t* la = smem + b * C::BUF_BYTES;
         uint8_t* lb = la + C::A_BYTES;
@@ -1346,7 +1347,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINW) void mt_pfamily_gemm_bf16_kern
         // the buffer the last step read (every wave: the barrier) is free
         // until the next step's loads, which wait for the barrier below
         if (S > 2) {
-            asm volatile("" ::: "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         }

@@ -26,6 +26,10 @@ typedef __attribute__((address_space(1))) const void glb_cvoid;
 constexpr int kBf16BM = 256;
 constexpr int kBf16SmallBM = 128;
 constexpr int kBf16BK = 64;
+// Inner length of a BF16 product: a 256-row block of a plane is addressed by
+// 32-bit byte offsets (rows x 2 kp, the K step's offset included).
+constexpr int64_t kBf16MaxInner = (int64_t)1 << 23;
+static_assert(kBf16BM * 2 * kBf16MaxInner <= (int64_t)1 << 32, "byte offsets in a plane's row block");
 // FP64 p-family GEMM: BM x BM output tile (BM = 128 or 64), K step 16.
 constexpr int kF64BK = 16;
 // Adjoint GEMMs: 128 x 128 (BF16) and 64 x 64 (FP64) output tiles.
