@@ -527,8 +527,8 @@ mt_status maxtimes_set_search_start(int32_t entry);
 int32_t maxtimes_search_start(void);
 
 /*
- * Deferred planes (plain products whose search start the pilot chooses,
- * families of at least five p).  p* is the largest stable p (Sec. 1), so an
+ * Deferred planes (plain products, and on the FP64 path APSP squarings, whose
+ * search start the pilot chooses, families of at least five p).  p* is the largest stable p (Sec. 1), so an
  * entry needs the planes of a smaller p only if it is unstable at every
  * larger one.  With on = 1, the default, the power planes of the two
  * smallest p (BF16 path), or of all but the three largest p (FP64 path, whose
@@ -555,10 +555,11 @@ int32_t maxtimes_deferred_planes(void);
  * Small products (Alg. 5 with the scaled call H' of Sec. 2.1, FP64 path):
  * maxtimes_estimate (and its _noalloc form) computes a product with
  * b * m * k * n <= max_work multiply-adds, options at most MT_FLAG_CLAMP and
- * MT_FLAG_NORM_CORRECT, b <= 65535 and m <= 2^21 in one kernel: each
- * workgroup takes the maxima of its 32 rows of A and 32 columns of B, then
- * forms S_p = A'^p B'^p for its 32 x 32 outputs in FP64 from the largest p
- * down and stops once each output has its p (the general path's seven to
+ * MT_FLAG_NORM_CORRECT, b <= 65535 and fewer than 2^22 tiles of 16 x 16 outputs
+ * per item in one kernel: each workgroup takes the maxima of its 16 rows of A
+ * and 16 columns of B, then forms S_p = A'^p B'^p for its 16 x 16 outputs in
+ * FP64 from the largest p down and stops once each output has its p (the
+ * general path's seven to
  * fourteen launches cost more than such a product's arithmetic).  Same
  * results as the general path up to the order of the FP64 sums; the
  * workspace argument is checked as for the general path and not used.
