@@ -1813,6 +1813,8 @@ hipError_t launch_apsp_gemm(const GemmGeom& g, const FamilyPlan& plan, const Epi
     if (e == hipSuccess && beside) {
         // its entries go straight to the list the tail runs: the sort, whose
         // tiles have handed over nothing, leaves them there
+        // (its name keeps the GEMM's as a prefix: timing by that prefix holds
+        // whichever of the two launches runs the squaring)
         EpiArgs s = a;
         s.sym_mode = kSymOnly;
         s.tail = epi.tail_sorted;
@@ -1822,7 +1824,7 @@ hipError_t launch_apsp_gemm(const GemmGeom& g, const FamilyPlan& plan, const Epi
         gs.tiles_m = gs.tiles_n = g.tiles_m * (kBf16BM / kBf16SmallBM);
         gs.bm = kBf16SmallBM;
         e = launch_gemm<FwdSmallCfg, SelectEpi<FwdSmallCfg, EPI_APSP_X, float, R1>>(gs, 1, plan, s,
-                                                                                "mt_triangle_gemm_bf16", st);
+                                                                                "mt_pfamily_gemm_bf16_triangle", st);
     }
     if (e == hipSuccess && epi.tail) e = launch_tail<EPI_APSP_X, float, R1>(g, 1, plan, a, cap, st);
     return e;
