@@ -559,10 +559,9 @@ int32_t maxtimes_deferred_planes(void);
  * per item in one kernel: each workgroup takes the maxima of its 16 rows of A
  * and 16 columns of B, then forms S_p = A'^p B'^p for its 16 x 16 outputs in
  * FP64 from the largest p down and stops once each output has its p (the
- * general path's seven to
- * fourteen launches cost more than such a product's arithmetic).  Same
- * results as the general path up to the order of the FP64 sums; the
- * workspace argument is checked as for the general path and not used.
+ * general path's seven to fourteen launches cost more than such a product's
+ * arithmetic).  Same results as the general path up to the order of the FP64
+ * sums; the workspace argument is checked as for the general path and not used.
  * max_work = 0 sends every product down the general path; the default is
  * 2^25.  MT_ERR_INVALID_ARG for a negative limit.  Process-wide; not
  * synchronised with calls in flight on other threads.
