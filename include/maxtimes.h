@@ -528,9 +528,9 @@ int32_t maxtimes_search_start(void);
 
 /*
  * Deferred planes (plain products, and on the FP64 path APSP squarings, whose
- * search start the pilot chooses, families of at least five p).  p* is the largest stable p (Sec. 1), so an
- * entry needs the planes of a smaller p only if it is unstable at every
- * larger one.  With on = 1, the default, the power planes of the two
+ * search start the pilot chooses, families of at least five p).  p* is the
+ * largest stable p (Sec. 1), so an entry needs the planes of a smaller p only
+ * if it is unstable at every larger one.  With on = 1, the default, the power planes of the two
  * smallest p (BF16 path), or of all but the three largest p (FP64 path, whose
  * tiny tau puts p* near the largest p), are not written with the others.
  * They are written before the GEMM when the pilot's sampled entries include
